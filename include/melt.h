@@ -76,7 +76,13 @@ typedef enum {
 
 /* Arithmetic of the projection GEMM (all accumulate in FP32; the basis is computed in
  * FP64 and rounded once):
- *   FP32     - FP32 operands (v_mfma_f32_32x32x2_f32)
+ *   FP32     - FP32 operands.  Each is the exact sum of three bfloat16 planes; six of the nine
+ *              plane products run on the bfloat16 matrix cores (the others are below 2^-25 of
+ *              a term), with an error against 64 bits no larger than the FP32 matrix cores'.
+ *              Frames whose samples the planes cannot hold (non-finite, or rounding to infinity
+ *              in bfloat16) are computed with plain FP32 arithmetic.  Geometries that would
+ *              pad the planes' 32-column groups by more than half (hops of a few samples) use
+ *              v_mfma_f32_32x32x2_f32.
  *   BF16     - bfloat16 operands
  *   FP16     - binary16 operands
  *   FP8_E4M3 - OCP E4M3 operands; each frame scaled by 448 / max|x_t| and each basis row by

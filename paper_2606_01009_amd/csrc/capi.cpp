@@ -56,7 +56,8 @@ static void free_plan(Plan *p) {
     void *bufs[] = {p->d_basis32, p->d_pack_f32, p->d_pack_h16, p->d_pack_lo, p->d_pack_f8, p->d_rowscale,
                     p->d_fb_w, p->d_fb_start, p->d_fb_off, p->d_twiddle, p->d_window, p->d_chunks[0],
                     p->d_chunks[1], p->d_nchunks, p->d_pack_dx, p->d_bwd_ws, p->d_bwd_rows, p->d_dct,
-                    p->d_dct_x3, p->d_lmel, p->d_seg32, p->d_col32, p->d_seg16, p->d_col16};
+                    p->d_dct_x3, p->d_lmel, p->d_seg32, p->d_col32, p->d_seg16, p->d_col16,
+                    p->d_segS, p->d_colS, p->d_pack_split};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     delete p;
@@ -134,6 +135,8 @@ melt_status melt_plan_create(const melt_config *cfg, int device, melt_plan *out)
     if (st == MELT_OK) st = alloc(&p->d_pack_h16, RT * p->geo16.n_groups * 64 * 8 * 2);
     if (st == MELT_OK) st = alloc(&p->d_pack_lo, RT * p->geo16.n_groups * 64 * 8 * 2);
     if (st == MELT_OK) st = alloc(&p->d_pack_f8, RT * ((p->N + 63) / 64) * 64 * 32);
+    if (st == MELT_OK && split_planes(*p))
+        st = alloc(&p->d_pack_split, size_t((p->M + 7) / 8) * p->geoS.n_groups * split_planes(*p) * 1024);
     if (st == MELT_OK) st = alloc((void **)&p->d_rowscale, RT * 32 * sizeof(float));
     if (st == MELT_OK) st = alloc((void **)&p->d_nchunks, 2 * sizeof(int));
     if (st == MELT_OK) {

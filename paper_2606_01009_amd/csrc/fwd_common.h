@@ -752,6 +752,24 @@ inline size_t ks_lds_bytes(const Plan &p, int bf) {
     return ks_red_offset(p, bf) + (size_t)((p.row_tiles + rg - 1) / rg) * 2048 * 4;
 }
 
+// Geometries the FP32-MFMA kernels and the 16-bit frame-split kernel take.
+inline bool f32_fits(const Plan &p) {
+    return (size_t)(kBF32 + p.geo32.J - 1) * lds_stride(p.geo32.Hp, 4) * 4 <= (size_t)kMaxLds && p.geo32.n_groups <= 512 &&
+           ((kBF32 + p.geo32.J - 1) * p.H + 255) / 256 <= 136;
+}
+inline bool h16_fs_fits(const Plan &p) {
+    return (size_t)(kBF32 + p.geo16.J - 1) * lds_stride(p.geo16.Hp, 2) * 2 * (prec_split(p) ? 2 : 1) <= (size_t)kMaxLds &&
+           p.geo16.n_groups <= 512;
+}
+
+// Split-plane kernel (melt_split.h): shape for a batch (parts = 0: the geometry does not fit)
+constexpr int kSplitChunk = 128;      // frames per chunk-table entry
+struct SplitShape;
+SplitShape split_shape(const Plan &p, int64_t est_chunks, int64_t n_frames);
+bool split_fits(const Plan &p);
+melt_status launch_melt_split_f32(Plan &p, const FwdTask &t);
+melt_status launch_melt_split_x3(Plan &p, const FwdTask &t);
+
 // per-family launchers (melt_f32.hip, melt_h16.hip, melt_f8.hip)
 melt_status launch_melt_f32(Plan &p, const FwdTask &t, bool warp_specialised);
 enum H16Kind { H16_LDS_DMA = 0, H16_REGISTER_STAGED = 1, H16_FRAME_SPLIT = 2, H16_K_SPLIT = 3, H16_PIPELINED = 4,

@@ -3,6 +3,7 @@
 #include <cstdio>
 #include <mutex>
 #include "fwd_common.h"
+#include "melt_split.h"
 
 namespace melt {
 
@@ -214,6 +215,29 @@ __global__ void k_pack_h16(const float *__restrict__ b32, int M, int N, int H, c
     }
 }
 
+// Planes of the split-plane kernel: [tile][group of 32][plane][lane][8], lane = row lane % 16 of
+// the 16-row tile, columns 8 (lane / 16) ..; rows 4q .. 4q + 3 are (cos, sin) of two Mel bins.
+// kind 0: three bfloat16 planes, 1: two bfloat16 planes, 2: two binary16 planes.
+__global__ void k_pack_split(const float *__restrict__ b32, int M, int N, int H, const int *__restrict__ seg,
+                             const int *__restrict__ col, int NG, int T16, int kind, unsigned short *__restrict__ out) {
+    const int P = kind == 0 ? 3 : 2;
+    const int64_t total = (int64_t)T16 * NG * 512;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+        const int e = i & 511, lane = e >> 3;
+        const int64_t tg = i >> 9;
+        const int g = (int)(tg % NG), t = (int)(tg / NG);
+        const int row = lane & 15, j = seg[g], c = col[g] + 8 * (lane >> 4) + (e & 7);
+        const int mel = split_tile_mel(t, row >> 2, T16) + ((row >> 1) & 1);
+        float v = 0.0f;
+        if (mel < M && c < min(H, N - j * H)) v = b32[(size_t)((row & 1) * M + mel) * N + j * H + c];
+        for (int p = 0; p < P; ++p) {
+            const unsigned short b = kind == 2 ? f32_to_f16_bits(v) : f32_to_bf16_bits(v);
+            out[((size_t)tg * P + p) * 512 + e] = b;
+            v -= kind == 2 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
+        }
+    }
+}
+
 // E4M3 pack of the basis: [rt][group of 64][lane][32 bytes].  blocks = 0: lane half h holds
 // k = 64 g + 32 h + byte (any k order serves a product with unit block scales, as long as the
 // frames use the same).  blocks = 1: the order in which the 32x32x64 MFMA's two 32-k scale
@@ -276,6 +300,8 @@ melt_status pack_tables_upload(Plan &p) {
     if (st == MELT_OK) st = upload_ints(p.geo32.col_of_group, &p.d_col32);
     if (st == MELT_OK) st = upload_ints(p.geo16.seg_of_group, &p.d_seg16);
     if (st == MELT_OK) st = upload_ints(p.geo16.col_of_group, &p.d_col16);
+    if (st == MELT_OK) st = upload_ints(p.geoS.seg_of_group, &p.d_segS);
+    if (st == MELT_OK) st = upload_ints(p.geoS.col_of_group, &p.d_colS);
     return st;
 }
 
@@ -284,6 +310,12 @@ melt_status pack_tables_upload(Plan &p) {
 // host synchronisation (the k-group tables were uploaded at plan creation).
 melt_status pack_basis(Plan &p, hipStream_t s) {
     const int RT = p.row_tiles;
+    if (split_planes(p))
+        k_pack_split<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, p.d_segS, p.d_colS, p.geoS.n_groups, (p.M + 7) / 8,
+                                         p.cfg.precision == MELT_PREC_FP32     ? 0
+                                         : p.cfg.precision == MELT_PREC_BF16X3 ? 1
+                                                                               : 2,
+                                         (unsigned short *)p.d_pack_split);
     switch (p.cfg.precision) {
     case MELT_PREC_FP32:
         k_pack_f32<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, p.d_seg32, p.d_col32, p.geo32.n_groups, RT,
@@ -374,17 +406,67 @@ melt_status launch_frame_offsets(const int64_t *d_off, int n_clips, int N, int H
 //   FP8 with 32-sample block scales  producer/consumer block-scaled kernel, then the
 //              one-buffer block-scaled kernel with 160- and 128-frame chunks
 enum VariantKind { V_F32_WS, V_F32_FS, V_H16_PP, V_H16_AS, V_H16_AP, V_H16_RS, V_H16_KS, V_H16_FS, V_F8_AS, V_F8_RS,
-                   V_F8B_AS, V_F8B_PC, V_H16_PC, V_F8_PC };
+                   V_F8B_AS, V_F8B_PC, V_H16_PC, V_F8_PC, V_SPLIT };
 struct Variant {
     VariantKind kind;
     int bf;          // frames per chunk
     int nbuf = 1;    // FP32 span buffers of the direct-to-LDS 16-bit kernel
 };
 
+// Shape of the split-plane kernel for a batch: the one with the fewest cycles in the model
+//   rounds over the CUs x (k-groups x RT x max(MFMA, L1) + fixed)
+// where a k-group of a tile costs FT NP MFMAs of 16 cycles on its SIMD or, if that is more, P KB
+// for each of the four multiply waves through the CU's 64-byte L1 port; the fixed part is an
+// item's barriers, hand-over and first fragment reads.  128-frame items are the cheapest per
+// frame; 64-frame ones (four row groups) serve rows too long for LDS at 128, and 32-frame ones
+// spread a call of few frames over the chip.
+SplitShape split_shape(const Plan &p, int64_t est_chunks, int64_t n_frames) {
+    const int P = split_planes(p), NP = P == 3 ? 6 : 3, T16 = (p.M + 7) / 8;
+    const Geometry &g = p.geoS;
+    static const struct {
+        int wf, ft, rt_max, pv[2];
+    } families[3] = {{2, 4, 8, {18, 0}}, {1, 4, 4, {18, 18}}, {2, 1, 2, {10, 10}}};
+    SplitShape best{0, 0, 0, 0, 0};
+    double best_cost = 1e300;
+    if (P == 0) return best;
+    for (int i = 0; i < 3; ++i) {
+        const auto &f = families[i];
+        SplitShape h{f.wf, f.ft, 0, 0, 0};
+        const int sf = split_sf(h), wr = 4 / f.wf;
+        const int vectors = (sf + g.J - 1) * (g.Hp / 4);
+        const int wide = i == 0 ? (P == 3 ? 26 : 34) : f.pv[1];
+        h.pv = vectors <= f.pv[0] * 256 ? f.pv[0] : wide;
+        if (vectors > h.pv * 256 || split_lds(p, P, h) > (size_t)kMaxLds) continue;
+        const int64_t subs = n_frames / sf + std::max<int64_t>(est_chunks - n_frames / kSplitChunk, 0);
+        for (int parts = (T16 + wr * f.rt_max - 1) / (wr * f.rt_max); parts <= (T16 + wr - 1) / wr; ++parts) {
+            h.parts = parts;
+            h.rt = (T16 + wr * parts - 1) / (wr * parts);
+            if (h.rt == 7) h.rt = 8;
+            const int64_t rounds = (std::max<int64_t>(subs, 1) * parts + p.cu_count - 1) / p.cu_count;
+            const double cost = (double)rounds * (std::max(f.ft * NP * 16, P * 64) * (double)g.n_groups * h.rt + 4500.0);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = h;
+            }
+        }
+    }
+    return best;
+}
+
+// The split-plane kernel takes a plan if a shape fits LDS and its k-groups of 32 do not pad the
+// frame by more than half (short hops do: at hop 8 three of four columns would be padding),
+// where FP32 MFMA on k-groups of 8 is the faster product again.
+bool split_fits(const Plan &p) {
+    return split_planes(p) && p.geoS.n_groups * 32 <= p.N + p.N / 2 + 32 && p.geoS.n_groups <= 512 &&
+           split_shape(p, 1 << 20, (int64_t)kSplitChunk << 20).parts > 0;
+}
+
 static std::vector<Variant> variant_list(const Plan &p) {
     std::vector<Variant> v;
     switch (p.cfg.precision) {
     case MELT_PREC_FP32:
+        // (the geometries the FP32-MFMA kernels refuse stay refused)
+        if (f32_fits(p) && split_fits(p)) v.push_back({V_SPLIT, kSplitChunk});
         v.push_back({V_F32_WS, kBF32});
         v.push_back({V_F32_FS, kBF32});
         break;
@@ -474,6 +556,7 @@ static std::vector<Variant> variant_list(const Plan &p) {
         if (pc_x3 && !pc_x3_first) v.push_back({V_H16_PC, 64});
         // frame-split: the fallback for every 16-bit precision (the split ones only where no
         // register-tile kernel applies)
+        if (x3 && v.empty() && h16_fs_fits(p) && split_fits(p)) v.push_back({V_SPLIT, kSplitChunk});
         if (!x3 || v.empty()) v.push_back({V_H16_FS, kBF32});
     }
     }
@@ -503,6 +586,8 @@ const char *forward_variant_name(const Plan &p, int i) {
     if (i < 0 || i >= p.n_variants) return "none";
     const Variant v = variant_at(p, i);
     const char *k = v.kind == V_H16_PP   ? (v.nbuf == 2 ? "h16-producer-consumer-2span" : "h16-producer-consumer")
+                    : v.kind == V_SPLIT  ? (p.cfg.precision == MELT_PREC_FP32 ? "f32-split-planes-frame-split"
+                                                                              : "h16-split-planes-frame-split")
                     : v.kind == V_F32_WS ? "f32-frame-split-warp-specialised"
                     : v.kind == V_F32_FS ? "f32-frame-split"
                     : v.kind == V_H16_AS ? (v.nbuf == 2 ? "h16-row-split-lds-dma2" : "h16-row-split-lds-dma")
@@ -547,6 +632,7 @@ melt_status launch_melt_table(Plan &p, int variant, const Chunk *tab, const int 
     const FwdTask t{tab, n_tab, est_chunks, n_frames, d_wave, d_out, d_proj, s};
     const Variant v = variant_at(p, variant);
     switch (v.kind) {
+    case V_SPLIT: return p.cfg.precision == MELT_PREC_FP32 ? launch_melt_split_f32(p, t) : launch_melt_split_x3(p, t);
     case V_F32_WS: return launch_melt_f32(p, t, true);
     case V_F32_FS: return launch_melt_f32(p, t, false);
     case V_H16_PP: return launch_melt_h16(p, t, H16_PIPELINED, v.bf, v.nbuf);

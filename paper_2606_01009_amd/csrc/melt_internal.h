@@ -60,9 +60,12 @@ struct Plan {
     void *d_pack_lo = nullptr;         // BF16x3 low part
     void *d_pack_f8 = nullptr;         // FP8 E4M3 packed basis
     float *d_rowscale = nullptr;       // FP8 per-row scales (packed row order)
+    void *d_pack_split = nullptr;      // operand planes in 16-row fragments (FP32 and split precisions)
     Geometry geo32, geo16, geo8;
+    Geometry geoS;                     // k-groups of 32 (split-plane kernel)
     int *d_seg32 = nullptr, *d_col32 = nullptr;   // segment / first column of each k-group (device)
     int *d_seg16 = nullptr, *d_col16 = nullptr;
+    int *d_segS = nullptr, *d_colS = nullptr;
     // comparator (FFT + CSR filterbank)
     float *d_fb_w = nullptr;           // filter weights, concatenated per Mel bin
     int *d_fb_start = nullptr;         // first bin of each filter
@@ -107,6 +110,10 @@ struct Plan {
 // compensated (split) 16-bit precisions: a high and a low part per operand, three products
 inline bool prec_split(const Plan &p) {
     return p.cfg.precision == MELT_PREC_BF16X3 || p.cfg.precision == MELT_PREC_FP16X3;
+}
+// precisions the split-plane kernel runs, and the planes of an operand there
+inline int split_planes(const Plan &p) {
+    return p.cfg.precision == MELT_PREC_FP32 ? 3 : prec_split(p) ? 2 : 0;
 }
 // 16-bit precisions whose operands are binary16
 inline bool prec_f16(const Plan &p) {

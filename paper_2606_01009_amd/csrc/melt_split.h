@@ -1,0 +1,558 @@
+// MelT forward on split operands: every FP32 value is the sum of P 16-bit planes and the
+// projection runs as the plane products that matter, on the 16-bit matrix cores with FP32
+// accumulation (Eq. dmp_projection, Eq. dmp_matrix_energy, Eq. meltf).
+//
+//   Split3BF16 (FP32)  three bfloat16 planes hold all 24 significand bits of an FP32 value
+//                      (each residual is exact), and bfloat16 has FP32's exponent range; of
+//                      the nine products the six down to 2^-16 relative are kept, so a term is
+//                      off by about 2^-26, below the FP32 rounding of the basis itself
+//   Split2BF16, Split2F16 (BF16X3, FP16X3)  hi and lo planes, three products
+//
+// What bounds it: the matrix cores (P = 3: six products, 147 GFLOP on 64 x 30 s at N = 400,
+// M = 80), then the L1 path the basis fragments stream through.  The layout follows from
+// that: a multiply wave owns FT tiles of 16 frames x RT tiles of 16 basis rows, so a basis
+// fragment of P KB read through L1 feeds FT NP MFMAs (4 x 6 x 16 cycles against 48 of the
+// shared L1 port) and a frame fragment read from LDS feeds RT NP.  16x16x32 tiles rather than
+// 32x32x16: 80 Mel bins are ten of them, five for each of the two row halves, where 32-row
+// tiles split 3 + 2.
+//
+// One workgroup per CU, 8 waves: 4 multiply (WF frame groups x 4 / WF row groups, one per
+// SIMD) and 4 stage.  The stagers load the next item's samples and split them in registers
+// while the multiply waves run; between the two barriers of an item they write the planes to
+// LDS while the multiply waves empty their accumulators.
+//
+// Measured (whole calls, same box): FP32 64 x 30 s, N 400, M 80: 213.5 us on FP32 MFMA, 123.4 us
+// here (200 TFLOP/s of the method, 1.2 PFLOP/s of products); FP32 ragged 512 clips, N 512,
+// M 128: 2.11 ms -> 1.00 ms (1.49 PFLOP/s of products); FP16X3 ragged, N 1024, M 128: 4.0 ms on
+// the frame-split kernel with 128-frame chunks -> 0.84-0.92 ms.  Relative error of the log-Mel
+// rows against 64 bits on the same calls: 4.5e-7 -> 3.5e-7, 5.6e-7 -> 4.1e-7, 7.2e-7 -> 5.4e-7.
+#pragma once
+#include <type_traits>
+#include "fwd_common.h"
+
+namespace melt {
+
+typedef unsigned split_u32x4 __attribute__((ext_vector_type(4)));
+
+// Four FP32 values -> P planes of four 16-bit values (two dwords each).
+struct Split3BF16 {
+    static constexpr int P = 3, NP = 6;
+    // plane products (basis plane, frame plane), frame plane 2 first: the k-loop refills the
+    // frame fragments plane by plane behind their last use, in this order
+    static constexpr int pa[6] = {0, 1, 0, 2, 1, 0}, pb[6] = {2, 1, 1, 0, 0, 0};
+    static constexpr int last_of_plane[3] = {5, 2, 0};      // index of the last product of frame plane p
+    __device__ static void split(f32x4 v, unsigned (&w)[6]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float x = v[2 * h], y = v[2 * h + 1];
+            const unsigned b0 = pk_bf16(x, y);
+            const float x1 = x - __builtin_bit_cast(float, b0 << 16), y1 = y - __builtin_bit_cast(float, b0 & 0xffff0000u);
+            const unsigned b1 = pk_bf16(x1, y1);
+            const float x2 = x1 - __builtin_bit_cast(float, b1 << 16), y2 = y1 - __builtin_bit_cast(float, b1 & 0xffff0000u);
+            w[h] = b0;
+            w[2 + h] = b1;
+            w[4 + h] = pk_bf16(x2, y2);
+        }
+    }
+    __device__ static f32x4 mma(split_u32x4 a, split_u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+struct Split2BF16 {
+    static constexpr int P = 2, NP = 3;
+    static constexpr int pa[3] = {0, 1, 0}, pb[3] = {1, 0, 0};
+    static constexpr int last_of_plane[2] = {2, 0};
+    __device__ static void split(f32x4 v, unsigned (&w)[4]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float x = v[2 * h], y = v[2 * h + 1];
+            const unsigned b0 = pk_bf16(x, y);
+            w[h] = b0;
+            w[2 + h] = pk_bf16(x - __builtin_bit_cast(float, b0 << 16), y - __builtin_bit_cast(float, b0 & 0xffff0000u));
+        }
+    }
+    __device__ static f32x4 mma(split_u32x4 a, split_u32x4 b, f32x4 c) { return Split3BF16::mma(a, b, c); }
+};
+struct Split2F16 {
+    static constexpr int P = 2, NP = 3;
+    static constexpr int pa[3] = {0, 1, 0}, pb[3] = {1, 0, 0};
+    static constexpr int last_of_plane[2] = {2, 0};
+    __device__ static void split(f32x4 v, unsigned (&w)[4]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float x = v[2 * h] * kF16x3Scale, y = v[2 * h + 1] * kF16x3Scale;
+            const unsigned b0 = pk_f16(x, y);
+            const cv_f32x2 r = __builtin_convertvector(__builtin_bit_cast(cv_f16x2, b0), cv_f32x2);
+            w[h] = b0;
+            w[2 + h] = pk_f16(x - r[0], y - r[1]);
+        }
+    }
+    __device__ static f32x4 mma(split_u32x4 a, split_u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    }
+};
+
+// Geometry of one launch, beside FwdArgs (whose S is the LDS row stride in 16-bit elements:
+// the P planes of a hop-block row side by side, then 16 bytes so that the stride is an odd
+// multiple of 16 bytes and the 16-byte reads of 16 consecutive rows hit distinct banks).
+struct SplitGeo {
+    int NG, GH;            // k-groups of 32: in all, and per full hop segment
+    int T16;               // tiles of 16 basis rows (8 Mel bins)
+    int nsub, parts;       // items per chunk: frame parts x row parts
+    const float *basis;    // the FP32 basis [2M][N]
+    int N;
+    int half_tail;         // the last k-group holds at most 16 columns of the frame
+};
+
+// First Mel bin of lane quarter q of 16-row tile t.  The accumulator of a 16x16 tile holds in
+// quarter q rows 4q .. 4q + 3, (cos, sin) of two bins.  Two neighbouring tiles share 16 bins,
+// four consecutive ones per quarter (two from each tile), so that a quarter stores 16 bytes;
+// the last tile of an odd count has its 8 bins to itself.
+__host__ __device__ __forceinline__ int split_tile_mel(int t, int q, int T16) {
+    return (T16 & 1) && t == T16 - 1 ? 8 * t + 2 * q : 16 * (t >> 1) + 4 * q + 2 * (t & 1);
+}
+
+// The stagers' share of one item: PV vectors of four columns per thread of 256, vector u of a
+// hop-block row-major walk (row u / VR, columns 4 (u % VR) ..), split into planes in registers.
+// Columns at or past the hop, and samples at or past the clip end, are zero.
+template <class Op, int PV>
+__device__ __forceinline__ void split_load(const FwdArgs &a, int64_t start, int64_t clip_end, int nrows, int lt,
+                                           float inv_vr, unsigned (&w)[PV][2 * Op::P]) {
+    // Every load is unconditional, so that all of a batch are in flight together.  Where the whole
+    // span (and the 3 samples a row's last vector may reach past it) lies in the clip: 16-byte
+    // loads, columns past the hop cleared afterwards.  At a clip's end: 4-byte loads, with an
+    // offset past the descriptor, which reads as zero, for columns and samples that do not exist.
+    const int span = nrows * a.H, VR = a.Hp >> 2;
+    const int64_t left = clip_end - start;
+    const bool padded = a.Hp != a.H;
+    const bool inside = nrows > 0 && left >= span + (padded ? 3 : 0);
+    const int records = (int)(inside ? span + (padded ? 3 : 0) : left < 0 ? 0 : left < span ? left : span);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void *)(a.wave + start), (short)0, records * 4, 0x00020000);
+    asm volatile("" : "+v"(lt));        // addresses formed here, not kept from item to item
+    // at most 14 vectors in flight, so that the raw and the split values of all PV fit the registers
+    constexpr int NB = PV > 14 ? 2 : 1, PB = (PV + NB - 1) / NB;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        f32x4 raw[PB];
+        auto at = [&](int v, int &r) {       // column of vector b PB + v; r: its row
+            const int u = lt + (b * PB + v) * 256;
+            r = (int)(((float)u + 0.5f) * inv_vr);
+            const int cv = u - r * VR;
+            r += (cv >= VR) - (cv < 0);
+            return 4 * (u - r * VR);
+        };
+        if (inside) {
+#pragma unroll
+            for (int v = 0; v < PB; ++v) {
+                int r;
+                const int col = at(v, r);
+                const int o = r < nrows && col < a.H ? r * a.H + col : 0;
+                raw[v] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, o * 4, 0, 0));
+            }
+            if (padded) {
+#pragma unroll
+                for (int v = 0; v < PB; ++v) {
+                    int r;
+                    const int col = at(v, r);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) raw[v][e] = col + e < a.H ? raw[v][e] : 0.0f;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < PB; ++v) {
+                int r;
+                const int col = at(v, r);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int o = r * a.H + col + e;
+                    const int off = r < nrows && col + e < a.H && o < records ? o * 4 : 0x7ffffff0;
+                    raw[v][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < PB; ++v)
+            if (b * PB + v < PV) Op::split(raw[v], w[b * PB + v < PV ? b * PB + v : 0]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+template <class Op, int PV>
+__device__ __forceinline__ void split_write(const FwdArgs &a, int nrows, int lt, float inv_vr,
+                                            const unsigned (&w)[PV][2 * Op::P], unsigned short *rows) {
+    const int VR = a.Hp >> 2;
+    // addresses formed here, not carried across the multiply phase
+    asm volatile("" : "+v"(lt));
+#pragma unroll
+    for (int v = 0; v < PV; ++v) {
+        const int u = lt + v * 256;
+        int r = (int)(((float)u + 0.5f) * inv_vr);
+        int cv = u - r * VR;
+        r += (cv >= VR) - (cv < 0);
+        if (r < nrows) {
+            unsigned short *d = rows + r * a.S + 4 * (u - r * VR);
+#pragma unroll
+            for (int p = 0; p < Op::P; ++p) *(uint2 *)(d + p * a.Hp) = uint2{w[v][2 * p], w[v][2 * p + 1]};
+        }
+    }
+}
+
+// One output recomputed with plain FP32 arithmetic: the planes of an infinity (or of a value
+// that rounds to one in bfloat16) are inf and -inf or NaN, so where the split projection is not
+// finite it is taken again without splitting.
+__device__ __forceinline__ void split_redo(const FwdArgs &a, const SplitGeo &g, int64_t first, int64_t row, int mel) {
+    const float *x = a.wave + first, *wr = g.basis + (size_t)mel * g.N, *wi = wr + (size_t)a.M * g.N;
+    float R = 0.0f, I = 0.0f;
+#pragma unroll 1
+    for (int n = 0; n < g.N; ++n) {
+        R = fmaf(x[n], wr[n], R);
+        I = fmaf(x[n], wi[n], I);
+    }
+    const float S = R * R + I * I;
+    a.out[row * a.M + mel] = a.out_kind == MELT_OUT_LOG_POWER       ? out_map_k<MELT_OUT_LOG_POWER>(S, a.eps)
+                             : a.out_kind == MELT_OUT_LOG_MAGNITUDE ? out_map_k<MELT_OUT_LOG_MAGNITUDE>(S, a.eps)
+                             : a.out_kind == MELT_OUT_POWER         ? S
+                                                                    : sqrtf(S);
+    if (a.proj) {
+        a.proj[row * (2 * a.M) + 2 * mel] = R;
+        a.proj[row * (2 * a.M) + 2 * mel + 1] = I;
+    }
+}
+
+// One item of a workgroup: frames [f0, f0 + nf) of a chunk.
+struct SplitItem {
+    int64_t start, clip_end, out_row;
+    int nf;
+};
+__device__ __forceinline__ SplitItem split_item(const FwdArgs &a, const SplitGeo &g, int w, int SF) {
+    const int ci = w / (g.nsub * g.parts);
+    const int f0 = ((w - ci * g.nsub * g.parts) / g.parts) * SF;
+    // through the scalar cache: a vector load's wait would also drain the wave's output stores
+    uint4 lo, hi;
+    load_chunk_scalar(a.chunks, ci, lo, hi);
+    const int64_t start = (int64_t)(((uint64_t)lo.y << 32) | lo.x), end = (int64_t)(((uint64_t)lo.w << 32) | lo.z);
+    const int64_t row = (int64_t)(((uint64_t)hi.y << 32) | hi.x);
+    const int nf = min(SF, (int)hi.z - f0);
+    return {start + (int64_t)f0 * a.H, end, row + f0, nf > 0 ? nf : 0};
+}
+
+// Output values of the two bins of each tile of one frame.
+template <int KIND, int RT>
+__device__ __forceinline__ void split_map(float eps, const f32x4 (&acc)[RT], float (&v)[2 * RT]) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const f32x4 y = acc[r];
+        v[2 * r] = out_map_k<KIND>(y[0] * y[0] + y[1] * y[1], eps);
+        v[2 * r + 1] = out_map_k<KIND>(y[2] * y[2] + y[3] * y[3], eps);
+    }
+}
+
+// Accumulators -> output rows.  tile[]: pairs (r, r + 1) start at even tiles.
+template <class Op, int FT, int RT>
+__device__ __forceinline__ void split_store(const FwdArgs &a, const SplitGeo &g, const SplitItem &it, int fbase, int lane,
+                                            const int (&tile)[RT], f32x4 (&acc)[FT][RT]) {
+    asm volatile("" : "+v"(lane));      // addresses formed per item, not kept across the multiply phase
+    const int q = lane >> 4, f0 = fbase + (lane & 15);
+    if constexpr (std::is_same<Op, Split2F16>::value) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) acc[f][r] *= 1.0f / kF16x3Scale;      // exact
+    }
+    if (a.proj) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const int m0 = split_tile_mel(tile[r], q, g.T16);
+#pragma unroll
+            for (int f = 0; f < FT; ++f) {
+                const int64_t row = it.out_row + f0 + 16 * f;
+                if (f0 + 16 * f >= it.nf || row >= a.n_frames || tile[r] >= g.T16) continue;
+                float *p = a.proj + row * (2 * a.M) + 2 * m0;
+                if (m0 + 1 < a.M) {
+                    *(float2 *)p = float2{acc[f][r][0], acc[f][r][1]};
+                    *(float2 *)(p + 2) = float2{acc[f][r][2], acc[f][r][3]};
+                } else if (m0 < a.M) {
+                    *(float2 *)p = float2{acc[f][r][0], acc[f][r][1]};
+                }
+            }
+        }
+    }
+    float probe = 0.0f;                 // stays 0 while every output is finite
+    // every bin of the wave's tiles exists and rows are whole 16-byte vectors: no edge tests
+    const bool whole = (a.M & 7) == 0 && max(tile[0], tile[RT - 1]) < g.T16 && tile[RT > 1 ? RT - 2 : 0] < g.T16;
+#pragma unroll
+    for (int f = 0; f < FT; ++f) {
+        const int64_t row = it.out_row + f0 + 16 * f;
+        if (f0 + 16 * f >= it.nf || row >= a.n_frames) continue;
+        float *o = a.out + row * a.M;
+        float v[2 * RT];
+        switch (a.out_kind) {
+        case MELT_OUT_LOG_POWER: split_map<MELT_OUT_LOG_POWER, RT>(a.eps, acc[f], v); break;
+        case MELT_OUT_LOG_MAGNITUDE: split_map<MELT_OUT_LOG_MAGNITUDE, RT>(a.eps, acc[f], v); break;
+        case MELT_OUT_POWER: split_map<MELT_OUT_POWER, RT>(a.eps, acc[f], v); break;
+        default: split_map<MELT_OUT_MAGNITUDE, RT>(a.eps, acc[f], v); break;
+        }
+#pragma unroll
+        for (int r = 0; r < RT; r += 2) {
+            const bool pair = r + 1 < RT;                       // known when unrolled
+            const int r1 = pair ? r + 1 : r;
+            const int m0 = split_tile_mel(tile[r], q, g.T16);
+            const float v0 = v[2 * r], v1 = v[2 * r + 1], v2 = v[2 * r1], v3 = v[2 * r1 + 1];
+            if constexpr (Op::P == 3) probe = fmaf(v0 + v1 + v2 + v3, 0.0f, probe);
+            if (whole) {
+                if (pair) *(f32x4 *)(o + m0) = f32x4{v0, v1, v2, v3};
+                else *(float2 *)(o + m0) = float2{v0, v1};
+            } else if (tile[r] < g.T16) {
+                if (m0 < a.M) o[m0] = v0;
+                if (m0 + 1 < a.M) o[m0 + 1] = v1;
+                if (pair && tile[r1] < g.T16) {
+                    if (m0 + 2 < a.M) o[m0 + 2] = v2;
+                    if (m0 + 3 < a.M) o[m0 + 3] = v3;
+                }
+            }
+        }
+    }
+    if constexpr (Op::P == 3) {
+        if (__any(!(probe == 0.0f))) {
+            uint64_t redo = 0;
+#pragma unroll
+            for (int f = 0; f < FT; ++f)
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const float R = acc[f][r][2 * k], I = acc[f][r][2 * k + 1];
+                        if (!((R * R + I * I) * 0.0f == 0.0f)) redo |= uint64_t(1) << ((f * RT + r) * 2 + k);
+                    }
+            while (redo) {
+                const int i = __builtin_ctzll(redo);
+                redo &= redo - 1;
+                const int k = i & 1, f = (i >> 1) / RT, r = (i >> 1) - f * RT;
+                int t = 0;
+#pragma unroll
+                for (int rr = 0; rr < RT; ++rr)
+                    if (rr == r) t = tile[rr];
+                const int fl = f0 + 16 * f, mel = split_tile_mel(t, q, g.T16) + k;
+                if (fl < it.nf && it.out_row + fl < a.n_frames && t < g.T16 && mel < a.M)
+                    split_redo(a, g, it.start + (int64_t)fl * a.H, it.out_row + fl, mel);
+            }
+        }
+    }
+}
+
+// Depth of the basis ring in tiles: the fragments of the tile D steps ahead are loaded as soon
+// as a tile's MFMAs have read theirs.  RT for 3 to 6 tiles (one k-group ahead: 384 cycles per
+// tile and more cover an L2 access), half of 6 and 8 (registers), and several k-groups for the
+// short steps of one or two tiles.
+constexpr int split_ring(int FT, int RT) { return RT >= 8 ? 4 : RT == 6 ? 3 : RT >= 3 ? RT : FT >= 4 ? 4 : 8; }
+
+template <class Op, int FT, int RT, int WF, int PV>
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void k_melt_split(FwdArgs a, SplitGeo g, const split_u32x4 *__restrict__ bpack) {
+    extern __shared__ __attribute__((aligned(16))) unsigned short rows[];
+    constexpr int P = Op::P, NP = Op::NP, SF = WF * FT * 16;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nitems = *a.n_chunks * g.nsub * g.parts;
+    const int G = gridDim.x;                       // a multiple of parts: the row part is the workgroup's
+    int w = blockIdx.x;
+    if (wid >= 4) {
+        const int lt = (int)threadIdx.x - 256;
+        const float inv_vr = 4.0f / (float)a.Hp;
+        unsigned pl[PV][2 * P];
+        SplitItem it{};
+        if (w < nitems) {
+            it = split_item(a, g, w, SF);
+            split_load<Op, PV>(a, it.start, it.clip_end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
+            split_write<Op, PV>(a, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl, rows);
+        }
+        __syncthreads();                           // rows of the first item ready
+        for (; w < nitems; w += G) {
+            const bool more = w + G < nitems;
+            if (more) {
+                it = split_item(a, g, w + G, SF);
+                split_load<Op, PV>(a, it.start, it.clip_end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
+            }
+            // split before the barrier, not between the two
+#pragma unroll
+            for (int v = 0; v < PV; ++v)
+#pragma unroll
+                for (int k = 0; k < 2 * P; ++k) asm volatile("" : "+v"(pl[v][k]));
+            __syncthreads();                       // A: the multiply waves are done with the rows
+            if (more) split_write<Op, PV>(a, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl, rows);
+            __syncthreads();                       // B: rows of the next item ready
+        }
+        return;
+    }
+    const int wf = wid % WF, wr = wid / WF;
+    constexpr int WR = 4 / WF, D = split_ring(FT, RT), U = D > RT ? D / RT : 1;
+    static_assert((U * RT) % D == 0, "the ring's slots repeat every U k-groups");
+    const int t0 = ((w % g.parts) * WR + wr) * RT;
+    int tile[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        // an odd tile count that starts at an odd tile keeps its unpaired tile for last
+        tile[r] = (RT & 1) && (t0 & 1) ? (r == RT - 1 ? t0 : t0 + 1 + r) : t0 + r;
+    }
+    const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)bpack, (short)0, g.T16 * g.NG * P * 1024, 0x00020000);
+    const int voff = lane * 16;
+    int toff[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) toff[r] = min(tile[r], g.T16 - 1) * g.NG * (P * 1024);
+    split_u32x4 A[D][P], B[FT][P];
+    auto load_a = [&](int slot, int r, int grp) {
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            A[slot][p] = __builtin_bit_cast(
+                split_u32x4, __builtin_amdgcn_raw_buffer_load_b128(brs, voff + p * 1024, toff[r] + grp * (P * 1024), 0));
+    };
+#pragma unroll
+    for (int s = 0; s < D; ++s) load_a(s, s % RT, min(s / RT, g.NG - 1));
+    __syncthreads();                               // rows of the first item ready
+    const int fbase = wf * FT * 16;
+    const int la0 = (fbase + (lane & 15)) * a.S + 8 * (lane >> 4);
+    for (; w < nitems; w += G) {
+        const SplitItem it = split_item(a, g, w, SF);
+        // two planes: a k-group's three products are summed on their own and added once, behind the
+        // next tile's first MFMAs (a third of the roundings at the running sum's magnitude)
+        f32x4 acc[FT][RT], sum[2][FT];
+#pragma unroll
+        for (int f = 0; f < FT; ++f)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) acc[f][r] = f32x4{};
+        auto load_b = [&](int p, int at) {
+#pragma unroll
+            for (int f = 0; f < FT; ++f) B[f][p] = *(const split_u32x4 *)(rows + at + f * 16 * a.S + p * a.Hp);
+        };
+        if (fbase < it.nf) {
+#pragma unroll
+            for (int p = P - 1; p >= 0; --p) load_b(p, la0);
+            int col = 0, at = la0;                 // k-group within its segment, its LDS offset
+            for (int g0 = 0; g0 < g.NG; g0 += U) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int grp = g0 + u;
+                    if (grp >= g.NG) break;
+                    // offset of the next k-group's columns (past the last: any valid ones)
+                    int nat = at + 32;
+                    if (++col == g.GH) {
+                        col = 0;
+                        nat = at + a.S - (g.GH - 1) * 32;
+                    }
+                    if (grp + 1 >= g.NG) nat = la0;
+                    at = nat;
+                    if (P == 2 && g.half_tail && grp + 1 == g.NG && lane >= 32) {
+                        // columns 16 .. 31 are samples after the frame (their weights are zero):
+                        // one that overflows binary16 must not reach it
+#pragma unroll
+                        for (int f = 0; f < FT; ++f)
+#pragma unroll
+                            for (int p = 0; p < P; ++p) B[f][p] = split_u32x4{};
+                    }
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) {
+                        const int slot = (u * RT + r) % D;
+#pragma unroll
+                        for (int k = 0; k < NP; ++k) {
+#pragma unroll
+                            for (int f = 0; f < FT; ++f) {
+                                if constexpr (P == 3)
+                                    acc[f][r] = Op::mma(A[slot][Op::pa[k]], B[f][Op::pb[k]], acc[f][r]);
+                                else
+                                    sum[r & 1][f] = Op::mma(A[slot][Op::pa[k]], B[f][Op::pb[k]], k ? sum[r & 1][f] : f32x4{});
+                            }
+                            if (P == 2 && k == 0 && r > 0) {
+#pragma unroll
+                                for (int f = 0; f < FT; ++f) acc[f][r - 1] += sum[(r - 1) & 1][f];
+                            }
+                            if (r == RT - 1) {
+#pragma unroll
+                                for (int p = 0; p < P; ++p)
+                                    if (Op::last_of_plane[p] == k) {
+                                        __builtin_amdgcn_sched_barrier(0);
+                                        load_b(p, nat);
+                                        __builtin_amdgcn_sched_barrier(0);
+                                    }
+                            }
+                        }
+                        // the slot's next tile: D steps on, wrapping to the next item's first
+                        const int ahead = r + D, dg = ahead / RT, rr = ahead - dg * RT;
+                        int ng = grp + dg;
+                        if (ng >= g.NG) ng -= g.NG;
+                        if (ng >= g.NG) ng = 0;
+                        __builtin_amdgcn_sched_barrier(0);
+                        load_a(slot, rr, ng);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (P == 2) {
+#pragma unroll
+                        for (int f = 0; f < FT; ++f) acc[f][RT - 1] += sum[(RT - 1) & 1][f];
+                    }
+                }
+            }
+            // the ring holds the tiles of steps NG RT .. NG RT + D - 1; where NG is no multiple of U
+            // they sit in rotated slots: refill from the first step
+            if (U > 1 && g.NG % U != 0) {
+#pragma unroll
+                for (int s = 0; s < D; ++s) load_a(s, s % RT, min(s / RT, g.NG - 1));
+            }
+        }
+        __syncthreads();                           // A: every row read; the stagers may overwrite
+        if (fbase < it.nf) split_store<Op, FT, RT>(a, g, it, fbase, lane, tile, acc);
+        __syncthreads();                           // B: rows of the next item ready
+    }
+}
+
+// ------------------------------------------------------------------ launch
+
+// A compiled shape: WF waves along the frames, FT frame tiles and RT row tiles per wave, PV
+// staging vectors per thread; `parts` row parts of 4 / WF RT tiles each.
+struct SplitShape {
+    int wf, ft, rt, pv, parts;
+};
+template <class Op, int FT, int RT, int WF, int PV>
+melt_status launch_split_k(const FwdArgs &a, const SplitGeo &g, const void *pack, size_t lds, int grid, hipStream_t s) {
+    allow_lds(k_melt_split<Op, FT, RT, WF, PV>);
+    k_melt_split<Op, FT, RT, WF, PV><<<grid, 512, lds, s>>>(a, g, (const split_u32x4 *)pack);
+    return hip_check(hipGetLastError(), "melt split launch");
+}
+
+// frames and LDS of a shape
+inline int split_sf(const SplitShape &h) { return h.wf * h.ft * 16; }
+inline size_t split_lds(const Plan &p, int P, const SplitShape &h) {
+    return (size_t)(split_sf(h) + p.geoS.J - 1) * (P * p.geoS.Hp + 8) * 2;
+}
+
+template <class Op>
+melt_status launch_split(Plan &p, const FwdTask &t) {
+    constexpr int P = Op::P;
+    const SplitShape h = split_shape(p, t.est_chunks, t.n_frames);
+    if (h.parts == 0) return set_error(MELT_E_UNSUPPORTED, "split kernel: unsupported geometry");
+    const Geometry &geo = p.geoS;
+    FwdArgs a = make_args(p, geo, P * geo.Hp + 8, t);
+    const int tail = p.N - (geo.J - 1) * p.H;
+    const int sf = split_sf(h);
+    const SplitGeo g{geo.n_groups, geo.Hp / 32, (p.M + 7) / 8, kSplitChunk / sf, h.parts, p.d_basis32, p.N,
+                     tail < p.H && tail % 32 > 0 && tail % 32 <= 16};
+    const int64_t items = t.est_chunks * g.nsub * g.parts;
+    const int grid = std::max(persistent_grid(p, items, 1) / h.parts, 1) * h.parts;
+    const size_t lds = split_lds(p, P, h);
+    const void *pk = p.d_pack_split;
+    const hipStream_t s = t.stream;
+    constexpr int PW = P == 3 ? 26 : 34;       // the wide staging of 128-frame items
+#define SPLIT_CASE(FT, RT, WF, PV) \
+    if (h.ft == FT && h.rt == RT && h.wf == WF && h.pv == PV) return launch_split_k<Op, FT, RT, WF, PV>(a, g, pk, lds, grid, s);
+    SPLIT_CASE(4, 1, 2, 18) SPLIT_CASE(4, 2, 2, 18) SPLIT_CASE(4, 3, 2, 18) SPLIT_CASE(4, 4, 2, 18)
+    SPLIT_CASE(4, 5, 2, 18) SPLIT_CASE(4, 6, 2, 18) SPLIT_CASE(4, 8, 2, 18)
+    SPLIT_CASE(4, 1, 2, PW) SPLIT_CASE(4, 2, 2, PW) SPLIT_CASE(4, 3, 2, PW) SPLIT_CASE(4, 4, 2, PW)
+    SPLIT_CASE(4, 5, 2, PW) SPLIT_CASE(4, 6, 2, PW) SPLIT_CASE(4, 8, 2, PW)
+    SPLIT_CASE(4, 1, 1, 18) SPLIT_CASE(4, 2, 1, 18) SPLIT_CASE(4, 3, 1, 18) SPLIT_CASE(4, 4, 1, 18)
+    SPLIT_CASE(1, 1, 2, 10) SPLIT_CASE(1, 2, 2, 10)
+#undef SPLIT_CASE
+    return set_error(MELT_E_UNSUPPORTED, "split kernel: no such shape");
+}
+
+}  // namespace melt

@@ -147,6 +147,9 @@ std::string tune_key(const Plan &p) {
     if (hipGetDeviceProperties(&prop, p.device) == hipSuccess) arch = prop.gcnArchName;
     std::ostringstream k;
     k << "prec=" << p.cfg.precision << ",n_fft=" << p.N << ",hop=" << p.H << ",n_mels=" << p.M << ",arch=" << arch;
+    // the variant list of these precisions starts with the split-plane kernel: an index stored
+    // for the list without it names another kernel
+    if (p.n_variants > 0 && split_planes(p) && std::strstr(forward_variant_name(p, 0), "split-planes")) k << ",list=2";
     return k.str();
 }
 
