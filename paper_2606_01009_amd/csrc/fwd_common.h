@@ -762,11 +762,8 @@ inline bool h16_fs_fits(const Plan &p) {
            p.geo16.n_groups <= 512;
 }
 
-// Split-plane kernel (melt_split.h): shape for a batch (parts = 0: the geometry does not fit)
+// Split-plane kernel (melt_split.h)
 constexpr int kSplitChunk = 128;      // frames per chunk-table entry
-struct SplitShape;
-SplitShape split_shape(const Plan &p, int64_t est_chunks, int64_t n_frames);
-bool split_fits(const Plan &p);
 melt_status launch_melt_split_f32(Plan &p, const FwdTask &t);
 melt_status launch_melt_split_x3(Plan &p, const FwdTask &t);
 

@@ -4,36 +4,25 @@
 //   G[t, 2m] = 2 R[t,m] g[t,m] map'(S),  G[t, 2m+1] = 2 I[t,m] g[t,m] map'(S)
 //   dx[s]    = sum over (t, n) with start_t + n = s of (G W)[t, n]       (overlap-add)
 //   dW       = G^T X                                                    (learnable basis)
-// Everything is FP32 with MFMA, deterministic (no floating-point atomics):
+// Everything is FP32, deterministic (no floating-point atomics); the two products run on three
+// bfloat16 planes per operand (bwd_split.hip):
 //   k_bwd_grad   G over every frame (a flat pass over the [T, M] gradient)
 //   k_bwd_fstart the start sample of every frame
-//   k_bwd_dx     owner-computes overlap-add: hop-block row b of dx is sum_j G[b - j] W_j,
-//                W_j = basis columns [jH, jH + H); each sample is written once
-//   k_bwd_dw_tiled  split-K GEMM G^T X over frames into per-split partials (LDS-tiled)
+//   dx           owner-computes overlap-add: hop-block row b of dx is sum_j G[b - j] W_j,
+//                W_j = basis columns [jH, jH + H); each sample is written once (k_bwd_dx, FP32
+//                MFMA, where dx_split_fits says no: fewer than 5 Mel bins, or too many hops)
+//   dW           split-K GEMM G^T X over frames into per-split partials
 //   k_bwd_reduce fixed-order sum of the partials into the stacked [2M, N] gradient
 #include <algorithm>
 
-#include "melt_internal.h"
+#include "bwd.h"
 
 namespace melt {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int kRowsDx = 128;       // hop-block rows per dx chunk (4 waves x 32)
 constexpr int kMaxCT = 8;          // column tiles of 32 samples per hop-block row (H <= 256)
-
-// A backward row chunk: up to kRowsDx hop-block rows of one clip.
-struct RowChunk {
-    int64_t sample_start;   // first sample of row 0 of the chunk
-    int64_t sample_end;     // clip end (exclusive)
-    int64_t g_row0;         // G row of clip frame b0 (= frame offset of the clip + b0)
-    int32_t n_rows;         // rows in this chunk
-    int32_t t_lo;           // -b0: chunk-local row index of the clip's frame 0
-    int32_t t_hi;           // T_c - b0: chunk-local index one past the clip's last frame
-    int32_t pad;
-};
-static_assert(sizeof(RowChunk) == 40, "RowChunk layout");
 
 // ------------------------------------------------------------------ schedule of row chunks
 
@@ -238,85 +227,23 @@ __global__ __launch_bounds__(256) void k_bwd_dx(const RowChunk *__restrict__ rc,
     }
 }
 
-// ------------------------------------------------------------------ dW: split-K G^T X
-
-// dW = G^T X, split over frames into per-split partials (q interleaved: q = 2m + {0: cos, 1:
-// sin}).  A[i = q][k = t] = G[t][q], B[k = t][col = n] = x[start_t + n].  A workgroup owns a
-// 128 (q) x 128 (n) block of dW over frames [t0, t1) of its split; each wave a 64 x 64 quarter (2 x 2 MFMA tiles).
-// Per step, 16 frames of G (rows of q) and of the implicitly framed waveform (x[start_t + n])
-// are staged in LDS (the next step's loads in flight during the MFMAs), then each wave runs
-// 8 k-steps of 2 frames over its 4 tiles.  Rows are padded to 160 floats, so the two half-
-// waves (frames 2s and 2s + 1) read different banks.
-constexpr int kDwKB = 16, kDwRow = 160;
-__global__ __launch_bounds__(256) void k_bwd_dw_tiled(const float *__restrict__ G, const int64_t *__restrict__ fstart,
-                                                      const float *__restrict__ wave, int64_t T, int M, int N,
-                                                      int splits, float *__restrict__ part) {
-    __shared__ float Gs[kDwKB * kDwRow], Xs[kDwKB * kDwRow];
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int Q = 2 * M;
-    const int QB = (Q + 127) / 128, NB = (N + 127) / 128, blocks = QB * NB;
-    const int split = blockIdx.x / blocks, bb = blockIdx.x - split * blocks;
-    const int qb = bb / NB, nb = bb - qb * NB;
-    const int q0 = qb * 128, n0 = nb * 128;
-    const int64_t per = (T + splits - 1) / splits;
-    const int64_t t0 = (int64_t)split * per, t1 = t0 + per < T ? t0 + per : T;
-    const int wq = (wid & 1) * 64, wn = (wid >> 1) * 64;
-    const int h = lane >> 5, l32 = lane & 31;
-    // staging role: frame row sr of the step, 8 consecutive q and 8 consecutive n at sc
-    const int sr = tid >> 4, sc = (tid & 15) * 8;
-    f32x16 acc00 = f32x16{}, acc01 = f32x16{}, acc10 = f32x16{}, acc11 = f32x16{};
-    float gr[8], xr[8];
-    auto load = [&](int64_t tb) {
-        const int64_t tf = tb + sr;
-        const int64_t st = tf < t1 ? fstart[tf] : -1;      // -1: no frame (zero row)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int q = q0 + sc + e, n = n0 + sc + e;
-            gr[e] = (st >= 0 && q < Q) ? G[tf * Q + q] : 0.0f;
-            xr[e] = (st >= 0 && n < N) ? wave[st + n] : 0.0f;
-        }
-    };
-    if (t0 < t1) load(t0);
-    for (int64_t tb = t0; tb < t1; tb += kDwKB) {
-        __syncthreads();                               // the previous step's LDS reads are done
-        *(f32x4 *)(Gs + sr * kDwRow + sc) = f32x4{gr[0], gr[1], gr[2], gr[3]};
-        *(f32x4 *)(Gs + sr * kDwRow + sc + 4) = f32x4{gr[4], gr[5], gr[6], gr[7]};
-        *(f32x4 *)(Xs + sr * kDwRow + sc) = f32x4{xr[0], xr[1], xr[2], xr[3]};
-        *(f32x4 *)(Xs + sr * kDwRow + sc + 4) = f32x4{xr[4], xr[5], xr[6], xr[7]};
-        __syncthreads();
-        if (tb + kDwKB < t1) load(tb + kDwKB);
-#pragma unroll
-        for (int k = 0; k < kDwKB / 2; ++k) {
-            const int row = (2 * k + h) * kDwRow;
-            const float a0 = Gs[row + wq + l32], a1 = Gs[row + wq + 32 + l32];
-            const float b0 = Xs[row + wn + l32], b1 = Xs[row + wn + 32 + l32];
-            acc00 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc00, 0, 0, 0);
-            acc01 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc01, 0, 0, 0);
-            acc10 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc10, 0, 0, 0);
-            acc11 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc11, 0, 0, 0);
-        }
-    }
-    // lane holds column n, rows q = tile base + 8(r/4) + 4h + r%4 (interleaved q)
-    float *p = part + (size_t)split * Q * N;
-    auto put = [&](const f32x16 &acc, int qbase, int nbase) {
-        const int n = nbase + l32;
-        if (n >= N) return;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int qq = qbase + 8 * (r >> 2) + 4 * h + (r & 3);
-            if (qq < Q) p[(size_t)qq * N + n] = acc[r];
-        }
-    };
-    put(acc00, q0 + wq, n0 + wn);
-    put(acc01, q0 + wq, n0 + wn + 32);
-    put(acc10, q0 + wq + 32, n0 + wn);
-    put(acc11, q0 + wq + 32, n0 + wn + 32);
-}
+// ------------------------------------------------------------------ dW
 
 // Sums the splits' partials in split order (so the result does not depend on the launch),
 // four consecutive n per thread with 16-byte loads when N is a multiple of 4, eight splits'
-// loads in flight at a time.
-__global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, int N, float *__restrict__ dW) {
+// loads in flight at a time.  A sum that is not finite is taken again in plain FP32 (redo): the
+// operand planes of an infinity are not a product with it.
+__device__ __forceinline__ float dw_redo(const float *G, const int64_t *fstart, const float *wave, int64_t T, int Q, int q,
+                                         int n) {
+    float s = 0.0f;
+#pragma unroll 1
+    for (int64_t t = 0; t < T; ++t)
+        if (fstart[t] >= 0) s = fmaf(G[t * Q + q], wave[fstart[t] + n], s);
+    return s;
+}
+__global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, int N, float *__restrict__ dW,
+                             const float *__restrict__ G, const int64_t *__restrict__ fstart,
+                             const float *__restrict__ wave, int64_t T) {
     const int64_t total = (int64_t)2 * M * N;
     if ((N & 3) == 0) {
         const int64_t total4 = total / 4;
@@ -333,6 +260,10 @@ __global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, 
             }
             for (; k < splits; ++k) s += *(const f32x4 *)(part + (size_t)k * total + 4 * i);
             const int q = (int)((4 * i) / N), n = (int)(4 * i - (int64_t)q * N);
+            if (!((s[0] + s[1] + s[2] + s[3]) * 0.0f == 0.0f)) {
+                for (int e = 0; e < 4; ++e)
+                    if (!(s[e] * 0.0f == 0.0f)) s[e] = dw_redo(G, fstart, wave, T, 2 * M, q, n + e);
+            }
             *(f32x4 *)(dW + (size_t)((q & 1) * M + (q >> 1)) * N + n) = s;   // interleaved q -> stacked rows
         }
         return;
@@ -341,6 +272,7 @@ __global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, 
         float s = 0.0f;
         for (int k = 0; k < splits; ++k) s += part[(size_t)k * total + i];
         const int q = (int)(i / N), n = (int)(i - (int64_t)q * N);
+        if (!(s * 0.0f == 0.0f)) s = dw_redo(G, fstart, wave, T, 2 * M, q, n);
         dW[(size_t)((q & 1) * M + (q >> 1)) * N + n] = s;    // interleaved q -> stacked rows
     }
 }
@@ -376,9 +308,11 @@ melt_status pack_basis_dx(Plan &p, hipStream_t s) {
     const int CT = (p.H + 31) / 32;
     if (CT > kMaxCT) return MELT_OK;     // dx unsupported for this hop; reported at call time
     const int J = p.geo32.J, QG = (2 * p.M + 7) / 8;
-    const size_t need = (size_t)CT * J * QG * 64 * 4 * sizeof(float);
+    const bool split = dx_split_fits(p);
+    const size_t need = split ? dx_split_pack_bytes(p) : (size_t)CT * J * QG * 64 * 4 * sizeof(float);
     melt_status st = grow(&p.d_pack_dx, &p.pack_dx_cap, need);
     if (st != MELT_OK) return st;
+    if (split) return dx_split_pack(p, p.d_pack_dx, s);
     k_pack_dx<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, J, CT, (float *)p.d_pack_dx);
     return hip_check(hipGetLastError(), "pack dx");
 }
@@ -398,10 +332,10 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
     const int CT = (H + 31) / 32;
     if (d_gwave && CT > kMaxCT) return set_error(MELT_E_UNSUPPORTED, "backward d/dwave supports hop <= 256");
     // workspace: proj (if recomputed) | G | frame starts | dW partials
-    // dW: 128 x 128 blocks, split over frames so that about two workgroups per CU run
-    const int dw_blocks = ((Q + 127) / 128) * ((N + 127) / 128);
+    // dW: blocks of the basis, split over frames so that about one workgroup per CU runs
+    const int dw_blocks = dw_split_blocks(p);
     const int splits = (int)std::max<int64_t>(
-        1, std::min<int64_t>({64, (2 * (int64_t)p.cu_count + dw_blocks - 1) / dw_blocks, n_frames / 64}));
+        1, std::min<int64_t>({64, ((int64_t)p.cu_count + dw_blocks - 1) / dw_blocks, n_frames / 64}));
     const size_t proj_b = d_proj ? 0 : sizeof(float) * n_frames * Q;
     const size_t g_b = sizeof(float) * n_frames * Q;
     const size_t fs_b = sizeof(int64_t) * n_frames;
@@ -462,8 +396,11 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
         const int S = ((Q + 7) / 8) * 8 + 4;
         const size_t lds = (size_t)(kRowsDx + J - 1) * S * sizeof(float);
         if (lds > 160 * 1024) return set_error(MELT_E_UNSUPPORTED, "backward LDS too large (n_mels * hop)");
-        const int grid = (int)std::min<int64_t>(n_frames / kRowsDx + n_clips + 1, p.cu_count);
-        switch (CT) {
+        const int64_t n_rc = n_frames / kRowsDx + n_clips + 1;
+        const int grid = (int)std::min<int64_t>(n_rc, p.cu_count);
+        if (dx_split_fits(p))
+            st = launch_dx_split(p, G, (const RowChunk *)p.d_bwd_rows, p.d_nchunks + 1, n_rc, n_frames, d_gwave, s);
+        else switch (CT) {
         case 1: st = launch_dx<1>(p, G, d_gwave, S, lds, grid, s); break;
         case 2: st = launch_dx<2>(p, G, d_gwave, S, lds, grid, s); break;
         case 3: st = launch_dx<3>(p, G, d_gwave, S, lds, grid, s); break;
@@ -476,10 +413,9 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
         if (st != MELT_OK) return st;
     }
     if (d_gbasis) {
-        k_bwd_dw_tiled<<<dw_blocks * splits, 256, 0, s>>>(G, fstart, d_wave, n_frames, M, N, splits, part);
-        st = hip_check(hipGetLastError(), "bwd dW");
+        st = launch_dw_split(p, G, fstart, d_wave, n_frames, splits, part, s);
         if (st != MELT_OK) return st;
-        k_bwd_reduce<<<512, 256, 0, s>>>(part, splits, M, N, d_gbasis);
+        k_bwd_reduce<<<512, 256, 0, s>>>(part, splits, M, N, d_gbasis, G, fstart, d_wave, n_frames);
         st = hip_check(hipGetLastError(), "bwd reduce");
     }
     return st;

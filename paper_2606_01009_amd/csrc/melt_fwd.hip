@@ -420,15 +420,13 @@ struct Variant {
 // item's barriers, hand-over and first fragment reads.  128-frame items are the cheapest per
 // frame; 64-frame ones (four row groups) serve rows too long for LDS at 128, and 32-frame ones
 // spread a call of few frames over the chip.
-SplitShape split_shape(const Plan &p, int64_t est_chunks, int64_t n_frames) {
-    const int P = split_planes(p), NP = P == 3 ? 6 : 3, T16 = (p.M + 7) / 8;
-    const Geometry &g = p.geoS;
+SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t est_chunks, int64_t n_frames) {
+    const int NP = P == 3 ? 6 : 3;
     static const struct {
         int wf, ft, rt_max, pv[2];
     } families[3] = {{2, 4, 8, {18, 0}}, {1, 4, 4, {18, 18}}, {2, 1, 2, {10, 10}}};
     SplitShape best{0, 0, 0, 0, 0};
     double best_cost = 1e300;
-    if (P == 0) return best;
     for (int i = 0; i < 3; ++i) {
         const auto &f = families[i];
         SplitShape h{f.wf, f.ft, 0, 0, 0};
@@ -436,13 +434,13 @@ SplitShape split_shape(const Plan &p, int64_t est_chunks, int64_t n_frames) {
         const int vectors = (sf + g.J - 1) * (g.Hp / 4);
         const int wide = i == 0 ? (P == 3 ? 26 : 34) : f.pv[1];
         h.pv = vectors <= f.pv[0] * 256 ? f.pv[0] : wide;
-        if (vectors > h.pv * 256 || split_lds(p, P, h) > (size_t)kMaxLds) continue;
+        if (vectors > h.pv * 256 || split_lds(P, g, h) > (size_t)kMaxLds) continue;
         const int64_t subs = n_frames / sf + std::max<int64_t>(est_chunks - n_frames / kSplitChunk, 0);
         for (int parts = (T16 + wr * f.rt_max - 1) / (wr * f.rt_max); parts <= (T16 + wr - 1) / wr; ++parts) {
             h.parts = parts;
             h.rt = (T16 + wr * parts - 1) / (wr * parts);
             if (h.rt == 7) h.rt = 8;
-            const int64_t rounds = (std::max<int64_t>(subs, 1) * parts + p.cu_count - 1) / p.cu_count;
+            const int64_t rounds = (std::max<int64_t>(subs, 1) * parts + cu_count - 1) / cu_count;
             const double cost = (double)rounds * (std::max(f.ft * NP * 16, P * 64) * (double)g.n_groups * h.rt + 4500.0);
             if (cost < best_cost) {
                 best_cost = cost;
@@ -456,9 +454,9 @@ SplitShape split_shape(const Plan &p, int64_t est_chunks, int64_t n_frames) {
 // The split-plane kernel takes a plan if a shape fits LDS and its k-groups of 32 do not pad the
 // frame by more than half (short hops do: at hop 8 three of four columns would be padding),
 // where FP32 MFMA on k-groups of 8 is the faster product again.
-bool split_fits(const Plan &p) {
+static bool split_fits(const Plan &p) {
     return split_planes(p) && p.geoS.n_groups * 32 <= p.N + p.N / 2 + 32 && p.geoS.n_groups <= 512 &&
-           split_shape(p, 1 << 20, (int64_t)kSplitChunk << 20).parts > 0;
+           split_shape(p.geoS, split_planes(p), (p.M + 7) / 8, p.cu_count, 1 << 20, (int64_t)kSplitChunk << 20).parts > 0;
 }
 
 static std::vector<Variant> variant_list(const Plan &p) {

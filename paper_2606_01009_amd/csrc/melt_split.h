@@ -114,21 +114,22 @@ __host__ __device__ __forceinline__ int split_tile_mel(int t, int q, int T16) {
 
 // The stagers' share of one item: PV vectors of four columns per thread of 256, vector u of a
 // hop-block row-major walk (row u / VR, columns 4 (u % VR) ..), split into planes in registers.
-// Columns at or past the hop, and samples at or past the clip end, are zero.
+// Columns at or past the hop, and samples outside [start + lo, end), are zero.
 template <class Op, int PV>
-__device__ __forceinline__ void split_load(const FwdArgs &a, int64_t start, int64_t clip_end, int nrows, int lt,
+__device__ __forceinline__ void split_load(const FwdArgs &a, int64_t start, int lo, int64_t end, int nrows, int lt,
                                            float inv_vr, unsigned (&w)[PV][2 * Op::P]) {
     // Every load is unconditional, so that all of a batch are in flight together.  Where the whole
     // span (and the 3 samples a row's last vector may reach past it) lies in the clip: 16-byte
     // loads, columns past the hop cleared afterwards.  At a clip's end: 4-byte loads, with an
     // offset past the descriptor, which reads as zero, for columns and samples that do not exist.
     const int span = nrows * a.H, VR = a.Hp >> 2;
-    const int64_t left = clip_end - start;
+    const int64_t left = end - start - lo;
     const bool padded = a.Hp != a.H;
-    const bool inside = nrows > 0 && left >= span + (padded ? 3 : 0);
-    const int records = (int)(inside ? span + (padded ? 3 : 0) : left < 0 ? 0 : left < span ? left : span);
+    const bool inside = nrows > 0 && lo == 0 && left >= span + (padded ? 3 : 0);
+    const int64_t some = left < span - lo ? left : span - lo;
+    const int records = (int)(inside ? span + (padded ? 3 : 0) : some > 0 ? some : 0);
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc((void *)(a.wave + start), (short)0, records * 4, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc((void *)(a.wave + (start + lo)), (short)0, records * 4, 0x00020000);
     asm volatile("" : "+v"(lt));        // addresses formed here, not kept from item to item
     // at most 14 vectors in flight, so that the raw and the split values of all PV fit the registers
     constexpr int NB = PV > 14 ? 2 : 1, PB = (PV + NB - 1) / NB;
@@ -166,8 +167,8 @@ __device__ __forceinline__ void split_load(const FwdArgs &a, int64_t start, int6
                 const int col = at(v, r);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int o = r * a.H + col + e;
-                    const int off = r < nrows && col + e < a.H && o < records ? o * 4 : 0x7ffffff0;
+                    const int o = r * a.H + col + e - lo;
+                    const int off = r < nrows && col + e < a.H && o >= 0 && o < records ? o * 4 : 0x7ffffff0;
                     raw[v][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
                 }
             }
@@ -221,22 +222,35 @@ __device__ __forceinline__ void split_redo(const FwdArgs &a, const SplitGeo &g, 
     }
 }
 
-// One item of a workgroup: frames [f0, f0 + nf) of a chunk.
+// One item of a workgroup: frames [f0, f0 + nf) of a chunk.  Its hop-block rows start at sample
+// `start`; samples before start + lo and from `end` on are zero.
 struct SplitItem {
-    int64_t start, clip_end, out_row;
-    int nf;
+    int64_t start, end, out_row;
+    int nf, lo;
 };
-__device__ __forceinline__ SplitItem split_item(const FwdArgs &a, const SplitGeo &g, int w, int SF) {
-    const int ci = w / (g.nsub * g.parts);
-    const int f0 = ((w - ci * g.nsub * g.parts) / g.parts) * SF;
-    // through the scalar cache: a vector load's wait would also drain the wave's output stores
-    uint4 lo, hi;
-    load_chunk_scalar(a.chunks, ci, lo, hi);
-    const int64_t start = (int64_t)(((uint64_t)lo.y << 32) | lo.x), end = (int64_t)(((uint64_t)lo.w << 32) | lo.z);
-    const int64_t row = (int64_t)(((uint64_t)hi.y << 32) | hi.x);
-    const int nf = min(SF, (int)hi.z - f0);
-    return {start + (int64_t)f0 * a.H, end, row + f0, nf > 0 ? nf : 0};
+// Chunk-table entries through the scalar cache: a vector load's wait would also drain the wave's
+// output stores.
+__device__ __forceinline__ int64_t split_scalar(const void *base, int64_t i) {
+    typedef const __attribute__((address_space(4))) int64_t *cptr;
+    return ((cptr)base)[i];
 }
+
+// What an item reads and what becomes of its accumulators.
+struct SplitForward {
+    FwdArgs a;
+    SplitGeo g;
+    __device__ SplitItem item(int w, int SF) const {
+        const int ci = w / (g.nsub * g.parts);
+        const int f0 = ((w - ci * g.nsub * g.parts) / g.parts) * SF;
+        static_assert(sizeof(Chunk) == 32, "four int64 per entry");
+        const int64_t st = split_scalar(a.chunks, 4 * (int64_t)ci), en = split_scalar(a.chunks, 4 * (int64_t)ci + 1);
+        const int64_t row = split_scalar(a.chunks, 4 * (int64_t)ci + 2);
+        const int nf = min(SF, (int)split_scalar(a.chunks, 4 * (int64_t)ci + 3) - f0);      // low half: n_frames
+        return {st + (int64_t)f0 * a.H, en, row + f0, nf > 0 ? nf : 0, 0};
+    }
+    template <class Op, int FT, int RT>
+    __device__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+};
 
 // Output values of the two bins of each tile of one frame.
 template <int KIND, int RT>
@@ -251,8 +265,8 @@ __device__ __forceinline__ void split_map(float eps, const f32x4 (&acc)[RT], flo
 
 // Accumulators -> output rows.  tile[]: pairs (r, r + 1) start at even tiles.
 template <class Op, int FT, int RT>
-__device__ __forceinline__ void split_store(const FwdArgs &a, const SplitGeo &g, const SplitItem &it, int fbase, int lane,
-                                            const int (&tile)[RT], f32x4 (&acc)[FT][RT]) {
+__device__ __forceinline__ void SplitForward::store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT],
+                                                    f32x4 (&acc)[FT][RT]) const {
     asm volatile("" : "+v"(lane));      // addresses formed per item, not kept across the multiply phase
     const int q = lane >> 4, f0 = fbase + (lane & 15);
     if constexpr (std::is_same<Op, Split2F16>::value) {
@@ -348,9 +362,11 @@ __device__ __forceinline__ void split_store(const FwdArgs &a, const SplitGeo &g,
 // short steps of one or two tiles.
 constexpr int split_ring(int FT, int RT) { return RT >= 8 ? 4 : RT == 6 ? 3 : RT >= 3 ? RT : FT >= 4 ? 4 : 8; }
 
-template <class Op, int FT, int RT, int WF, int PV>
+template <class Job, class Op, int FT, int RT, int WF, int PV>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void k_melt_split(FwdArgs a, SplitGeo g, const split_u32x4 *__restrict__ bpack) {
+void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
+    const FwdArgs &a = job.a;
+    const SplitGeo &g = job.g;
     extern __shared__ __attribute__((aligned(16))) unsigned short rows[];
     constexpr int P = Op::P, NP = Op::NP, SF = WF * FT * 16;
     const int lane = threadIdx.x & 63;
@@ -364,16 +380,16 @@ void k_melt_split(FwdArgs a, SplitGeo g, const split_u32x4 *__restrict__ bpack) 
         unsigned pl[PV][2 * P];
         SplitItem it{};
         if (w < nitems) {
-            it = split_item(a, g, w, SF);
-            split_load<Op, PV>(a, it.start, it.clip_end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
+            it = job.item(w, SF);
+            split_load<Op, PV>(a, it.start, it.lo, it.end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
             split_write<Op, PV>(a, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl, rows);
         }
         __syncthreads();                           // rows of the first item ready
         for (; w < nitems; w += G) {
             const bool more = w + G < nitems;
             if (more) {
-                it = split_item(a, g, w + G, SF);
-                split_load<Op, PV>(a, it.start, it.clip_end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
+                it = job.item(w + G, SF);
+                split_load<Op, PV>(a, it.start, it.lo, it.end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
             }
             // split before the barrier, not between the two
 #pragma unroll
@@ -415,7 +431,7 @@ void k_melt_split(FwdArgs a, SplitGeo g, const split_u32x4 *__restrict__ bpack) 
     const int fbase = wf * FT * 16;
     const int la0 = (fbase + (lane & 15)) * a.S + 8 * (lane >> 4);
     for (; w < nitems; w += G) {
-        const SplitItem it = split_item(a, g, w, SF);
+        const SplitItem it = job.item(w, SF);
         // two planes: a k-group's three products are summed on their own and added once, behind the
         // next tile's first MFMAs (a third of the roundings at the running sum's magnitude)
         f32x4 acc[FT][RT], sum[2][FT];
@@ -501,7 +517,7 @@ void k_melt_split(FwdArgs a, SplitGeo g, const split_u32x4 *__restrict__ bpack) 
             }
         }
         __syncthreads();                           // A: every row read; the stagers may overwrite
-        if (fbase < it.nf) split_store<Op, FT, RT>(a, g, it, fbase, lane, tile, acc);
+        if (fbase < it.nf) job.template store<Op, FT, RT>(it, fbase, lane, tile, acc);
         __syncthreads();                           // B: rows of the next item ready
     }
 }
@@ -509,42 +525,35 @@ void k_melt_split(FwdArgs a, SplitGeo g, const split_u32x4 *__restrict__ bpack) 
 // ------------------------------------------------------------------ launch
 
 // A compiled shape: WF waves along the frames, FT frame tiles and RT row tiles per wave, PV
-// staging vectors per thread; `parts` row parts of 4 / WF RT tiles each.
+// staging vectors per thread; `parts` row parts of 4 / WF RT tiles each (0: nothing fits).
 struct SplitShape {
     int wf, ft, rt, pv, parts;
 };
-template <class Op, int FT, int RT, int WF, int PV>
-melt_status launch_split_k(const FwdArgs &a, const SplitGeo &g, const void *pack, size_t lds, int grid, hipStream_t s) {
-    allow_lds(k_melt_split<Op, FT, RT, WF, PV>);
-    k_melt_split<Op, FT, RT, WF, PV><<<grid, 512, lds, s>>>(a, g, (const split_u32x4 *)pack);
+inline int split_sf(const SplitShape &h) { return h.wf * h.ft * 16; }
+inline size_t split_lds(int P, const Geometry &g, const SplitShape &h) {
+    return (size_t)(split_sf(h) + g.J - 1) * (P * g.Hp + 8) * 2;
+}
+// The shape for n_frames frames in est_chunks chunks of kSplitChunk (melt_fwd.hip).
+SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t est_chunks, int64_t n_frames);
+
+template <class Job, class Op, int FT, int RT, int WF, int PV>
+melt_status launch_split_k(const Job &job, const void *pack, size_t lds, int grid, hipStream_t s) {
+    allow_lds(k_melt_split<Job, Op, FT, RT, WF, PV>);
+    k_melt_split<Job, Op, FT, RT, WF, PV><<<grid, 512, lds, s>>>(job, (const split_u32x4 *)pack);
     return hip_check(hipGetLastError(), "melt split launch");
 }
 
-// frames and LDS of a shape
-inline int split_sf(const SplitShape &h) { return h.wf * h.ft * 16; }
-inline size_t split_lds(const Plan &p, int P, const SplitShape &h) {
-    return (size_t)(split_sf(h) + p.geoS.J - 1) * (P * p.geoS.Hp + 8) * 2;
-}
-
-template <class Op>
-melt_status launch_split(Plan &p, const FwdTask &t) {
-    constexpr int P = Op::P;
-    const SplitShape h = split_shape(p, t.est_chunks, t.n_frames);
+template <class Op, class Job>
+melt_status launch_split(const Plan &p, Job job, const Geometry &geo, const SplitShape &h, const void *pk, int64_t est_chunks,
+                         hipStream_t s) {
     if (h.parts == 0) return set_error(MELT_E_UNSUPPORTED, "split kernel: unsupported geometry");
-    const Geometry &geo = p.geoS;
-    FwdArgs a = make_args(p, geo, P * geo.Hp + 8, t);
-    const int tail = p.N - (geo.J - 1) * p.H;
-    const int sf = split_sf(h);
-    const SplitGeo g{geo.n_groups, geo.Hp / 32, (p.M + 7) / 8, kSplitChunk / sf, h.parts, p.d_basis32, p.N,
-                     tail < p.H && tail % 32 > 0 && tail % 32 <= 16};
-    const int64_t items = t.est_chunks * g.nsub * g.parts;
-    const int grid = std::max(persistent_grid(p, items, 1) / h.parts, 1) * h.parts;
-    const size_t lds = split_lds(p, P, h);
-    const void *pk = p.d_pack_split;
-    const hipStream_t s = t.stream;
-    constexpr int PW = P == 3 ? 26 : 34;       // the wide staging of 128-frame items
+    job.g.nsub = kSplitChunk / split_sf(h);
+    job.g.parts = h.parts;
+    const int grid = std::max(persistent_grid(p, est_chunks * job.g.nsub * h.parts, 1) / h.parts, 1) * h.parts;
+    const size_t lds = split_lds(Op::P, geo, h);
+    constexpr int PW = Op::P == 3 ? 26 : 34;       // the wide staging of 128-frame items
 #define SPLIT_CASE(FT, RT, WF, PV) \
-    if (h.ft == FT && h.rt == RT && h.wf == WF && h.pv == PV) return launch_split_k<Op, FT, RT, WF, PV>(a, g, pk, lds, grid, s);
+    if (h.ft == FT && h.rt == RT && h.wf == WF && h.pv == PV) return launch_split_k<Job, Op, FT, RT, WF, PV>(job, pk, lds, grid, s);
     SPLIT_CASE(4, 1, 2, 18) SPLIT_CASE(4, 2, 2, 18) SPLIT_CASE(4, 3, 2, 18) SPLIT_CASE(4, 4, 2, 18)
     SPLIT_CASE(4, 5, 2, 18) SPLIT_CASE(4, 6, 2, 18) SPLIT_CASE(4, 8, 2, 18)
     SPLIT_CASE(4, 1, 2, PW) SPLIT_CASE(4, 2, 2, PW) SPLIT_CASE(4, 3, 2, PW) SPLIT_CASE(4, 4, 2, PW)
@@ -553,6 +562,18 @@ melt_status launch_split(Plan &p, const FwdTask &t) {
     SPLIT_CASE(1, 1, 2, 10) SPLIT_CASE(1, 2, 2, 10)
 #undef SPLIT_CASE
     return set_error(MELT_E_UNSUPPORTED, "split kernel: no such shape");
+}
+
+// The forward over a chunk table.
+template <class Op>
+melt_status launch_split_forward(const Plan &p, const FwdTask &t) {
+    const Geometry &geo = p.geoS;
+    const int T16 = (p.M + 7) / 8, tail = p.N - (geo.J - 1) * p.H;
+    const SplitShape h = split_shape(geo, Op::P, T16, p.cu_count, t.est_chunks, t.n_frames);
+    const SplitForward job{make_args(p, geo, Op::P * geo.Hp + 8, t),
+                           {geo.n_groups, geo.Hp / 32, T16, 0, 0, p.d_basis32, p.N,
+                            tail < p.H && tail % 32 > 0 && tail % 32 <= 16}};
+    return launch_split<Op>(p, job, geo, h, p.d_pack_split, t.est_chunks, t.stream);
 }
 
 }  // namespace melt

@@ -3,6 +3,6 @@
 
 namespace melt {
 melt_status launch_melt_split_x3(Plan &p, const FwdTask &t) {
-    return prec_f16(p) ? launch_split<Split2F16>(p, t) : launch_split<Split2BF16>(p, t);
+    return prec_f16(p) ? launch_split_forward<Split2F16>(p, t) : launch_split_forward<Split2BF16>(p, t);
 }
 }  // namespace melt

@@ -108,3 +108,61 @@ def test_overflow_after_a_frame_stays_outside(torch, melt):
             assert not np.isfinite(got[t]).all()
         else:
             assert np.array_equal(got[t], clean[t])
+
+
+@pytest.mark.parametrize("geom", [(16000, 480, 161, 64), (16000, 400, 160, 9), (8000, 256, 80, 24), (16000, 320, 160, 65),
+                                  (16000, 300, 33, 17), (22050, 1024, 256, 128), (16000, 400, 160, 3)])
+def test_backward_shapes(torch, melt, orc, geom):
+    """d/dwave and d/dbasis on operand planes: hops and Mel counts that fill no tile, blocks of
+    128 x 256 basis elements with remainders, frame ranges that end inside a step of 32, clips
+    shorter than a chunk of hop rows, and (3 Mel bins) the FP32-MFMA d/dwave kernel beside the
+    plane d/dbasis."""
+    from tests.test_gpu_backward import _case
+    sr, N, H, M = geom
+    wave, off = workloads.random_clips([N - 1, N, 70 * H + N + 3, 5 * H + N + 1, 131 * H + N], seed=N + M)
+    _case(torch, melt, orc, wave, off, float(sr), N, H, M, label=f"backward {geom}")
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_upstream_gradients_the_planes_cannot_hold(torch, melt, bad):
+    """One infinite or NaN upstream gradient: the samples and basis rows it reaches are non-finite
+    in the way FP32 arithmetic makes them, everything else is bit for bit as without it.  The
+    samples that only share the frame's last hop-block row meet it with zero weights, so they are
+    recomputed in plain FP32: finite, and within both sums' rounding of the clean ones."""
+    N, H, M = 400, 160, 40
+    plan = melt.MeltPlan(sample_rate=16000, n_fft=N, hop=H, n_mels=M, output=melt.MELT_OUT_POWER)
+    wave, off = workloads.random_clips([200 * H + N, 40 * H + N], seed=6)
+    T = melt.total_frames(off, N, H)
+    d_wave, d_off = torch.from_numpy(wave).cuda(), torch.from_numpy(off).cuda()
+    proj = torch.empty((T, 2 * M), device="cuda")
+    plan.forward(d_wave, d_off, T, proj=proj)
+    g = torch.randn((T, M), generator=torch.Generator().manual_seed(1))
+    g[50, 7] = 0.0
+    gw0, gb0 = (x.cpu().numpy() for x in plan.backward(d_wave, d_off, T, g.cuda(), proj=proj))
+    g[50, 7] = bad
+    gw, gb = (x.cpu().numpy() for x in plan.backward(d_wave, d_off, T, g.cuda(), proj=proj))
+    hit = np.zeros(wave.size, bool)
+    hit[50 * H:50 * H + N] = True
+    last = np.zeros(wave.size, bool)
+    last[50 * H + N:53 * H] = True
+    assert np.array_equal(gw[~hit & ~last], gw0[~hit & ~last])
+    W, P = plan.basis(), proj.cpu().numpy()
+    G = 2 * P.astype(np.float64) * np.repeat(g.double().numpy(), 2, axis=1)
+    G[50, 14:16] = 0.0
+    Wq = np.abs(W.reshape(2, M, N).transpose(1, 0, 2).reshape(2 * M, N).astype(np.float64))      # interleaved rows
+    mass = np.array([sum(np.abs(G[t]) @ Wq[:, s - t * H] for t in range(50, 53) if t * H <= s < t * H + N)
+                     for s in np.flatnonzero(last)])
+    terms = 2 * M * 3 + 3
+    assert np.all(np.abs(gw[last].astype(np.float64) - gw0[last]) <= 2 * terms * 2.0 ** -24 * (1 + 1e-3) * mass)
+    rows = np.zeros(2 * M, bool)
+    rows[[7, M + 7]] = True
+    assert np.array_equal(gb[~rows], gb0[~rows])
+    # G of the bin is inf (sign of R, I) or NaN; a product with it is inf, or NaN where the weight is 0
+    with np.errstate(invalid="ignore"):
+        gr, gi = np.float32(2) * P[50, 14] * np.float32(bad), np.float32(2) * P[50, 15] * np.float32(bad)
+        want_w = gr * W[7] + gi * W[M + 7]
+        want_b = np.stack([gr * wave[50 * H:50 * H + N], gi * wave[50 * H:50 * H + N]])
+    for got, want in ((gw[hit], want_w), (gb[rows], want_b)):
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        inf = np.isinf(want)
+        assert np.array_equal(np.isinf(got), inf) and np.array_equal(got[inf], want[inf])
