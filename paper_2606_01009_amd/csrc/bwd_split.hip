@@ -23,7 +23,9 @@ struct SplitDx {
     FwdArgs a;             // wave = G, out = dx, chunks = the RowChunk table
     SplitGeo g;            // basis: stacked [2M][N]
     int hop;
-    __device__ SplitItem item(int w, int SF) const {
+    __device__ __forceinline__ bool lists() const { return false; }
+    __device__ __forceinline__ int start(Chunk *) const { return 0; }
+    __device__ __forceinline__ SplitItem item(int w, int, const Chunk *, int SF) const {
         const int ci = w / (g.nsub * g.parts);
         const int f0 = ((w - ci * g.nsub * g.parts) / g.parts) * SF;
         static_assert(sizeof(RowChunk) == 40, "five int64 per entry");
@@ -41,7 +43,7 @@ struct SplitDx {
         return {start, start + (int64_t)max(r_hi, r_lo) * a.H, (int64_t)ci * kSplitChunk + f0, nf, r_lo * a.H};
     }
     template <class Op, int FT, int RT>
-    __device__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+    __device__ __forceinline__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
 };
 
 // four floats at any 4-byte address (the hop and the clips' starts may be odd)

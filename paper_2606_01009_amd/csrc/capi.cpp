@@ -237,9 +237,7 @@ melt_status melt_forward_proj(melt_plan plan, const float *d_wave, const int64_t
     st = hip_check(hipSetDevice(p->device), "hipSetDevice");
     if (st != MELT_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    st = launch_schedule(*p, 0, d_clip_offsets, n_clips, melt_chunk_frames(*p), n_frames, s);
-    if (st != MELT_OK) return st;
-    return launch_melt_main(*p, d_wave, d_out, d_proj, s);
+    return launch_melt_forward(*p, d_clip_offsets, n_clips, n_frames, d_wave, d_out, d_proj, s);
 }
 
 melt_status melt_forward_noalloc(melt_plan plan, const float *d_wave, const int64_t *d_clip_offsets,
@@ -262,9 +260,7 @@ melt_status stft_mel_forward(melt_plan plan, const float *d_wave, const int64_t 
     st = hip_check(hipSetDevice(p->device), "hipSetDevice");
     if (st != MELT_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    st = launch_schedule(*p, 1, d_clip_offsets, n_clips, stft_chunk_frames(*p), n_frames, s);
-    if (st != MELT_OK) return st;
-    return launch_stft_main(*p, d_wave, d_out, s);
+    return launch_stft_forward(*p, d_clip_offsets, n_clips, n_frames, d_wave, d_out, s);
 }
 
 melt_status melt_batch_prepare(melt_plan plan, const int64_t *d_clip_offsets, int32_t n_clips, int64_t n_frames,

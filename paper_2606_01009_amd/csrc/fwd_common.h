@@ -20,7 +20,7 @@
 // melt_f8.hip; melt_fwd.hip holds the schedule, the basis packing and the variant table.
 #pragma once
 #include <vector>
-#include "melt_internal.h"
+#include "schedule.h"
 
 namespace melt {
 
@@ -87,11 +87,6 @@ __device__ __forceinline__ unsigned fp8x4(float a, float b, float c, float d) {
 
 // A chunk-table entry read into scalar registers (every lane of a workgroup uses the same
 // chunk, so buffer descriptors built from it need no waterfall loop).
-__device__ __forceinline__ int64_t uniform64(int64_t v) {
-    const int lo = __builtin_amdgcn_readfirstlane((int)(v & 0xffffffff));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
-    return (int64_t)(((uint64_t)(unsigned)hi << 32) | (unsigned)lo);
-}
 __device__ __forceinline__ Chunk read_chunk(const Chunk *tab, int c) {
     Chunk e = tab[c];
     e.sample_start = uniform64(e.sample_start);
@@ -114,6 +109,8 @@ struct FwdArgs {
     int out_kind;
     float eps;
     float invH;            // 1 / H rounded to FP32 (row index of a span position)
+    ClipTable clips;       // off set: the kernel finds its own chunks, chunks and n_chunks are not read
+    int list_off;          // bytes from the dynamic LDS to the chunk list (kernels that keep one)
     float acc_scale;       // multiplies the accumulated projections (exact power of two; 1 unless FP16X3)
 };
 
@@ -146,6 +143,22 @@ __device__ __forceinline__ Chunk ring_get(const ChunkRing &r, int i) {
     e.clip = __builtin_amdgcn_readfirstlane(e.clip);
     return e;
 }
+
+// The start of a kernel that schedules itself: every wave finds the chunk count, the first fills
+// the ring (its one window: such a kernel runs at most kRing iterations, which keeps the search out
+// of the chunk loop and its registers) or the list of kListEntries of the kernels that keep one.
+// For the whole workgroup, with a barrier.
+__device__ __forceinline__ int ring_start(const FwdArgs &a, ChunkRing &r, int c0, int cstep) {
+    const int n = chunk_list(a.clips, a.H, c0 + (int64_t)(threadIdx.x & 63) * cstep, kRing + 2, r.e, threadIdx.x < 64);
+    __syncthreads();
+    return n;
+}
+__device__ __forceinline__ int list_start(const FwdArgs &a, Chunk *list, int64_t c_lane) {
+    const int n = chunk_list(a.clips, a.H, c_lane, kListEntries, list, threadIdx.x < 64);
+    __syncthreads();
+    return n;
+}
+constexpr int kListBytes = kListEntries * (int)sizeof(Chunk);
 
 // Natural log from the hardware base-2 logarithm (v_log_f32, about 1 ulp on normal
 // inputs) times ln 2.  Arguments are S + eps or sqrt(S) + eps with S >= 0 and eps >= the
@@ -607,6 +620,7 @@ struct FwdTask {
     float *out;
     float *proj;
     hipStream_t stream;
+    ClipTable clips{};     // off set: no table, the kernel schedules itself
 };
 
 inline FwdArgs make_args(const Plan &p, const Geometry &g, int S, const FwdTask &t) {
@@ -626,6 +640,8 @@ inline FwdArgs make_args(const Plan &p, const Geometry &g, int S, const FwdTask 
     a.out_kind = p.kern_out;
     a.eps = (float)p.cfg.log_eps;
     a.invH = (float)(1.0 / p.H);
+    a.clips = t.clips;
+    a.list_off = 0;
     a.acc_scale = p.cfg.precision == MELT_PREC_FP16X3 ? 1.0f / kF16x3Scale : 1.0f;
     return a;
 }
@@ -712,6 +728,11 @@ inline bool pc_fits(const Plan &p) {
     const int ng = p.geo16.n_groups;
     return ng == 10 || ng == 16 || ng == 20 || ng == 25;
 }
+
+// Room for the chunk list of a self-scheduling producer/consumer kernel after its LDS.
+bool pc_list_fits(const Plan &p, bool f8b, int bf);
+// Whether the split-plane kernel schedules a batch itself (melt_fwd.hip)
+bool split_self_scheduled(const Plan &p, int64_t est_chunks, int64_t n_frames);
 
 // K-split 16-bit kernel (frames too long for one wave's basis tile): two waves per row tile,
 // the first holding the k-groups of the first J0 hop segments (ns0 groups), the second the

@@ -150,25 +150,27 @@ __global__ __launch_bounds__(512) void k_melt_f8_as(FwdArgs a, const i32x8 *__re
     float *mpre = mfull + bf + a.J - 1;                                          // [bf + J - 1] prefix maxima
     float *bmax = sinv + bf;                   // or [(bf + J - 1) H / 16] block maxima (same area)
     float *scratch = lds_f8 + scr_off;                                           // FP32 span
+    // before the basis tile is in registers
+    __shared__ ChunkRing ring;
+    const bool own = a.clips.off != nullptr;
+    const int nch = own ? ring_start(a, ring, blockIdx.x, gridDim.x) : *a.n_chunks;
     i32x8 A[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) A[g] = bq[((size_t)rt * NG + g) * 64 + lane];
     float rinv[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) rinv[r] = rinv_g[rt * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)];
-    const int nch = *a.n_chunks;
     // the next chunk's span is copied by the waves with the least multiply work (those
     // sharing a row tile; the upper half of the waves when every wave owns one): only they
     // wait for it, so the other waves never wait on their own output stores
     const int dma0 = full < nw ? full : nw / 2;
     const bool dma_wave = wid >= dma0;
     int c = blockIdx.x;
-    if (c < nch) async_span(a, read_chunk(a.chunks, c), scratch);
+    if (c < nch) async_span(a, own ? ring_get(ring, 0) : read_chunk(a.chunks, c), scratch);
     async_wait();
-    __shared__ ChunkRing ring;
     for (int it = 0; c < nch; c += gridDim.x, ++it) {
         const int ri = it % kRing;
-        if (ri == 0) ring_fill(ring, a.chunks, c, gridDim.x, nch);
+        if (ri == 0 && !own) ring_fill(ring, a.chunks, c, gridDim.x, nch);
         __syncthreads();                           // span of chunk c is in scratch; the image is free
         const Chunk ch = ring_get(ring, ri);
         const Chunk chn = ring_get(ring, ri + 1);
@@ -695,9 +697,13 @@ __global__ __launch_bounds__(768) void k_melt_f8b_pc(FwdArgs a, const i32x8 *__r
     float *span = lds_pc + scr_off;
     const int bph = a.H >> 5;
     const float inv_bph = 1.0f / (float)bph;
-    const int nch = *a.n_chunks;
     const int cstep = gridDim.x / rgroups;
     const int c0 = blockIdx.x / rgroups;
+    // descriptors: the four slots, or the list of a kernel that schedules itself
+    const bool own = a.clips.off != nullptr;
+    Chunk *slots = own ? reinterpret_cast<Chunk *>(reinterpret_cast<char *>(lds_pc) + a.list_off) : dslot;
+    const int smask = own ? kListEntries - 1 : 3;
+    const int nch = own ? list_start(a, slots, c0 + (int64_t)(threadIdx.x & 63) * cstep) : *a.n_chunks;
     // codes past a chunk's blocks (read for blocks past a frame, or frames past the chunk) are
     // finite from the start, in both buffers
     for (int i = threadIdx.x; i < n_codes; i += blockDim.x) {
@@ -708,18 +714,18 @@ __global__ __launch_bounds__(768) void k_melt_f8b_pc(FwdArgs a, const i32x8 *__r
     // buffer 0 and start the copy of chunk 1.  Producers and consumers then run loops of their
     // own (so that neither role's registers are live in the other's), with one barrier per
     // chunk in both.
-    if (wid == nc && lane < 3 && c0 + lane * cstep < nch) dslot[lane] = a.chunks[c0 + lane * cstep];
+    if (!own && wid == nc && lane < 3 && c0 + lane * cstep < nch) dslot[lane] = a.chunks[c0 + lane * cstep];
     // the first chunk is copied and converted by every wave (blocks w, w + 12, ...); after a
     // barrier the producers start the copy of the second
     if (c0 < nch) {
-        const Chunk ch = read_chunk(a.chunks, c0);
+        const Chunk ch = own ? slot_get(slots, 0) : read_chunk(a.chunks, c0);
         copy_owned8(a, ch, span, wid, nw);
         async_wait();
         convert_owned8<false>(a, ch, span, buf0, S8, reinterpret_cast<int *>(buf0 + code_off), inv_bph, wid, nw, ch);
     }
     __syncthreads();
     if (producer) {
-        if (c0 + cstep < nch) copy_owned8(a, read_chunk(a.chunks, c0 + cstep), span, pw, np);
+        if (c0 + cstep < nch) copy_owned8(a, own ? slot_get(slots, 1) : read_chunk(a.chunks, c0 + cstep), span, pw, np);
         for (int it = 0; c0 + it * cstep < nch; ++it) {
             __syncthreads();                       // chunk it converted; buffer (it + 1) & 1 free
             const int c = c0 + it * cstep;
@@ -729,14 +735,14 @@ __global__ __launch_bounds__(768) void k_melt_f8b_pc(FwdArgs a, const i32x8 *__r
             // that reached HBM and a wait for every outstanding memory operation), loaded
             // through the scalar cache so that storing it waits for no copy
             uint4 nd0 = {}, nd1 = {};
-            const bool load_desc = wid == nc && c + 3 * cstep < nch;
+            const bool load_desc = !own && wid == nc && c + 3 * cstep < nch;
             async_wait();                          // this producer's copies of chunk it + 1
             if (load_desc) load_chunk_scalar(a.chunks, c + 3 * cstep, nd0, nd1);
-            const Chunk ch1 = slot_get(dslot, (it + 1) & 3);
+            const Chunk ch1 = slot_get(slots, (it + 1) & smask);
             unsigned char *rows = buf0 + ((it + 1) & 1) * buf_bytes;
             int *codes = reinterpret_cast<int *>(rows + code_off);
             if (c + 2 * cstep < nch)
-                convert_owned8<true>(a, ch1, span, rows, S8, codes, inv_bph, pw, np, slot_get(dslot, (it + 2) & 3));
+                convert_owned8<true>(a, ch1, span, rows, S8, codes, inv_bph, pw, np, slot_get(slots, (it + 2) & smask));
             else
                 convert_owned8<false>(a, ch1, span, rows, S8, codes, inv_bph, pw, np, ch1);
             if (load_desc && lane == 0) {
@@ -756,7 +762,7 @@ __global__ __launch_bounds__(768) void k_melt_f8b_pc(FwdArgs a, const i32x8 *__r
     const float *ri = rinv_s + 32 * wid + 4 * (lane >> 5);
     for (int it = 0; c0 + it * cstep < nch; ++it) {
         __syncthreads();                           // chunk it converted; buffer (it + 1) & 1 free
-        const Chunk ch = slot_get(dslot, it & 3);
+        const Chunk ch = slot_get(slots, it & smask);
         const unsigned char *rows = buf0 + (it & 1) * buf_bytes;
         const int *codes = reinterpret_cast<const int *>(rows + code_off);
         const int nft = (ch.n_frames + 31) >> 5;
@@ -1050,10 +1056,14 @@ melt_status launch_melt_f8b(Plan &p, const FwdTask &t, int bf, bool pc) {
     if (ng8 != 4 && ng8 != 7 && ng8 != 8 && ng8 != 16)
         return set_error(MELT_E_UNSUPPORTED, "FP8 kernel supports n_fft in (192, 256], (384, 512], (960, 1024]");
     const Geometry &g = p.geo32;
-    const FwdArgs a = make_args(p, g, lds_stride(g.Hp, 4), t);
-    const size_t lds = pc ? f8b_pc_lds_bytes(p, bf) : f8b_lds_bytes(p, bf);
+    FwdArgs a = make_args(p, g, lds_stride(g.Hp, 4), t);
+    size_t lds = pc ? f8b_pc_lds_bytes(p, bf) : f8b_lds_bytes(p, bf);
     if (lds + (pc ? f8b_pc_static_bytes() : (size_t)kRingBytes) > (size_t)kMaxLds)
         return set_error(MELT_E_UNSUPPORTED, "frame geometry exceeds LDS for the FP8 kernel");
+    if (t.clips.off) {                  // the chunk list after the buffers (pc_list_fits)
+        a.list_off = (int)((lds + 15) & ~size_t(15));
+        lds = (size_t)a.list_off + kListBytes;
+    }
     F8BlockTable bt{};
     const int S8 = f8b_stride(p);
     for (int i = 0; i < 2 * ng8; ++i) {

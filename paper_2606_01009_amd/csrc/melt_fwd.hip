@@ -9,74 +9,24 @@ namespace melt {
 
 // ------------------------------------------------------------------ schedule
 
-// inclusive prefix sum over the 64 lanes of a wave (shuffles, no barrier)
-__device__ __forceinline__ int64_t wave_scan(int64_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int64_t u = __shfl_up(v, d, 64);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
-
-// a / b for 0 <= a, 0 < b < 2^31: 32-bit division when a fits (the 64-bit one is a long
-// software sequence)
-__device__ __forceinline__ int64_t udiv_nonneg(int64_t a, int b) {
-    return a <= 0x7fffffff ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
-}
-
-// Chunk table for at most 64 clips, with no barrier: every wave holds the clips in its lanes
-// (lane = clip) and scans their frame and chunk counts in registers; entry q (taken by lane
-// q % 64 of wave (q / 64) % 16) finds its clip by a binary search over the lanes' chunk
-// prefix sums (shuffles, every lane active).  n_chunks receives min(total, cap).
+// Chunk table for at most 64 clips, with no barrier: every wave scans the clips in its lanes and
+// writes every (16 gridDim)-th group of 64 entries.  n_chunks receives min(total, cap).
 __global__ __launch_bounds__(1024) void k_schedule64(const int64_t *__restrict__ off, int n_clips, int N, int H,
                                                      int bf, Chunk *__restrict__ tab, int64_t cap,
                                                      int *__restrict__ n_out) {
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int64_t st = 0, L = 0;
-    if (lane < n_clips) {
-        st = off[lane];
-        L = off[lane + 1] - st;
-    }
-    const int64_t T = (L >= N) ? 1 + udiv_nonneg(L - N, H) : 0;
-    const int64_t K = udiv_nonneg(T + bf - 1, bf);
-    const int64_t pf = wave_scan(T, lane), pc = wave_scan(K, lane);
-    const int64_t total = __shfl(pc, 63, 64);
-    const int64_t nv = total < cap ? total : cap;
+    const int lane = threadIdx.x & 63, w = blockIdx.x * 16 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const ClipScan s = clip_scan(off, n_clips, N, H, bf);
     // the same on every lane; made scalar so the loop below keeps every lane active
-    const int64_t n = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(nv >> 32)) << 32) |
-                                (uint32_t)__builtin_amdgcn_readfirstlane((int)nv));
-    for (int64_t q0 = 64 * w; q0 < n; q0 += 1024) {      // wave-uniform trip count
-        const int64_t q = q0 + lane;
-        int t = 0;                                       // clips whose chunks all precede q
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1)
-            if (__shfl(pc, t + d - 1, 64) <= q) t += d;
-        // every shuffle runs on all lanes: a lane left out of one (a shuffle under a
-        // condition) would read as zero to the lanes that source from it
-        const int tp = t > 0 ? t - 1 : 0;
-        const int64_t pc_p = __shfl(pc, tp, 64), pf_p = __shfl(pf, tp, 64);
-        const int64_t pf_t = __shfl(pf, t & 63, 64);
-        const int64_t st_t = __shfl(st, t & 63, 64), L_t = __shfl(L, t & 63, 64);
-        const int64_t kc0 = t > 0 ? pc_p : 0;
-        const int64_t fb = t > 0 ? pf_p : 0;
-        const int64_t Tt = pf_t - fb;
-        if (q < n) {
-            const int64_t k = q - kc0;
-            Chunk e;
-            e.sample_start = st_t + k * bf * (int64_t)H;
-            e.sample_end = st_t + L_t;
-            e.out_row = fb + k * bf;
-            e.n_frames = (int)((Tt - k * bf) < bf ? (Tt - k * bf) : bf);
-            e.clip = t;
-            tab[q] = e;
-        }
+    const int64_t n = uniform64(s.total < cap ? s.total : cap);
+    for (int64_t q0 = 64 * w; q0 < n; q0 += 1024 * gridDim.x) {      // wave-uniform trip count
+        const Chunk e = clip_chunk(s, H, bf, q0 + lane);
+        if (q0 + lane < n) tab[q0 + lane] = e;
     }
-    if (threadIdx.x == 0) *n_out = (int)n;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = (int)n;
 }
 
-// One workgroup: prefix sums over the clips of frame counts and chunk counts, then the
-// chunk table.  n_chunks receives min(total, cap).
+// Any number of clips: every workgroup forms the prefix sums of frame and chunk counts over the
+// clips, 1024 at a time, and writes its share of the chunk table.  n_chunks receives min(total, cap).
 __global__ __launch_bounds__(1024) void k_schedule(const int64_t *__restrict__ off, int n_clips, int N,
                                                    int H, int bf, Chunk *__restrict__ tab, int64_t cap,
                                                    int *__restrict__ n_out) {
@@ -115,7 +65,7 @@ __global__ __launch_bounds__(1024) void k_schedule(const int64_t *__restrict__ o
         // entries of this block of clips, written by all threads: entry q belongs to the
         // first clip t whose inclusive chunk prefix exceeds q (binary search)
         const int64_t total = sc[1023];
-        for (int64_t q = tid; q < total; q += 1024) {
+        for (int64_t q = tid + 1024 * (int64_t)blockIdx.x; q < total; q += 1024 * (int64_t)gridDim.x) {
             int lo = 0, hi = 1023;
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
@@ -144,7 +94,7 @@ __global__ __launch_bounds__(1024) void k_schedule(const int64_t *__restrict__ o
         }
         __syncthreads();
     }
-    if (tid == 0) *n_out = (int)(carry_c < cap ? carry_c : cap);
+    if (blockIdx.x == 0 && tid == 0) *n_out = (int)(carry_c < cap ? carry_c : cap);
 }
 
 __global__ __launch_bounds__(1024) void k_frame_offsets(const int64_t *__restrict__ off, int n_clips, int N,
@@ -355,6 +305,16 @@ melt_status ensure_chunks(Plan &p, int which, int64_t needed) {
     return MELT_OK;
 }
 
+// One workgroup writes about 1024 entries in the time it takes to find them, so longer tables are
+// shared by several (the comparator's table of 64 x 30 s, 8000 entries: 8.6 us with one).
+static melt_status enqueue_schedule(const Plan &p, const int64_t *d_off, int n_clips, int bf, int64_t need, Chunk *tab,
+                                    int64_t cap, int *n_tab, hipStream_t s) {
+    const int grid = (int)std::min<int64_t>(16, (need + 1023) / 1024);
+    if (n_clips <= 64) k_schedule64<<<grid, 1024, 0, s>>>(d_off, n_clips, p.N, p.H, bf, tab, cap, n_tab);
+    else k_schedule<<<grid, 1024, 0, s>>>(d_off, n_clips, p.N, p.H, bf, tab, cap, n_tab);
+    return hip_check(hipGetLastError(), "schedule launch");
+}
+
 melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clips, int bf_max, int64_t n_frames,
                             hipStream_t s) {
     // Chunks of at most bf_max frames (the kernel's LDS image).  The comparator sizes its
@@ -366,13 +326,7 @@ melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clip
     const int64_t need = n_frames / bf + n_clips + 1;
     melt_status st = ensure_chunks(p, which, need);
     if (st != MELT_OK) return st;
-    if (n_clips <= 64)
-        k_schedule64<<<1, 1024, 0, s>>>(d_off, n_clips, p.N, p.H, bf, p.d_chunks[which], p.chunk_cap[which],
-                                        p.d_nchunks + which);
-    else
-        k_schedule<<<1, 1024, 0, s>>>(d_off, n_clips, p.N, p.H, bf, p.d_chunks[which], p.chunk_cap[which],
-                                      p.d_nchunks + which);
-    st = hip_check(hipGetLastError(), "schedule launch");
+    st = enqueue_schedule(p, d_off, n_clips, bf, need, p.d_chunks[which], p.chunk_cap[which], p.d_nchunks + which, s);
     if (st == MELT_OK) {
         p.prepared_frames[which] = n_frames;
         p.prepared_bf[which] = bf;
@@ -457,6 +411,14 @@ SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t 
 static bool split_fits(const Plan &p) {
     return split_planes(p) && p.geoS.n_groups * 32 <= p.N + p.N / 2 + 32 && p.geoS.n_groups <= 512 &&
            split_shape(p.geoS, split_planes(p), (p.M + 7) / 8, p.cu_count, 1 << 20, (int64_t)kSplitChunk << 20).parts > 0;
+}
+
+bool split_self_scheduled(const Plan &p, int64_t est_chunks, int64_t n_frames) {
+    const int P = split_planes(p);
+    const SplitShape h = split_shape(p.geoS, P, (p.M + 7) / 8, p.cu_count, est_chunks, n_frames);
+    if (h.parts == 0 || split_lds(P, p.geoS, h) + kListBytes > (size_t)kMaxLds) return false;
+    const int64_t items = est_chunks * (kSplitChunk / split_sf(h)) * h.parts;
+    return items <= (int64_t)(kListEntries - 1) * split_grid(p, h, items);
 }
 
 static std::vector<Variant> variant_list(const Plan &p) {
@@ -625,9 +587,58 @@ melt_status launch_melt_main(Plan &p, const float *d_wave, float *d_out, float *
     return launch_cepstrum(p, p.d_lmel, n_frames, d_out, s);
 }
 
+static melt_status launch_variant(Plan &p, int variant, const FwdTask &t);
+
 melt_status launch_melt_table(Plan &p, int variant, const Chunk *tab, const int *n_tab, int64_t est_chunks,
                               int64_t n_frames, const float *d_wave, float *d_out, float *d_proj, hipStream_t s) {
-    const FwdTask t{tab, n_tab, est_chunks, n_frames, d_wave, d_out, d_proj, s};
+    return launch_variant(p, variant, FwdTask{tab, n_tab, est_chunks, n_frames, d_wave, d_out, d_proj, s});
+}
+
+// Whether a call's kernel finds its own chunks (schedule.h): one of the kernels that can, at most
+// 64 clips (a wave's lanes), and few enough chunks that each workgroup's share fits its list of
+// kListEntries or ring of kRing.  The shares: est_chunks over the workgroups of a row group (each
+// kernel runs at least cu_count / row groups of them, and a row group is at least 4 tiles), or
+// over the split kernel's items.  Measured at 64 x 30 s (5.3 us of schedule kernel, and the gap
+// after it, saved): see the kernels; one 1 s clip, FP32: 13.1 -> 9.7 us a call.
+static bool self_scheduled(const Plan &p, int variant, int n_clips, int64_t n_frames) {
+    const Variant v = variant_at(p, variant);
+    if (n_clips > 64) return false;
+    const int64_t est = n_frames / v.bf + n_clips, groups = (p.row_tiles + 3) / 4;
+    switch (v.kind) {
+    case V_SPLIT: return split_self_scheduled(p, est, n_frames);
+    case V_H16_PC:
+    case V_F8B_PC: return pc_list_fits(p, v.kind == V_F8B_PC, v.bf) && est * groups <= (int64_t)kListEntries * p.cu_count;
+    case V_H16_AS:
+    case V_H16_KS:
+    case V_F8_AS: return est * groups <= (int64_t)kRing * p.cu_count;
+    default: return false;
+    }
+}
+
+static melt_status launch_melt_clips(Plan &p, int variant, const int64_t *d_off, int n_clips, int64_t n_frames,
+                                     const float *d_wave, float *d_out, float *d_proj, hipStream_t s) {
+    const int bf = melt_chunk_frames(p, variant);
+    const int64_t est = n_frames / bf + n_clips;
+    FwdTask t{nullptr, nullptr, est, n_frames, d_wave, d_out, d_proj, s};
+    t.clips = {d_off, n_clips, p.N, bf, (int)est};
+    return launch_variant(p, variant, t);
+}
+
+// The forward over a batch: without a chunk table where the kernel schedules itself (a batch
+// prepared earlier then stays prepared), through table 0 otherwise.
+melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
+                                float *d_out, float *d_proj, hipStream_t s) {
+    if (!self_scheduled(p, p.tune_variant, n_clips, n_frames)) {
+        const melt_status st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p), n_frames, s);
+        return st == MELT_OK ? launch_melt_main(p, d_wave, d_out, d_proj, s) : st;
+    }
+    if (p.K == 0) return launch_melt_clips(p, p.tune_variant, d_off, n_clips, n_frames, d_wave, d_out, d_proj, s);
+    melt_status st = ensure_lmel(p, n_frames);
+    if (st == MELT_OK) st = launch_melt_clips(p, p.tune_variant, d_off, n_clips, n_frames, d_wave, p.d_lmel, d_proj, s);
+    return st == MELT_OK ? launch_cepstrum(p, p.d_lmel, n_frames, d_out, s) : st;
+}
+
+static melt_status launch_variant(Plan &p, int variant, const FwdTask &t) {
     const Variant v = variant_at(p, variant);
     switch (v.kind) {
     case V_SPLIT: return p.cfg.precision == MELT_PREC_FP32 ? launch_melt_split_f32(p, t) : launch_melt_split_x3(p, t);
@@ -698,9 +709,9 @@ melt_status forward_noalloc(Plan &p, const float *d_wave, const int64_t *d_off, 
     int *n_tab = static_cast<int *>(base);
     Chunk *tab = reinterpret_cast<Chunk *>(static_cast<unsigned char *>(base) + kScratchTable);
     // the schedule kernels write the count unconditionally, so nothing in the scratch needs clearing
-    if (n_clips <= 64) k_schedule64<<<1, 1024, 0, s>>>(d_off, n_clips, p.N, p.H, bf, tab, kScratchChunks, n_tab);
-    else k_schedule<<<1, 1024, 0, s>>>(d_off, n_clips, p.N, p.H, bf, tab, kScratchChunks, n_tab);
-    const melt_status st = hip_check(hipGetLastError(), "schedule launch");
+    if (self_scheduled(p, v, n_clips, n_frames))
+        return launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, d_out, nullptr, s);
+    const melt_status st = enqueue_schedule(p, d_off, n_clips, bf, need, tab, kScratchChunks, n_tab, s);
     if (st != MELT_OK) return st;
     return launch_melt_table(p, v, tab, n_tab, need - 1, n_frames, d_wave, d_out, nullptr, s);
 }

@@ -203,6 +203,12 @@ __global__ __launch_bounds__(512) void k_melt_h16_as(FwdArgs a, const uint4 *__r
     float *span0 = lds_as + scr_off;               // FP32 spans, after the operand rows
     float *span1 = span0 + (nbuf == 2 ? scr_len : 0);
     zero_pad_columns<Conv>(a, bf + a.J - 1, rows, blockDim.x, lo_off);
+    // before the basis tile is in registers
+    __shared__ ChunkRing ring;
+    const int cstep = gridDim.x / rgroups;         // the grid is a multiple of rgroups
+    int c = blockIdx.x / rgroups;
+    const bool own = a.clips.off != nullptr;
+    const int nch = own ? ring_start(a, ring, c, cstep) : *a.n_chunks;
     uint4 A[NS];
     uint4 Al[X3 ? NS : 1];
 #pragma unroll
@@ -215,19 +221,15 @@ __global__ __launch_bounds__(512) void k_melt_h16_as(FwdArgs a, const uint4 *__r
     const int wu = __builtin_amdgcn_readfirstlane(wid);
     const int dma0 = L.full < nw ? L.full : nw / 2;    // first copying wave
     const bool dma_wave = wu >= dma0;
-    const int nch = *a.n_chunks;
-    const int cstep = gridDim.x / rgroups;         // the grid is a multiple of rgroups
-    int c = blockIdx.x / rgroups;
     // prologue: every wave copies the first span; the copying waves also start the second
-    if (c < nch) async_span(a, read_chunk(a.chunks, c), span0);
+    if (c < nch) async_span(a, own ? ring_get(ring, 0) : read_chunk(a.chunks, c), span0);
     int ahead = 0;
     if (nbuf == 2 && dma_wave && c + cstep < nch)
-        ahead = async_span_waves(a, read_chunk(a.chunks, c + cstep), span1, wu - dma0, nw - dma0);
+        ahead = async_span_waves(a, own ? ring_get(ring, 1) : read_chunk(a.chunks, c + cstep), span1, wu - dma0, nw - dma0);
     wait_vm_younger(ahead);
-    __shared__ ChunkRing ring;
     for (int it = 0; c < nch; c += cstep, ++it) {
         const int ri = it % kRing;
-        if (ri == 0) ring_fill(ring, a.chunks, c, cstep, nch);
+        if (ri == 0 && !own) ring_fill(ring, a.chunks, c, cstep, nch);
         float *cur = (it & 1) ? span1 : span0;
         __syncthreads();                           // span of chunk c has landed; rows are free
         const Chunk ch = ring_get(ring, ri);
@@ -592,23 +594,28 @@ __global__ __launch_bounds__(X3 ? 512 : 768) void k_melt_h16_pc(FwdArgs a, const
     unsigned short *rows0 = reinterpret_cast<unsigned short *>(lds_hpc);
     unsigned short *rows1 = rows0 + rows_len;
     float *span = lds_hpc + scr_off;
-    const int nch = *a.n_chunks;
     const int cstep = gridDim.x / rgroups;
     const int c0 = blockIdx.x / rgroups;
+    // a kernel that schedules itself has the descriptors of all its chunks in a list of its own,
+    // and the slots below are the list's
+    const bool own = a.clips.off != nullptr;
+    Chunk *slots = own ? reinterpret_cast<Chunk *>(reinterpret_cast<char *>(lds_hpc) + a.list_off) : dslot;
+    const int smask = own ? kListEntries - 1 : 3;
+    const int nch = own ? list_start(a, slots, c0 + (int64_t)(threadIdx.x & 63) * cstep) : *a.n_chunks;
     zero_pad_columns<Conv>(a, bf + a.J - 1, rows0, blockDim.x, lo_off);
     zero_pad_columns<Conv>(a, bf + a.J - 1, rows1, blockDim.x, lo_off);
-    if (wid == nc && lane < 3 && c0 + lane * cstep < nch) dslot[lane] = a.chunks[c0 + lane * cstep];
+    if (!own && wid == nc && lane < 3 && c0 + lane * cstep < nch) dslot[lane] = a.chunks[c0 + lane * cstep];
     // the first chunk is copied and converted by every wave (blocks w, w + nw, ...); after a
     // barrier the producers start the copy of the second
     if (c0 < nch) {
-        const Chunk ch = read_chunk(a.chunks, c0);
+        const Chunk ch = own ? ring_slot(slots, 0) : read_chunk(a.chunks, c0);
         copy_owned(a, ch, span, wid, nw);
         async_wait();
         convert_owned<Conv>(a, ch, span, rows0, lo_off, wid, nw);
     }
     __syncthreads();
     if (producer) {
-        if (c0 + cstep < nch) copy_owned(a, read_chunk(a.chunks, c0 + cstep), span, pw, np);
+        if (c0 + cstep < nch) copy_owned(a, own ? ring_slot(slots, 1) : read_chunk(a.chunks, c0 + cstep), span, pw, np);
         for (int it = 0; c0 + it * cstep < nch; ++it) {
             __syncthreads();                       // chunk it converted; buffer (it + 1) & 1 free
             const int c = c0 + it * cstep;
@@ -618,17 +625,17 @@ __global__ __launch_bounds__(X3 ? 512 : 768) void k_melt_h16_pc(FwdArgs a, const
             // that reached HBM and a wait for every outstanding memory operation), loaded
             // through the scalar cache so that storing it waits for no copy
             uint4 nd0 = {}, nd1 = {};
-            const bool load_desc = wid == nc && c + 3 * cstep < nch;
+            const bool load_desc = !own && wid == nc && c + 3 * cstep < nch;
             async_wait();                          // this producer's copies of chunk it + 1
             if (load_desc) load_chunk_scalar(a.chunks, c + 3 * cstep, nd0, nd1);
-            const Chunk ch1 = ring_slot(dslot, (it + 1) & 3);
+            const Chunk ch1 = ring_slot(slots, (it + 1) & smask);
             convert_owned<Conv>(a, ch1, span, ((it + 1) & 1) ? rows1 : rows0, lo_off, pw, np);
             if (load_desc && lane == 0) {
                 uint4 *dst = reinterpret_cast<uint4 *>(dslot + ((it + 3) & 3));
                 dst[0] = nd0;
                 dst[1] = nd1;
             }
-            if (c + 2 * cstep < nch) copy_owned(a, ring_slot(dslot, (it + 2) & 3), span, pw, np);
+            if (c + 2 * cstep < nch) copy_owned(a, ring_slot(slots, (it + 2) & smask), span, pw, np);
         }
         return;
     }
@@ -644,7 +651,7 @@ __global__ __launch_bounds__(X3 ? 512 : 768) void k_melt_h16_pc(FwdArgs a, const
     }
     for (int it = 0; c0 + it * cstep < nch; ++it) {
         __syncthreads();                           // chunk it converted; buffer (it + 1) & 1 free
-        const Chunk ch = ring_slot(dslot, it & 3);
+        const Chunk ch = ring_slot(slots, it & smask);
         const unsigned short *rows = (it & 1) ? rows1 : rows0;
         const int nft = (ch.n_frames + 31) >> 5;
         for (int ft = 0; ft < nft; ++ft) {
@@ -684,22 +691,24 @@ __global__ __launch_bounds__(512) void k_melt_h16_ks(FwdArgs a, const uint4 *__r
     float *scratch = lds_ks + scr_off;
     float *red = lds_ks + red_off + rl * 2048;     // [2 tiles][16 registers][64 lanes]
     zero_pad_columns<Conv>(a, bf + a.J - 1, rows, blockDim.x, 0);
+    // before the basis tile is in registers
+    __shared__ ChunkRing ring;
+    const int cstep = gridDim.x / rgroups;
+    int c = blockIdx.x / rgroups;
+    const bool own = a.clips.off != nullptr;
+    const int nch = own ? ring_start(a, ring, c, cstep) : *a.n_chunks;
     uint4 A[NS0];
     const uint4 Al[1] = {};
 #pragma unroll
     for (int s = 0; s < NS0; ++s)
         A[s] = (kh == 0 || s < NS1) ? bhi[((size_t)rt * G + kh * NS0 + s) * 64 + lane] : uint4{};
-    const int nch = *a.n_chunks;
-    const int cstep = gridDim.x / rgroups;
     const int wu = __builtin_amdgcn_readfirstlane(wid);
     const bool copier = wu >= gt_n;                // second-half waves: no output stores
-    int c = blockIdx.x / rgroups;
-    if (c < nch) async_span(a, read_chunk(a.chunks, c), scratch);
+    if (c < nch) async_span(a, own ? ring_get(ring, 0) : read_chunk(a.chunks, c), scratch);
     async_wait();
-    __shared__ ChunkRing ring;
     for (int it = 0; c < nch; c += cstep, ++it) {
         const int ri = it % kRing;
-        if (ri == 0) ring_fill(ring, a.chunks, c, cstep, nch);
+        if (ri == 0 && !own) ring_fill(ring, a.chunks, c, cstep, nch);
         __syncthreads();                           // span of chunk c is in scratch; rows are free
         const Chunk ch = ring_get(ring, ri);
         const Chunk chn = ring_get(ring, ri + 1);
@@ -938,6 +947,12 @@ size_t pc_x3_lds_bytes(const Plan &p, int bf) {
     return 4 * pc_rows_bytes(p, bf) + (size_t)(bf + p.geo16.J - 1) * p.H * 4;
 }
 
+bool pc_list_fits(const Plan &p, bool f8b, int bf) {
+    const size_t lds = f8b ? f8b_pc_lds_bytes(p, bf) + f8b_pc_static_bytes()
+                           : (prec_split(p) ? pc_x3_lds_bytes(p, bf) : pc_lds_bytes(p, bf)) + 4 * sizeof(Chunk);
+    return lds + 16 + kListBytes <= (size_t)kMaxLds;
+}
+
 template <class Conv, int NS, bool X3, bool F16>
 static melt_status launch_pc_ns(Plan &p, const FwdArgs &a, const GroupTableBig &gt, size_t lds, int grid, int bf,
                                 int rg, hipStream_t s) {
@@ -1022,12 +1037,15 @@ melt_status launch_melt_h16(Plan &p, const FwdTask &t, H16Kind kind, int bf, int
         const size_t lds = x3 ? pc_x3_lds_bytes(p, bf) : pc_lds_bytes(p, bf);
         if (lds + 4 * sizeof(Chunk) > (size_t)kMaxLds) return set_error(MELT_E_UNSUPPORTED, "frame geometry exceeds LDS");
         const int rg = x3 ? pc_x3_row_groups(p) : row_groups(p);
+        FwdArgs a2 = a;
+        a2.list_off = (int)((lds + 15) & ~size_t(15));
+        const size_t lds2 = t.clips.off ? (size_t)a2.list_off + kListBytes : lds;
         const int per_group = (int)std::max<int64_t>(1, std::min<int64_t>(t.est_chunks, ((int64_t)p.cu_count + rg - 1) / rg));
         const int grid = per_group * rg;
-        if (x3 && f16) return launch_pc<ConvF16X3, true, true>(p, a, gt, lds, grid, bf, rg, s);
-        if (x3) return launch_pc<ConvBF16X3, true, false>(p, a, gt, lds, grid, bf, rg, s);
-        if (f16) return launch_pc<ConvF16, false, true>(p, a, gt, lds, grid, bf, rg, s);
-        return launch_pc<ConvBF16, false, false>(p, a, gt, lds, grid, bf, rg, s);
+        if (x3 && f16) return launch_pc<ConvF16X3, true, true>(p, a2, gt, lds2, grid, bf, rg, s);
+        if (x3) return launch_pc<ConvBF16X3, true, false>(p, a2, gt, lds2, grid, bf, rg, s);
+        if (f16) return launch_pc<ConvF16, false, true>(p, a2, gt, lds2, grid, bf, rg, s);
+        return launch_pc<ConvBF16, false, false>(p, a2, gt, lds2, grid, bf, rg, s);
     }
     if (kind == H16_PIPELINED) {
         if (!pp_fits(p)) return set_error(MELT_E_UNSUPPORTED, "producer/consumer kernel: no producer waves");

@@ -239,17 +239,29 @@ __device__ __forceinline__ int64_t split_scalar(const void *base, int64_t i) {
 struct SplitForward {
     FwdArgs a;
     SplitGeo g;
-    __device__ SplitItem item(int w, int SF) const {
+    // Whether the kernel finds its own chunks: then list[k] is the chunk of the workgroup's item k.
+    __device__ __forceinline__ bool lists() const { return a.clips.off != nullptr; }
+    __device__ __forceinline__ int start(Chunk *list) const {
+        const int w = blockIdx.x + (threadIdx.x & 63) * gridDim.x;
+        return list_start(a, list, w / (g.nsub * g.parts));
+    }
+    __device__ __forceinline__ SplitItem item(int w, int k, const Chunk *list, int SF) const {
         const int ci = w / (g.nsub * g.parts);
         const int f0 = ((w - ci * g.nsub * g.parts) / g.parts) * SF;
         static_assert(sizeof(Chunk) == 32, "four int64 per entry");
+        if (lists()) {
+            const Chunk e = list[k];
+            const int nf = min(SF, __builtin_amdgcn_readfirstlane(e.n_frames) - f0);
+            return {uniform64(e.sample_start) + (int64_t)f0 * a.H, uniform64(e.sample_end), uniform64(e.out_row) + f0,
+                    nf > 0 ? nf : 0, 0};
+        }
         const int64_t st = split_scalar(a.chunks, 4 * (int64_t)ci), en = split_scalar(a.chunks, 4 * (int64_t)ci + 1);
         const int64_t row = split_scalar(a.chunks, 4 * (int64_t)ci + 2);
         const int nf = min(SF, (int)split_scalar(a.chunks, 4 * (int64_t)ci + 3) - f0);      // low half: n_frames
         return {st + (int64_t)f0 * a.H, en, row + f0, nf > 0 ? nf : 0, 0};
     }
     template <class Op, int FT, int RT>
-    __device__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+    __device__ __forceinline__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
 };
 
 // Output values of the two bins of each tile of one frame.
@@ -371,31 +383,32 @@ void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
     constexpr int P = Op::P, NP = Op::NP, SF = WF * FT * 16;
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nitems = *a.n_chunks * g.nsub * g.parts;
+    Chunk *list = reinterpret_cast<Chunk *>(reinterpret_cast<char *>(rows) + a.list_off);
+    const int nitems = (job.lists() ? job.start(list) : *a.n_chunks) * g.nsub * g.parts;
     const int G = gridDim.x;                       // a multiple of parts: the row part is the workgroup's
-    int w = blockIdx.x;
+    int w = blockIdx.x, k = 0;                     // item, and how many the workgroup had before it
     if (wid >= 4) {
         const int lt = (int)threadIdx.x - 256;
         const float inv_vr = 4.0f / (float)a.Hp;
         unsigned pl[PV][2 * P];
         SplitItem it{};
         if (w < nitems) {
-            it = job.item(w, SF);
+            it = job.item(w, 0, list, SF);
             split_load<Op, PV>(a, it.start, it.lo, it.end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
             split_write<Op, PV>(a, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl, rows);
         }
         __syncthreads();                           // rows of the first item ready
-        for (; w < nitems; w += G) {
+        for (; w < nitems; w += G, ++k) {
             const bool more = w + G < nitems;
             if (more) {
-                it = job.item(w + G, SF);
+                it = job.item(w + G, k + 1, list, SF);
                 split_load<Op, PV>(a, it.start, it.lo, it.end, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl);
             }
             // split before the barrier, not between the two
 #pragma unroll
             for (int v = 0; v < PV; ++v)
 #pragma unroll
-                for (int k = 0; k < 2 * P; ++k) asm volatile("" : "+v"(pl[v][k]));
+                for (int e = 0; e < 2 * P; ++e) asm volatile("" : "+v"(pl[v][e]));
             __syncthreads();                       // A: the multiply waves are done with the rows
             if (more) split_write<Op, PV>(a, it.nf ? it.nf + a.J - 1 : 0, lt, inv_vr, pl, rows);
             __syncthreads();                       // B: rows of the next item ready
@@ -430,8 +443,8 @@ void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
     __syncthreads();                               // rows of the first item ready
     const int fbase = wf * FT * 16;
     const int la0 = (fbase + (lane & 15)) * a.S + 8 * (lane >> 4);
-    for (; w < nitems; w += G) {
-        const SplitItem it = job.item(w, SF);
+    for (; w < nitems; w += G, ++k) {
+        const SplitItem it = job.item(w, k, list, SF);
         // two planes: a k-group's three products are summed on their own and added once, behind the
         // next tile's first MFMAs (a third of the roundings at the running sum's magnitude)
         f32x4 acc[FT][RT], sum[2][FT];
@@ -472,22 +485,22 @@ void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
                     for (int r = 0; r < RT; ++r) {
                         const int slot = (u * RT + r) % D;
 #pragma unroll
-                        for (int k = 0; k < NP; ++k) {
+                        for (int m = 0; m < NP; ++m) {
 #pragma unroll
                             for (int f = 0; f < FT; ++f) {
                                 if constexpr (P == 3)
-                                    acc[f][r] = Op::mma(A[slot][Op::pa[k]], B[f][Op::pb[k]], acc[f][r]);
+                                    acc[f][r] = Op::mma(A[slot][Op::pa[m]], B[f][Op::pb[m]], acc[f][r]);
                                 else
-                                    sum[r & 1][f] = Op::mma(A[slot][Op::pa[k]], B[f][Op::pb[k]], k ? sum[r & 1][f] : f32x4{});
+                                    sum[r & 1][f] = Op::mma(A[slot][Op::pa[m]], B[f][Op::pb[m]], m ? sum[r & 1][f] : f32x4{});
                             }
-                            if (P == 2 && k == 0 && r > 0) {
+                            if (P == 2 && m == 0 && r > 0) {
 #pragma unroll
                                 for (int f = 0; f < FT; ++f) acc[f][r - 1] += sum[(r - 1) & 1][f];
                             }
                             if (r == RT - 1) {
 #pragma unroll
                                 for (int p = 0; p < P; ++p)
-                                    if (Op::last_of_plane[p] == k) {
+                                    if (Op::last_of_plane[p] == m) {
                                         __builtin_amdgcn_sched_barrier(0);
                                         load_b(p, nat);
                                         __builtin_amdgcn_sched_barrier(0);
@@ -536,6 +549,11 @@ inline size_t split_lds(int P, const Geometry &g, const SplitShape &h) {
 // The shape for n_frames frames in est_chunks chunks of kSplitChunk (melt_fwd.hip).
 SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t est_chunks, int64_t n_frames);
 
+// workgroups: a multiple of the row parts
+inline int split_grid(const Plan &p, const SplitShape &h, int64_t items) {
+    return std::max(persistent_grid(p, items, 1) / h.parts, 1) * h.parts;
+}
+
 template <class Job, class Op, int FT, int RT, int WF, int PV>
 melt_status launch_split_k(const Job &job, const void *pack, size_t lds, int grid, hipStream_t s) {
     allow_lds(k_melt_split<Job, Op, FT, RT, WF, PV>);
@@ -549,8 +567,12 @@ melt_status launch_split(const Plan &p, Job job, const Geometry &geo, const Spli
     if (h.parts == 0) return set_error(MELT_E_UNSUPPORTED, "split kernel: unsupported geometry");
     job.g.nsub = kSplitChunk / split_sf(h);
     job.g.parts = h.parts;
-    const int grid = std::max(persistent_grid(p, est_chunks * job.g.nsub * h.parts, 1) / h.parts, 1) * h.parts;
-    const size_t lds = split_lds(Op::P, geo, h);
+    const int grid = split_grid(p, h, est_chunks * job.g.nsub * h.parts);
+    size_t lds = split_lds(Op::P, geo, h);
+    if (job.a.clips.off) {
+        job.a.list_off = (int)lds;                 // a multiple of 16
+        lds += kListBytes;
+    }
     constexpr int PW = Op::P == 3 ? 26 : 34;       // the wide staging of 128-frame items
 #define SPLIT_CASE(FT, RT, WF, PV) \
     if (h.ft == FT && h.rt == RT && h.wf == WF && h.pv == PV) return launch_split_k<Job, Op, FT, RT, WF, PV>(job, pk, lds, grid, s);

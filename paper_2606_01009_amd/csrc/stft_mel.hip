@@ -15,7 +15,7 @@
 // butterflies whose twiddles are compile-time constants.
 #include <cmath>
 
-#include "melt_internal.h"
+#include "schedule.h"
 
 namespace melt {
 
@@ -270,7 +270,11 @@ struct StftArgs {
     int fb_nnz;
     int M, H;
     float eps;
+    ClipTable clips;          // off set: every wave finds its own chunks (chunks and n_chunks not read)
+    int list_off;             // bytes from the dynamic LDS to the waves' chunk lists
 };
+
+constexpr int kStftList = 8;      // chunks of one wave at most when it finds them itself
 
 // output map of kind KIND (a melt_output); ln from the hardware base-2 logarithm, whose
 // argument v + eps >= eps is a normal FP32 number
@@ -346,10 +350,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE)
     const int p3 = lane / TPF, k1 = lane - p3 * TPF;                  // step-3 role
     const bool act3 = p3 < FPW && k1 < N1;
 
-    const int nch = *a.n_chunks;
     const int nw = gridDim.x * WAVES;
     int c = blockIdx.x * WAVES + wid;
+    // (the 1024-point shape has no register to spare for it: it spilled)
+    const bool own = N1 != 32 && a.clips.off != nullptr;
+    Chunk *list = reinterpret_cast<Chunk *>(reinterpret_cast<char *>(smem) + a.list_off) + kStftList * wid;
+    const int nch = own ? chunk_list(a.clips, a.H, c + (int64_t)lane * nw, kStftList, list, true) : *a.n_chunks;
+    wave_sync();
     if (c >= nch) return;
+    // the wave's chunk k (index c), wave-uniform
+    auto chunk_at = [&](int k) {
+        if (!own) return a.chunks[c];
+        const Chunk e = list[k];
+        return Chunk{uniform64(e.sample_start), uniform64(e.sample_end), uniform64(e.out_row),
+                     __builtin_amdgcn_readfirstlane(e.n_frames), 0};
+    };
+    int kth = 0;
     // samples of one sub-task for this lane: frames 2 p1 and 2 p1 + 1 at points N2 n1 + n2
     float xa[N1], xb[N1];
     auto load = [&](const Chunk &ch, int sub) {
@@ -365,7 +381,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE)
             xb[n1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vb, N2 * n1 * 4, 0));
         }
     };
-    Chunk ch = a.chunks[c];
+    Chunk ch = chunk_at(0);
     int sub = 0;
     if (PREFETCH) load(ch, 0);
     for (;;) {
@@ -379,7 +395,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE)
             sub = 0;
             c += nw;
             more = c < nch;
-            if (more) ch = a.chunks[c];
+            if (more) ch = chunk_at(++kth);
         }
         // step 1: window, N1-point DFTs over n1, four-step twiddle, store as [k1][n2]
         cf z[N1];
@@ -613,6 +629,13 @@ int stft_chunk_frames(const Plan &p) {
     return stft_shape(p.N, sh) ? 2 * sh.FPW * sh.SUB : 32;
 }
 
+// workgroups per CU that LDS allows, and the persistent grid of a batch
+static int stft_per_cu(size_t lds) { return std::max(1, std::min(4, (int)((160 * 1024) / std::max<size_t>(lds, 1)))); }
+static int stft_grid(const Plan &p, size_t lds, int64_t n_frames, int bf, int n_clips) {
+    const int64_t est = (n_frames / bf + n_clips + kStftWaves - 1) / kStftWaves;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(est, (int64_t)p.cu_count * stft_per_cu(lds)));
+}
+
 // Chunk size for a batch of n_frames, in whole sub-tasks (1 to SUB).  Waves take chunks from
 // a queue, so a batch runs in ceil(chunks / resident waves) rounds, each as long as one chunk.
 // A short batch (at most four one-sub-task rounds) takes one sub-task per chunk, which
@@ -625,8 +648,7 @@ int stft_batch_chunk_frames(const Plan &p, int64_t n_frames) {
     if (!stft_shape(p.N, sh)) return 32;
     const int sub = 2 * sh.FPW;
     const size_t lds = stft_lds_bytes(sh, p.M, p.fb_nnz);
-    const int per_cu = std::max(1, std::min(4, (int)((160 * 1024) / std::max<size_t>(lds, 1))));
-    const int64_t waves = (int64_t)p.cu_count * per_cu * kStftWaves;
+    const int64_t waves = (int64_t)p.cu_count * stft_per_cu(lds) * kStftWaves;
     const int64_t tasks = (n_frames + sub - 1) / sub;
     if (tasks <= 4 * waves) return sub;
     int best_s = 1;
@@ -642,16 +664,39 @@ int stft_batch_chunk_frames(const Plan &p, int64_t n_frames) {
     return best_s * sub;
 }
 
+static melt_status launch_stft(Plan &p, const ClipTable &clips, int64_t n_frames, int bf, int n_clips, const float *d_wave,
+                               float *d_out, hipStream_t s);
+
 melt_status launch_stft_main(Plan &p, const float *d_wave, float *d_out, hipStream_t s) {
+    return launch_stft(p, ClipTable{}, p.prepared_frames[1], p.prepared_bf[1], p.prepared_clips[1], d_wave, d_out, s);
+}
+
+// Without a chunk table where every wave can find its chunks itself: at most 64 clips and
+// kStftList chunks per wave, with room for the lists that costs no workgroup per CU.
+melt_status launch_stft_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
+                                float *d_out, hipStream_t s) {
+    StftShape sh;
+    const int bf = n_frames > 0 ? std::min(stft_chunk_frames(p), stft_batch_chunk_frames(p, n_frames)) : 32;
+    if (n_clips <= 64 && stft_shape(p.N, sh) && sh.N1 != 32 && p.d_twiddle) {
+        const size_t lds = stft_lds_bytes(sh, p.M, p.fb_nnz), with = lds + 16 + kStftWaves * kStftList * sizeof(Chunk);
+        const int64_t est = n_frames / bf + n_clips;
+        if (stft_per_cu(with) == stft_per_cu(lds) && with <= 160 * 1024 &&
+            est <= (int64_t)kStftList * kStftWaves * stft_grid(p, lds, n_frames, bf, n_clips))
+            return launch_stft(p, ClipTable{d_off, n_clips, p.N, bf, (int)est}, n_frames, bf, n_clips, d_wave, d_out, s);
+    }
+    const melt_status st = launch_schedule(p, 1, d_off, n_clips, stft_chunk_frames(p), n_frames, s);
+    return st == MELT_OK ? launch_stft_main(p, d_wave, d_out, s) : st;
+}
+
+static melt_status launch_stft(Plan &p, const ClipTable &clips, int64_t n_frames, int bf, int n_clips, const float *d_wave,
+                               float *d_out, hipStream_t s) {
     StftShape sh;
     if (!stft_shape(p.N, sh) || !p.d_twiddle)
         return set_error(MELT_E_UNSUPPORTED, "comparator FFT supports n_fft in {256, 400, 512, 1024, 1200}");
-    const int64_t n_frames = p.prepared_frames[1];
     if (n_frames < 0) return set_error(MELT_E_INVALID_ARG, "no batch prepared");
     if (n_frames == 0) return MELT_OK;
-    const size_t lds = stft_lds_bytes(sh, p.M, p.fb_nnz);
+    size_t lds = stft_lds_bytes(sh, p.M, p.fb_nnz);
     if (lds > 160 * 1024) return set_error(MELT_E_UNSUPPORTED, "comparator LDS too large");
-    const int bf = p.prepared_bf[1];
     // MFCC: the log-Mel rows go to the plan workspace, then the DCT-II product to d_out
     float *mel_out = d_out;
     if (p.K > 0) {
@@ -674,9 +719,15 @@ melt_status launch_stft_main(Plan &p, const float *d_wave, float *d_out, hipStre
     a.M = p.M;
     a.H = p.H;
     a.eps = (float)p.cfg.log_eps;
-    const int per_cu = std::max(1, std::min(4, (int)((160 * 1024) / lds)));
-    const int64_t est = (n_frames / bf + p.prepared_clips[1] + kStftWaves - 1) / kStftWaves;
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(est, (int64_t)p.cu_count * per_cu));
+    const int grid = stft_grid(p, lds, n_frames, bf, n_clips);
+    a.clips = clips;
+    a.list_off = 0;
+    if (clips.off) {
+        // after the dynamic part (lds counts the static twiddles too)
+        const size_t dyn = (lds - (size_t)sh.N1 * sh.N2 * 8 + 15) & ~size_t(15);
+        a.list_off = (int)dyn;
+        lds = dyn + kStftWaves * kStftList * sizeof(Chunk) + (size_t)sh.N1 * sh.N2 * 8;
+    }
     melt_status st;
     switch (p.N) {
     case 400: st = launch_shape<20, 20, 8>(a, p.kern_out, lds, grid, s); break;
