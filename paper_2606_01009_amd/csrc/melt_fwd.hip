@@ -316,7 +316,7 @@ static melt_status enqueue_schedule(const Plan &p, const int64_t *d_off, int n_c
 }
 
 melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clips, int bf_max, int64_t n_frames,
-                            hipStream_t s) {
+                            hipStream_t s, int variant) {
     // Chunks of at most bf_max frames (the kernel's LDS image).  The comparator sizes its
     // chunks to the batch (whole sub-tasks, a few chunks per resident wave); measured, the
     // same for the MelT kernels costs more in per-chunk overhead than it gains, so their
@@ -331,7 +331,7 @@ melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clip
         p.prepared_frames[which] = n_frames;
         p.prepared_bf[which] = bf;
         p.prepared_clips[which] = n_clips;
-        if (which == 0) p.prepared_variant = p.tune_variant;
+        if (which == 0) p.prepared_variant = variant < 0 ? p.tune_variant : variant;
     }
     return st;
 }
@@ -343,7 +343,8 @@ melt_status launch_frame_offsets(const int64_t *d_off, int n_clips, int N, int H
 
 // Kernel variants of a plan, in the order the autotuner times them (p.tune_variant selects;
 // the first one is the default):
-//   FP32       frame-split with staging waves, frame-split with register prefetch
+//   FP32       operand planes (melt_split.h), frame-split on FP32 MFMA with staging waves, the same
+//              with register prefetch
 //   BF16/FP16  the 12-wave producer/consumer kernel (96- or 64-frame chunks) where its
 //              register tiles and LDS fit; row pairs (two basis tiles per wave) where they fit;
 //              row-split with direct-to-LDS staging (one span buffer: 128- then 64-frame
@@ -354,13 +355,14 @@ melt_status launch_frame_offsets(const int64_t *d_off, int n_clips, int N, int H
 //   BF16X3 / FP16X3  the 8-wave producer/consumer kernel (hi and lo tiles, 64-frame chunks)
 //              where it fits, then as above without row pairs and K-split, with one-span
 //              chunks of 96 then 64 frames
-//   FP8        row-split with direct-to-LDS staging (the largest chunk that fits LDS; 64-frame
+//   FP8        frame-split (hops that are multiples of 32, up to 8 row tiles), row-split with
+//              direct-to-LDS staging (the largest chunk that fits LDS; 64-frame
 //              chunks at two workgroups per CU), row-split with register staging, then the
 //              producer/consumer kernel (first beyond 8 row tiles, which the others do not take)
 //   FP8 with 32-sample block scales  producer/consumer block-scaled kernel, then the
 //              one-buffer block-scaled kernel with 160- and 128-frame chunks
 enum VariantKind { V_F32_WS, V_F32_FS, V_H16_PP, V_H16_AS, V_H16_AP, V_H16_RS, V_H16_KS, V_H16_FS, V_F8_AS, V_F8_RS,
-                   V_F8B_AS, V_F8B_PC, V_H16_PC, V_F8_PC, V_SPLIT };
+                   V_F8B_AS, V_F8B_PC, V_H16_PC, V_F8_PC, V_SPLIT, V_F8_FS };
 struct Variant {
     VariantKind kind;
     int bf;          // frames per chunk
@@ -437,6 +439,7 @@ static std::vector<Variant> variant_list(const Plan &p) {
         const int ng8 = (p.N + 63) / 64;
         const bool pc = (ng8 == 4 || ng8 == 7 || ng8 == 8) && p.H % 4 == 0 && p.N % 4 == 0 &&
                         f8_pc_lds_bytes(p, 64) + 4 * sizeof(Chunk) + 8 * 32 * 4 <= (size_t)kMaxLds;
+        if (f8fs_fits(p)) v.push_back({V_F8_FS, 128});
         if (pc && p.row_tiles > 8) v.push_back({V_F8_PC, 64});
         for (int bf : {128, 96, 64, 32})
             if (f8_as_lds_bytes(p, bf) + kRingBytes <= (size_t)kMaxLds) {
@@ -479,6 +482,9 @@ static std::vector<Variant> variant_list(const Plan &p) {
         const bool pc_x3 = x3 && pc_fits(p) && pc_x3_lds_bytes(p, 64) + 4 * sizeof(Chunk) <= (size_t)kMaxLds;
         const bool pc_x3_first = pc_x3 && (p.row_tiles + 4) / 5 <= 4;
         if (pc_x3_first) v.push_back({V_H16_PC, 64});
+        // frame lengths without a register tile for it (N = 512, 480, ...): operand planes first
+        // (512 ragged clips, N 512, M 128: 942 -> 676 us BF16X3; one 1 s clip: 23.2 -> 10.1 us)
+        if (x3 && !pc_fits(p) && h16_fs_fits(p) && split_fits(p)) v.push_back({V_SPLIT, kSplitChunk});
         if (!x3 && ap_fits(p) && as_lds_bytes(p, 128) + kRingBytes <= (size_t)kMaxLds) v.push_back({V_H16_AP, 128});
         if (as_fits(p)) {
             // one span buffer (128 then 64 frames per chunk; 96 then 64 for BF16X3), then two
@@ -516,7 +522,6 @@ static std::vector<Variant> variant_list(const Plan &p) {
         if (pc_x3 && !pc_x3_first) v.push_back({V_H16_PC, 64});
         // frame-split: the fallback for every 16-bit precision (the split ones only where no
         // register-tile kernel applies)
-        if (x3 && v.empty() && h16_fs_fits(p) && split_fits(p)) v.push_back({V_SPLIT, kSplitChunk});
         if (!x3 || v.empty()) v.push_back({V_H16_FS, kBF32});
     }
     }
@@ -559,6 +564,7 @@ const char *forward_variant_name(const Plan &p, int i) {
                     : v.kind == V_H16_KS ? "h16-k-split-lds-dma"
                     : v.kind == V_H16_FS ? "h16-frame-split"
                     : v.kind == V_F8_AS  ? "f8-row-split-lds-dma"
+                    : v.kind == V_F8_FS  ? "f8-frame-split"
                     : v.kind == V_F8_PC  ? "f8-producer-consumer-lds-dma"
                     : v.kind == V_F8B_AS ? "f8-block-scaled-lds-dma"
                     : v.kind == V_F8B_PC ? "f8-block-scaled-producer-consumer-lds-dma"
@@ -608,6 +614,7 @@ static bool self_scheduled(const Plan &p, int variant, int n_clips, int64_t n_fr
     case V_SPLIT: return split_self_scheduled(p, est, n_frames);
     case V_H16_PC:
     case V_F8B_PC: return pc_list_fits(p, v.kind == V_F8B_PC, v.bf) && est * groups <= (int64_t)kListEntries * p.cu_count;
+    case V_F8_FS: return est <= (int64_t)kListEntries * p.cu_count;
     case V_H16_AS:
     case V_H16_KS:
     case V_F8_AS: return est * groups <= (int64_t)kRing * p.cu_count;
@@ -624,17 +631,31 @@ static melt_status launch_melt_clips(Plan &p, int variant, const int64_t *d_off,
     return launch_variant(p, variant, t);
 }
 
+// The variant of one call.  The FP8 kernels with per-frame scales give the same bits, so unless a
+// variant is pinned a call may take either: where 64-frame chunks fill at most one round of the
+// CUs, the row-split kernel on those spreads wider and starts without the basis in LDS (16 x 4 s:
+// 11.9 us against 14.1 us frame-split at 80 Mel bins, 12.3 against 16.5 at 128); below 4 row
+// tiles the frame-split one is the faster there too (10.5 against 11.9 us at 24 Mel bins).
+static int call_variant(const Plan &p, int n_clips, int64_t n_frames) {
+    const int v = p.tune_variant;
+    if (p.tune_pinned || variant_at(p, v).kind != V_F8_FS || p.row_tiles < 4 || n_frames / 64 + n_clips > p.cu_count) return v;
+    for (int i = 0; i < p.n_variants; ++i)
+        if (p.var_kind[i] == V_F8_AS && p.var_bf[i] == 64) return i;
+    return v;
+}
+
 // The forward over a batch: without a chunk table where the kernel schedules itself (a batch
 // prepared earlier then stays prepared), through table 0 otherwise.
 melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, float *d_proj, hipStream_t s) {
-    if (!self_scheduled(p, p.tune_variant, n_clips, n_frames)) {
-        const melt_status st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p), n_frames, s);
+    const int v = call_variant(p, n_clips, n_frames);
+    if (!self_scheduled(p, v, n_clips, n_frames)) {
+        const melt_status st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p, v), n_frames, s, v);
         return st == MELT_OK ? launch_melt_main(p, d_wave, d_out, d_proj, s) : st;
     }
-    if (p.K == 0) return launch_melt_clips(p, p.tune_variant, d_off, n_clips, n_frames, d_wave, d_out, d_proj, s);
+    if (p.K == 0) return launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, d_out, d_proj, s);
     melt_status st = ensure_lmel(p, n_frames);
-    if (st == MELT_OK) st = launch_melt_clips(p, p.tune_variant, d_off, n_clips, n_frames, d_wave, p.d_lmel, d_proj, s);
+    if (st == MELT_OK) st = launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, p.d_lmel, d_proj, s);
     return st == MELT_OK ? launch_cepstrum(p, p.d_lmel, n_frames, d_out, s) : st;
 }
 
@@ -652,6 +673,7 @@ static melt_status launch_variant(Plan &p, int variant, const FwdTask &t) {
     case V_H16_KS: return launch_melt_h16(p, t, H16_K_SPLIT, v.bf);
     case V_H16_FS: return launch_melt_h16(p, t, H16_FRAME_SPLIT, v.bf);
     case V_F8_AS: return launch_melt_f8(p, t, true, v.bf);
+    case V_F8_FS: return launch_melt_f8_fs(p, t);
     case V_F8_PC: return launch_melt_f8_pc(p, t, v.bf);
     case V_F8_RS: return launch_melt_f8(p, t, false, v.bf);
     case V_F8B_AS: return launch_melt_f8b(p, t, v.bf, false);
@@ -709,8 +731,9 @@ melt_status forward_noalloc(Plan &p, const float *d_wave, const int64_t *d_off, 
     int *n_tab = static_cast<int *>(base);
     Chunk *tab = reinterpret_cast<Chunk *>(static_cast<unsigned char *>(base) + kScratchTable);
     // the schedule kernels write the count unconditionally, so nothing in the scratch needs clearing
-    if (self_scheduled(p, v, n_clips, n_frames))
-        return launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, d_out, nullptr, s);
+    const int vc = call_variant(p, n_clips, n_frames);
+    if (self_scheduled(p, vc, n_clips, n_frames))
+        return launch_melt_clips(p, vc, d_off, n_clips, n_frames, d_wave, d_out, nullptr, s);
     const melt_status st = enqueue_schedule(p, d_off, n_clips, bf, need, tab, kScratchChunks, n_tab, s);
     if (st != MELT_OK) return st;
     return launch_melt_table(p, v, tab, n_tab, need - 1, n_frames, d_wave, d_out, nullptr, s);

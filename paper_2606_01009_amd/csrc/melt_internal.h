@@ -103,6 +103,7 @@ struct Plan {
     // tuning
     int cu_count = 256;
     int tune_variant = 0;                          // index of the chosen kernel variant
+    bool tune_pinned = false;                      // chosen by melt_set_variant or the autotuner
     int tune_grid = 0;                             // workgroups per CU (0 = kernel default)
     std::string last_tune;
 };
@@ -135,8 +136,9 @@ melt_status pack_tables_upload(Plan &p);         // k-group tables of the pack k
 melt_status pack_basis(Plan &p, hipStream_t s);   // enqueue only: no allocation, no synchronisation
 melt_status pack_basis_dx(Plan &p, hipStream_t s);
 melt_status ensure_chunks(Plan &p, int which, int64_t needed);
+// (variant: the MelT kernel variant that table 0 is for, -1 = the plan's)
 melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clips, int bf, int64_t n_frames,
-                            hipStream_t s);
+                            hipStream_t s, int variant = -1);
 melt_status launch_frame_offsets(const int64_t *d_off, int n_clips, int N, int H, int64_t *d_fo,
                                  hipStream_t s);
 // chunk size (frames) of MelT kernel variant v / of the plan's chosen variant / of the comparator

@@ -147,9 +147,10 @@ std::string tune_key(const Plan &p) {
     if (hipGetDeviceProperties(&prop, p.device) == hipSuccess) arch = prop.gcnArchName;
     std::ostringstream k;
     k << "prec=" << p.cfg.precision << ",n_fft=" << p.N << ",hop=" << p.H << ",n_mels=" << p.M << ",arch=" << arch;
-    // the variant list of these precisions starts with the split-plane kernel: an index stored
-    // for the list without it names another kernel
-    if (p.n_variants > 0 && split_planes(p) && std::strstr(forward_variant_name(p, 0), "split-planes")) k << ",list=2";
+    // a list that starts with a kernel of its second edition: an index stored for the first one
+    // names another kernel
+    const char *first = forward_variant_name(p, 0);
+    if (std::strstr(first, "split-planes") || std::strstr(first, "f8-frame-split")) k << ",list=2";
     return k.str();
 }
 
@@ -194,6 +195,7 @@ void apply_tune_cache(Plan &p) {
     if (cache_lookup(path, tune_key(p), v, g)) {
         if (v >= 0 && v < forward_variants(p)) {
             p.tune_variant = v;
+            p.tune_pinned = true;
         }
         if (g >= 0 && g <= 4) p.tune_grid = g;
     }
@@ -319,6 +321,7 @@ melt_status melt_set_variant(melt_plan plan, int32_t v, int32_t grid_per_cu) {
     if (v < 0 || v >= forward_variants(*p)) return set_error(MELT_E_INVALID_ARG, "variant out of range");
     if (grid_per_cu < 0 || grid_per_cu > 4) return set_error(MELT_E_INVALID_ARG, "grid_per_cu must be in [0, 4]");
     p->tune_variant = v;
+    p->tune_pinned = true;
     p->tune_grid = grid_per_cu;
     return MELT_OK;
 }
@@ -375,6 +378,7 @@ melt_status melt_autotune(melt_plan plan, int64_t total_frames, char *desc, int3
         }
     }
     p->tune_variant = best_v;
+    p->tune_pinned = true;
     p->tune_grid = best_g;
     p->prepared_frames[0] = -1;
     if (e0) (void)hipEventDestroy(e0);
