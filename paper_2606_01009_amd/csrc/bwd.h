@@ -1,6 +1,6 @@
 // What the backward's host side (melt_bwd.hip) and its split-plane products (bwd_split.hip) share.
 #pragma once
-#include "melt_internal.h"
+#include "pack.h"
 
 namespace melt {
 
@@ -21,7 +21,7 @@ static_assert(sizeof(RowChunk) == 40, "RowChunk layout");
 // dx on operand planes: whether the plan's geometry fits, its basis layout, the launch
 bool dx_split_fits(const Plan &p);
 size_t dx_split_pack_bytes(const Plan &p);
-melt_status dx_split_pack(const Plan &p, void *out, hipStream_t s);
+PackJob dx_split_job(const Plan &p, void *out);
 melt_status launch_dx_split(const Plan &p, const float *G, const RowChunk *rows, const int *n_rows, int64_t est_chunks,
                             int64_t n_frames, float *dx, hipStream_t s);
 // dW on operand planes: blocks of dW, and the partial sums of `splits` frame ranges

@@ -115,28 +115,6 @@ __device__ __forceinline__ void SplitDx::store(const SplitItem &it, int fbase, i
     }
 }
 
-// Fragments [tile][group][plane][lane][8]: row 16 t + lane % 16 = sample c of a hop, columns
-// segment s = group / GH (j = J - 1 - s) and interleaved q = 32 (group % GH) + 8 (lane / 16) + e.
-__global__ void k_pack_dx_split(const float *__restrict__ b32, int M, int N, int H, int J, int GH, int T16,
-                                unsigned short *__restrict__ out) {
-    const int NG = J * GH;
-    const int64_t total = (int64_t)T16 * NG * 512;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int e = i & 511, lane = e >> 3;
-        const int64_t tg = i >> 9;
-        const int gr = (int)(tg % NG), t = (int)(tg / NG);
-        const int s = gr / GH, j = J - 1 - s, q = 32 * (gr - s * GH) + 8 * (lane >> 4) + (e & 7);
-        const int c = 16 * t + (lane & 15), n = j * H + c;
-        float v = 0.0f;
-        if (q < 2 * M && c < H && n < N) v = b32[(size_t)((q & 1) * M + (q >> 1)) * N + n];
-        for (int p = 0; p < 3; ++p) {
-            const unsigned short b = f32_to_bf16_bits(v);
-            out[((size_t)tg * 3 + p) * 512 + e] = b;
-            v -= bf16_bits_to_f32(b);
-        }
-    }
-}
-
 // k-groups of G rows: J segments of 2M columns
 static Geometry dx_geometry(const Plan &p) { return make_geometry(2 * p.M * p.geo32.J, 2 * p.M, 32); }
 
@@ -151,10 +129,8 @@ bool dx_split_fits(const Plan &p) {
 
 size_t dx_split_pack_bytes(const Plan &p) { return (size_t)((p.H + 15) / 16) * dx_geometry(p).n_groups * 3 * 1024; }
 
-melt_status dx_split_pack(const Plan &p, void *out, hipStream_t s) {
-    const Geometry g = dx_geometry(p);
-    k_pack_dx_split<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, g.J, g.Hp / 32, (p.H + 15) / 16, (unsigned short *)out);
-    return hip_check(hipGetLastError(), "pack dx");
+PackJob dx_split_job(const Plan &p, void *out) {
+    return {PACK_DX_PLANES, out, nullptr, nullptr, dx_geometry(p).Hp / 32, (p.H + 15) / 16, 3};
 }
 
 melt_status launch_dx_split(const Plan &p, const float *G, const RowChunk *rows, const int *n_rows, int64_t est_chunks,

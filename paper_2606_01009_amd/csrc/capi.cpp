@@ -159,7 +159,7 @@ melt_status melt_plan_create(const melt_config *cfg, int device, melt_plan *out)
     }
     if (st == MELT_OK) init_variants(*p);
     if (st == MELT_OK) st = pack_tables_upload(*p);
-    if (st == MELT_OK) st = pack_basis(*p, nullptr);
+    if (st == MELT_OK) st = pack_basis(*p, p->d_basis32, nullptr);
     if (st == MELT_OK) st = hip_check(hipStreamSynchronize(nullptr), "pack basis");
     if (st == MELT_OK) st = stft_plan_build(*p);
     if (st == MELT_OK) st = ensure_chunks(*p, 0, 4096);
@@ -206,13 +206,8 @@ melt_status melt_plan_get_basis(melt_plan plan, float *h_basis) {
 melt_status melt_plan_set_basis(melt_plan plan, const float *d_basis, void *stream) {
     if (!plan || !d_basis) return set_error(MELT_E_INVALID_ARG, "NULL argument");
     Plan *p = reinterpret_cast<Plan *>(plan);
-    hipStream_t s = (hipStream_t)stream;
-    melt_status st = hip_check(hipSetDevice(p->device), "hipSetDevice");
-    if (st != MELT_OK) return st;
-    st = hip_check(hipMemcpyAsync(p->d_basis32, d_basis, sizeof(float) * 2 * p->M * p->N, hipMemcpyDeviceToDevice, s),
-                   "copy basis");
-    if (st != MELT_OK) return st;
-    return pack_basis(*p, s);
+    const melt_status st = hip_check(hipSetDevice(p->device), "hipSetDevice");
+    return st == MELT_OK ? pack_basis(*p, d_basis, (hipStream_t)stream) : st;
 }
 
 melt_status melt_frame_offsets(melt_plan plan, const int64_t *d_clip_offsets, int32_t n_clips,

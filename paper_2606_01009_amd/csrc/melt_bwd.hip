@@ -130,6 +130,43 @@ __global__ __launch_bounds__(256) void k_bwd_grad(const float *__restrict__ gout
     }
 }
 
+// Up to 64 clips: the start sample of every frame (-1 past the last one) and the row chunks, from
+// the clips in the lanes of each wave (schedule.h; a frame is a chunk of one).  One launch where
+// the chunk table, the fill, the frame starts and the row schedule were four.
+__global__ __launch_bounds__(256) void k_bwd_tables(const int64_t *__restrict__ off, int n_clips, int N, int H,
+                                                    int64_t n_frames, int64_t *__restrict__ fstart,
+                                                    RowChunk *__restrict__ rc, int64_t rc_cap, int *__restrict__ n_rc) {
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = gridDim.x * 4;
+    const ClipScan s = clip_scan(off, n_clips, N, H, 1);
+    const int64_t total = uniform64(s.total);
+    for (int64_t q0 = 64 * wave; q0 < n_frames; q0 += 64 * waves) {       // wave-uniform trip count
+        const int64_t q = q0 + lane;
+        const Chunk e = clip_chunk(s, H, 1, q);
+        if (q < n_frames) fstart[q] = q < total ? e.sample_start : -1;
+    }
+    if (!rc) return;
+    // rows covering the whole clip (samples in no frame get zero gradient)
+    const int64_t L = s.L > 0 ? s.L : 0, R = (L + H - 1) / H, K = (R + kRowsDx - 1) / kRowsDx;
+    const int64_t before = __shfl_up(s.pf, 1, 64), T = s.pf - (lane ? before : 0);
+    const int64_t pk = wave_scan(K, lane), nk = uniform64(__shfl(pk, 63, 64)), n = nk < rc_cap ? nk : rc_cap;
+    if (wave == 0 && lane == 0) *n_rc = (int)n;
+    for (int64_t q0 = 64 * wave; q0 < n; q0 += 64 * waves) {
+        const int64_t q = q0 + lane;
+        int t = 0;                                                       // clips whose chunks all precede q
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1)
+            if (__shfl(pk, t + d - 1, 64) <= q) t += d;
+        const int tp = t > 0 ? t - 1 : 0;
+        const int64_t pk_p = __shfl(pk, tp, 64), pf_p = __shfl(s.pf, tp, 64);
+        const int64_t st = __shfl(s.st, t & 63, 64), Lt = __shfl(L, t & 63, 64), Tt = __shfl(T, t & 63, 64);
+        const int64_t b0 = (q - (t > 0 ? pk_p : 0)) * kRowsDx, Rt = (Lt + H - 1) / H;
+        if (q < n)
+            rc[q] = RowChunk{st + b0 * H, st + Lt, (t > 0 ? pf_p : 0) + b0, (int32_t)((Rt - b0) < kRowsDx ? (Rt - b0) : kRowsDx),
+                             (int32_t)-b0, (int32_t)(Tt - b0), 0};
+    }
+}
+
 // one workgroup per forward chunk: the start sample of each of its frames
 __global__ __launch_bounds__(256) void k_bwd_fstart(const Chunk *__restrict__ chunks, const int *__restrict__ n_chunks,
                                                     int64_t n_frames, int H, int64_t *__restrict__ fstart) {
@@ -142,29 +179,6 @@ __global__ __launch_bounds__(256) void k_bwd_fstart(const Chunk *__restrict__ ch
 }
 
 // ------------------------------------------------------------------ dx: owner-computes overlap-add
-
-// Basis for dx, fragment order [ct][j][q-group of 8][lane][4]: B[k = q][col = c] =
-// W_q[jH + 32 ct + c] with q the interleaved row (2m cosine, 2m+1 sine) and lane half h
-// holding q = 8 qg + 4 h + i for MFMA step i.
-__global__ void k_pack_dx(const float *__restrict__ b32, int M, int N, int H, int J, int CT, float *__restrict__ out) {
-    const int QG = (2 * M + 7) / 8;
-    const int64_t total = (int64_t)CT * J * QG * 64 * 4;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int e = i & 3;
-        const int lane = (i >> 2) & 63;
-        int64_t r = i >> 8;
-        const int qg = (int)(r % QG);
-        r /= QG;
-        const int j = (int)(r % J);
-        const int ct = (int)(r / J);
-        const int q = qg * 8 + 4 * (lane >> 5) + e;
-        const int c = ct * 32 + (lane & 31);
-        const int n = j * H + c;
-        float v = 0.0f;
-        if (q < 2 * M && c < H && n < N) v = b32[(size_t)((q & 1) * M + (q >> 1)) * N + n];
-        out[i] = v;
-    }
-}
 
 // 4 waves x 32 hop-block rows; each wave computes its rows x all CT column tiles.  G rows
 // [b0 - J + 1, b0 + 128) of the clip are staged in LDS (zero outside the clip's frames).
@@ -295,26 +309,24 @@ melt_status grow(void **p, size_t *cap, size_t need) {
 }
 
 template <int CT>
-melt_status launch_dx(Plan &p, const float *G, float *dx, int S, size_t lds, int grid, hipStream_t s) {
+melt_status launch_dx(Plan &p, const float *G, int64_t n_frames, float *dx, int S, size_t lds, int grid, hipStream_t s) {
     (void)hipFuncSetAttribute((const void *)k_bwd_dx<CT>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     k_bwd_dx<CT><<<grid, 256, lds, s>>>((const RowChunk *)p.d_bwd_rows, p.d_nchunks + 1, G, (const f32x4 *)p.d_pack_dx,
-                                        p.M, p.H, p.geo32.J, S, p.prepared_frames[0], dx);
+                                        p.M, p.H, p.geo32.J, S, n_frames, dx);
     return hip_check(hipGetLastError(), "bwd dx launch");
 }
 
 }  // namespace
 
-melt_status pack_basis_dx(Plan &p, hipStream_t s) {
+melt_status pack_dx_job(Plan &p, PackJobs &jobs) {
     const int CT = (p.H + 31) / 32;
     if (CT > kMaxCT) return MELT_OK;     // dx unsupported for this hop; reported at call time
     const int J = p.geo32.J, QG = (2 * p.M + 7) / 8;
     const bool split = dx_split_fits(p);
     const size_t need = split ? dx_split_pack_bytes(p) : (size_t)CT * J * QG * 64 * 4 * sizeof(float);
-    melt_status st = grow(&p.d_pack_dx, &p.pack_dx_cap, need);
-    if (st != MELT_OK) return st;
-    if (split) return dx_split_pack(p, p.d_pack_dx, s);
-    k_pack_dx<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, J, CT, (float *)p.d_pack_dx);
-    return hip_check(hipGetLastError(), "pack dx");
+    const melt_status st = grow(&p.d_pack_dx, &p.pack_dx_cap, need);
+    if (st == MELT_OK) jobs.add(split ? dx_split_job(p, p.d_pack_dx) : PackJob{PACK_DX, p.d_pack_dx, nullptr, nullptr, J, CT, 0});
+    return st;
 }
 
 melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_off, int n_clips, int64_t n_frames,
@@ -356,24 +368,41 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
         if (st != MELT_OK) return st;
         d_gout = gl;
     }
-    // forward chunk table (table 0); projections recomputed when not supplied
-    st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p), n_frames, s);
-    if (st != MELT_OK) return st;
     const float *proj = d_proj;
     if (!proj) {
-        float *tmp_out = G;   // G's space holds the (unused) log output of the recomputation first
-        st = launch_melt_main(p, d_wave, tmp_out, proj_ws, s);
+        // recomputed; G's space holds the (unused) output of the recomputation first
+        st = launch_melt_forward(p, d_off, n_clips, n_frames, d_wave, G, proj_ws, s);
         if (st != MELT_OK) return st;
         proj = proj_ws;
     }
-    k_fill_i64<<<256, 256, 0, s>>>(fstart, n_frames, -1);
-    st = hip_check(hipGetLastError(), "bwd fill");
-    if (st != MELT_OK) return st;
-    const int64_t nchunk_est = n_frames / melt_chunk_frames(p) + n_clips + 1;
-    const int grid_prep = (int)std::min<int64_t>(nchunk_est, (int64_t)p.cu_count * 4);
-    k_bwd_fstart<<<grid_prep, 256, 0, s>>>(p.d_chunks[0], p.d_nchunks, n_frames, H, fstart);
-    st = hip_check(hipGetLastError(), "bwd frame starts");
-    if (st != MELT_OK) return st;
+    // frame starts and, for dx, row chunks: rows cover every sample of every clip (samples no
+    // frame covers get 0: their G rows are zero)
+    const int64_t rows_cap = n_frames / kRowsDx + 2 * (int64_t)n_clips + 2 + (int64_t)n_clips * (J + 1);
+    if (d_gwave) {
+        st = grow(&p.d_bwd_rows, &p.bwd_rows_cap, sizeof(RowChunk) * rows_cap);
+        if (st != MELT_OK) return st;
+    }
+    const int64_t rc_cap = (int64_t)(p.bwd_rows_cap / sizeof(RowChunk));
+    if (n_clips <= 64) {
+        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((n_frames + 255) / 256, p.cu_count));
+        k_bwd_tables<<<grid, 256, 0, s>>>(d_off, n_clips, N, H, n_frames, fstart,
+                                          d_gwave ? (RowChunk *)p.d_bwd_rows : nullptr, rc_cap, p.d_nchunks + 1);
+        st = hip_check(hipGetLastError(), "bwd tables");
+        if (st != MELT_OK) return st;
+        keep_prepared(p, 0, n_clips, n_frames);
+    } else {
+        st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p), n_frames, s);
+        if (st != MELT_OK) return st;
+        k_fill_i64<<<256, 256, 0, s>>>(fstart, n_frames, -1);
+        const int64_t nchunk_est = n_frames / melt_chunk_frames(p) + n_clips + 1;
+        const int grid_prep = (int)std::min<int64_t>(nchunk_est, (int64_t)p.cu_count * 4);
+        k_bwd_fstart<<<grid_prep, 256, 0, s>>>(p.d_chunks[0], p.d_nchunks, n_frames, H, fstart);
+        if (d_gwave)
+            k_schedule_rows<<<1, 1024, 0, s>>>(d_off, n_clips, N, H, (RowChunk *)p.d_bwd_rows, rc_cap, p.d_nchunks + 1);
+        st = hip_check(hipGetLastError(), "bwd tables");
+        if (st != MELT_OK) return st;
+    }
+    if (d_gwave) p.prepared_frames[1] = -1;      // table 1's count now describes row chunks
     {
         const int64_t n_elems = n_frames * M;
         const int vec = ((uintptr_t)proj % 16 == 0) && ((uintptr_t)d_gout % 8 == 0) && ((uintptr_t)G % 16 == 0);
@@ -383,16 +412,6 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
     st = hip_check(hipGetLastError(), "bwd gradient of the projections");
     if (st != MELT_OK) return st;
     if (d_gwave) {
-        // rows cover every sample of every clip (samples no frame covers get 0: their G
-        // rows are zero)
-        const int64_t rows_cap = n_frames / kRowsDx + 2 * (int64_t)n_clips + 2 + (int64_t)n_clips * (J + 1);
-        st = grow(&p.d_bwd_rows, &p.bwd_rows_cap, sizeof(RowChunk) * rows_cap);
-        if (st != MELT_OK) return st;
-        k_schedule_rows<<<1, 1024, 0, s>>>(d_off, n_clips, N, H, (RowChunk *)p.d_bwd_rows,
-                                           (int64_t)(p.bwd_rows_cap / sizeof(RowChunk)), p.d_nchunks + 1);
-        st = hip_check(hipGetLastError(), "bwd row schedule");
-        if (st != MELT_OK) return st;
-        p.prepared_frames[1] = -1;   // table 1's count now describes row chunks
         const int S = ((Q + 7) / 8) * 8 + 4;
         const size_t lds = (size_t)(kRowsDx + J - 1) * S * sizeof(float);
         if (lds > 160 * 1024) return set_error(MELT_E_UNSUPPORTED, "backward LDS too large (n_mels * hop)");
@@ -401,14 +420,14 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
         if (dx_split_fits(p))
             st = launch_dx_split(p, G, (const RowChunk *)p.d_bwd_rows, p.d_nchunks + 1, n_rc, n_frames, d_gwave, s);
         else switch (CT) {
-        case 1: st = launch_dx<1>(p, G, d_gwave, S, lds, grid, s); break;
-        case 2: st = launch_dx<2>(p, G, d_gwave, S, lds, grid, s); break;
-        case 3: st = launch_dx<3>(p, G, d_gwave, S, lds, grid, s); break;
-        case 4: st = launch_dx<4>(p, G, d_gwave, S, lds, grid, s); break;
-        case 5: st = launch_dx<5>(p, G, d_gwave, S, lds, grid, s); break;
-        case 6: st = launch_dx<6>(p, G, d_gwave, S, lds, grid, s); break;
-        case 7: st = launch_dx<7>(p, G, d_gwave, S, lds, grid, s); break;
-        default: st = launch_dx<8>(p, G, d_gwave, S, lds, grid, s); break;
+        case 1: st = launch_dx<1>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        case 2: st = launch_dx<2>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        case 3: st = launch_dx<3>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        case 4: st = launch_dx<4>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        case 5: st = launch_dx<5>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        case 6: st = launch_dx<6>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        case 7: st = launch_dx<7>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
+        default: st = launch_dx<8>(p, G, n_frames, d_gwave, S, lds, grid, s); break;
         }
         if (st != MELT_OK) return st;
     }

@@ -4,6 +4,7 @@
 #include <mutex>
 #include "fwd_common.h"
 #include "melt_split.h"
+#include "pack.h"
 
 namespace melt {
 
@@ -125,65 +126,92 @@ __global__ __launch_bounds__(1024) void k_frame_offsets(const int64_t *__restric
     if (tid == 0) fo[n_clips] = carry;
 }
 
-// FP32 pack: [rt][group][lane][4]
-__global__ void k_pack_f32(const float *__restrict__ b32, int M, int N, int H, const int *__restrict__ seg,
-                           const int *__restrict__ col, int NG, int RT, float *__restrict__ out) {
-    const int64_t total = (int64_t)RT * NG * 64 * 4;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int e = i & 3;
-        const int lane = (i >> 2) & 63;
-        const int64_t tg = i >> 8;
-        const int g = (int)(tg % NG), rt = (int)(tg / NG);
-        out[i] = packed_value(b32, M, N, H, rt, seg[g], col[g], 4, lane, e);
-    }
+// FP32: [rt][group][lane][4]
+__device__ __forceinline__ void pack_f32(const PackJob &j, const float *b32, int M, int N, int H, int64_t i) {
+    const int lane = (i >> 2) & 63;
+    const int64_t tg = i >> 8;
+    const int g = (int)(tg % j.NG), rt = (int)(tg / j.NG);
+    ((float *)j.out)[i] = packed_value(b32, M, N, H, rt, j.seg[g], j.col[g], 4, lane, i & 3);
 }
 
-// 16-bit pack: [rt][group][lane][8]; kind 0 = bf16, 1 = fp16, 2 = bf16 low part of the split,
-// 3 = fp16 low part of the split
-__global__ void k_pack_h16(const float *__restrict__ b32, int M, int N, int H, const int *__restrict__ seg,
-                           const int *__restrict__ col, int NG, int RT, int kind, unsigned short *__restrict__ out) {
-    const int64_t total = (int64_t)RT * NG * 64 * 8;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int e = i & 7;
-        const int lane = (i >> 3) & 63;
-        const int64_t tg = i >> 9;
-        const int g = (int)(tg % NG), rt = (int)(tg / NG);
-        const float v = packed_value(b32, M, N, H, rt, seg[g], col[g], 8, lane, e);
-        unsigned short r;
-        if (kind == 0) {
-            r = f32_to_bf16_bits(v);
-        } else if (kind == 1) {
-            r = f32_to_f16_bits(v);
-        } else if (kind == 3) {
-            const float hi = f16_bits_to_f32(f32_to_f16_bits(v));
-            r = f32_to_f16_bits(v - hi);
-        } else {
-            const float hi = bf16_bits_to_f32(f32_to_bf16_bits(v));
-            r = f32_to_bf16_bits(v - hi);
-        }
-        out[i] = r;
+// 16-bit: [rt][group][lane][8]
+__device__ __forceinline__ void pack_h16(const PackJob &j, const float *b32, int M, int N, int H, int64_t i) {
+    const int lane = (i >> 3) & 63;
+    const int64_t tg = i >> 9;
+    const int g = (int)(tg % j.NG), rt = (int)(tg / j.NG);
+    const float v = packed_value(b32, M, N, H, rt, j.seg[g], j.col[g], 8, lane, i & 7);
+    ((unsigned short *)j.out)[i] = j.form == 0   ? f32_to_bf16_bits(v)
+                                   : j.form == 1 ? f32_to_f16_bits(v)
+                                   : j.form == 2 ? f32_to_bf16_bits(v - bf16_bits_to_f32(f32_to_bf16_bits(v)))
+                                                 : f32_to_f16_bits(v - f16_bits_to_f32(f32_to_f16_bits(v)));
+}
+
+// P planes of a value, 512 elements apart
+__device__ __forceinline__ void put_planes(unsigned short *out, float v, int form) {
+    const int P = form & 7;
+    for (int p = 0; p < P; ++p) {
+        const unsigned short b = form & 8 ? f32_to_f16_bits(v) : f32_to_bf16_bits(v);
+        out[p * 512] = b;
+        v -= form & 8 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
     }
 }
 
 // Planes of the split-plane kernel: [tile][group of 32][plane][lane][8], lane = row lane % 16 of
 // the 16-row tile, columns 8 (lane / 16) ..; rows 4q .. 4q + 3 are (cos, sin) of two Mel bins.
-// kind 0: three bfloat16 planes, 1: two bfloat16 planes, 2: two binary16 planes.
-__global__ void k_pack_split(const float *__restrict__ b32, int M, int N, int H, const int *__restrict__ seg,
-                             const int *__restrict__ col, int NG, int T16, int kind, unsigned short *__restrict__ out) {
-    const int P = kind == 0 ? 3 : 2;
-    const int64_t total = (int64_t)T16 * NG * 512;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int e = i & 511, lane = e >> 3;
-        const int64_t tg = i >> 9;
-        const int g = (int)(tg % NG), t = (int)(tg / NG);
-        const int row = lane & 15, j = seg[g], c = col[g] + 8 * (lane >> 4) + (e & 7);
-        const int mel = split_tile_mel(t, row >> 2, T16) + ((row >> 1) & 1);
-        float v = 0.0f;
-        if (mel < M && c < min(H, N - j * H)) v = b32[(size_t)((row & 1) * M + mel) * N + j * H + c];
-        for (int p = 0; p < P; ++p) {
-            const unsigned short b = kind == 2 ? f32_to_f16_bits(v) : f32_to_bf16_bits(v);
-            out[((size_t)tg * P + p) * 512 + e] = b;
-            v -= kind == 2 ? f16_bits_to_f32(b) : bf16_bits_to_f32(b);
+__device__ __forceinline__ void pack_planes(const PackJob &j, const float *b32, int M, int N, int H, int64_t i) {
+    const int e = i & 511, lane = e >> 3;
+    const int64_t tg = i >> 9;
+    const int g = (int)(tg % j.NG), t = (int)(tg / j.NG);
+    const int row = lane & 15, sg = j.seg[g], c = j.col[g] + 8 * (lane >> 4) + (e & 7);
+    const int mel = split_tile_mel(t, row >> 2, j.tiles) + ((row >> 1) & 1);
+    float v = 0.0f;
+    if (mel < M && c < min(H, N - sg * H)) v = b32[(size_t)((row & 1) * M + mel) * N + sg * H + c];
+    put_planes((unsigned short *)j.out + (size_t)tg * (j.form & 7) * 512 + e, v, j.form);
+}
+
+// The backward's dx, FP32: fragments [ct][segment j][q-group of 8][lane][4], B[k = q][col = c] =
+// W_q[jH + 32 ct + c] with q the interleaved row (2m cosine, 2m+1 sine) and lane half h holding
+// q = 8 qg + 4 h + i for MFMA step i.  NG = segments.
+__device__ __forceinline__ void pack_dx(const PackJob &j, const float *b32, int M, int N, int H, int64_t i) {
+    const int QG = (2 * M + 7) / 8, lane = (i >> 2) & 63;
+    int64_t r = i >> 8;
+    const int qg = (int)(r % QG);
+    r /= QG;
+    const int sg = (int)(r % j.NG), ct = (int)(r / j.NG);
+    const int q = qg * 8 + 4 * (lane >> 5) + (int)(i & 3), c = ct * 32 + (lane & 31), n = sg * H + c;
+    ((float *)j.out)[i] = q < 2 * M && c < H && n < N ? b32[(size_t)((q & 1) * M + (q >> 1)) * N + n] : 0.0f;
+}
+
+// The backward's dx on planes: [tile][group][plane][lane][8], row 16 t + lane % 16 = sample c of a
+// hop, columns segment s = group / GH (j = J - 1 - s) and interleaved q = 32 (group % GH) +
+// 8 (lane / 16) + e.  NG = GH, the groups of one segment.
+__device__ __forceinline__ void pack_dx_planes(const PackJob &j, const float *b32, int M, int N, int H, int64_t i) {
+    const int J = (N + H - 1) / H, NG = J * j.NG, e = i & 511, lane = e >> 3;
+    const int64_t tg = i >> 9;
+    const int gr = (int)(tg % NG), t = (int)(tg / NG);
+    const int s = gr / j.NG, sg = J - 1 - s, q = 32 * (gr - s * j.NG) + 8 * (lane >> 4) + (e & 7);
+    const int c = 16 * t + (lane & 15), n = sg * H + c;
+    float v = 0.0f;
+    if (q < 2 * M && c < H && n < N) v = b32[(size_t)((q & 1) * M + (q >> 1)) * N + n];
+    put_planes((unsigned short *)j.out + (size_t)tg * (j.form & 7) * 512 + e, v, j.form);
+}
+
+__global__ __launch_bounds__(256) void k_pack(PackJobs jobs, const float *__restrict__ b32, int M, int N, int H) {
+    const PackJob &j = jobs.job[blockIdx.x % jobs.n];
+    const int64_t first = (blockIdx.x / jobs.n) * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)(gridDim.x / jobs.n) * blockDim.x;
+    const int64_t total = j.kind == PACK_COPY       ? (int64_t)2 * M * N
+                          : j.kind == PACK_F32      ? (int64_t)j.tiles * j.NG * 256
+                          : j.kind == PACK_DX       ? (int64_t)j.tiles * j.NG * ((2 * M + 7) / 8) * 256
+                          : j.kind == PACK_DX_PLANES ? (int64_t)j.tiles * j.NG * ((N + H - 1) / H) * 512
+                                                     : (int64_t)j.tiles * j.NG * 512;
+    for (int64_t i = first; i < total; i += step) {
+        switch (j.kind) {
+        case PACK_COPY: ((float *)j.out)[i] = b32[i]; break;
+        case PACK_F32: pack_f32(j, b32, M, N, H, i); break;
+        case PACK_H16: pack_h16(j, b32, M, N, H, i); break;
+        case PACK_PLANES: pack_planes(j, b32, M, N, H, i); break;
+        case PACK_DX: pack_dx(j, b32, M, N, H, i); break;
+        case PACK_DX_PLANES: pack_dx_planes(j, b32, M, N, H, i); break;
         }
     }
 }
@@ -255,40 +283,32 @@ melt_status pack_tables_upload(Plan &p) {
     return st;
 }
 
-// Re-packs the FP32 basis d_basis32 into the layout of the plan's precision (the only one
-// its kernels read) and the backward's dx layout, enqueued on `s`: no allocation and no
-// host synchronisation (the k-group tables were uploaded at plan creation).
-melt_status pack_basis(Plan &p, hipStream_t s) {
+// Packs the basis `src` (device, stacked [2M][N]) into the layouts of the plan's precision and the
+// backward's dx, and into d_basis32 unless that is where it is: enqueued on `s`, no allocation
+// after plan creation and no host synchronisation (the k-group tables were uploaded then).
+melt_status pack_basis(Plan &p, const float *src, hipStream_t s) {
     const int RT = p.row_tiles;
+    PackJobs jobs;
+    if (src != p.d_basis32) jobs.add({PACK_COPY, p.d_basis32, nullptr, nullptr, 0, 0, 0});
     if (split_planes(p))
-        k_pack_split<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, p.d_segS, p.d_colS, p.geoS.n_groups, (p.M + 7) / 8,
-                                         p.cfg.precision == MELT_PREC_FP32     ? 0
-                                         : p.cfg.precision == MELT_PREC_BF16X3 ? 1
-                                                                               : 2,
-                                         (unsigned short *)p.d_pack_split);
+        jobs.add({PACK_PLANES, p.d_pack_split, p.d_segS, p.d_colS, p.geoS.n_groups, (p.M + 7) / 8,
+                  split_planes(p) + (prec_f16(p) ? 8 : 0)});
     switch (p.cfg.precision) {
-    case MELT_PREC_FP32:
-        k_pack_f32<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, p.d_seg32, p.d_col32, p.geo32.n_groups, RT,
-                                       (float *)p.d_pack_f32);
-        break;
+    case MELT_PREC_FP32: jobs.add({PACK_F32, p.d_pack_f32, p.d_seg32, p.d_col32, p.geo32.n_groups, RT, 0}); break;
     case MELT_PREC_FP8_E4M3:
     case MELT_PREC_FP8_E4M3_BLOCK32:
-        k_pack_f8<<<RT, 256, 0, s>>>(p.d_basis32, p.M, p.N, (p.N + 63) / 64,
+        k_pack_f8<<<RT, 256, 0, s>>>(src, p.M, p.N, (p.N + 63) / 64,
                                      p.cfg.precision == MELT_PREC_FP8_E4M3_BLOCK32 ? 1 : 0, (unsigned *)p.d_pack_f8,
                                      p.d_rowscale);
         break;
-    default: {
-        const int kind_hi = prec_f16(p) ? 1 : 0;
-        k_pack_h16<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, p.d_seg16, p.d_col16, p.geo16.n_groups, RT, kind_hi,
-                                       (unsigned short *)p.d_pack_h16);
-        if (prec_split(p))
-            k_pack_h16<<<256, 256, 0, s>>>(p.d_basis32, p.M, p.N, p.H, p.d_seg16, p.d_col16, p.geo16.n_groups, RT,
-                                           kind_hi == 1 ? 3 : 2, (unsigned short *)p.d_pack_lo);
+    default:
+        jobs.add({PACK_H16, p.d_pack_h16, p.d_seg16, p.d_col16, p.geo16.n_groups, RT, prec_f16(p) ? 1 : 0});
+        if (prec_split(p)) jobs.add({PACK_H16, p.d_pack_lo, p.d_seg16, p.d_col16, p.geo16.n_groups, RT, prec_f16(p) ? 3 : 2});
     }
-    }
-    const melt_status st = hip_check(hipGetLastError(), "pack basis");
+    const melt_status st = pack_dx_job(p, jobs);
     if (st != MELT_OK) return st;
-    return pack_basis_dx(p, s);
+    if (jobs.n > 0) k_pack<<<256 * jobs.n, 256, 0, s>>>(jobs, src, p.M, p.N, p.H);
+    return hip_check(hipGetLastError(), "pack basis");
 }
 
 melt_status ensure_chunks(Plan &p, int which, int64_t needed) {
@@ -644,6 +664,13 @@ static int call_variant(const Plan &p, int n_clips, int64_t n_frames) {
     return v;
 }
 
+// After a call that built no table: a batch prepared earlier stays prepared if it is of the
+// call's size (as when the call is over that batch); any other is dropped, as a call that builds
+// its own table in the same place drops it.
+void keep_prepared(Plan &p, int which, int n_clips, int64_t n_frames) {
+    if (p.prepared_frames[which] != n_frames || p.prepared_clips[which] != n_clips) p.prepared_frames[which] = -1;
+}
+
 // The forward over a batch: without a chunk table where the kernel schedules itself (a batch
 // prepared earlier then stays prepared), through table 0 otherwise.
 melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
@@ -653,6 +680,7 @@ melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int6
         const melt_status st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p, v), n_frames, s, v);
         return st == MELT_OK ? launch_melt_main(p, d_wave, d_out, d_proj, s) : st;
     }
+    keep_prepared(p, 0, n_clips, n_frames);
     if (p.K == 0) return launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, d_out, d_proj, s);
     melt_status st = ensure_lmel(p, n_frames);
     if (st == MELT_OK) st = launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, p.d_lmel, d_proj, s);

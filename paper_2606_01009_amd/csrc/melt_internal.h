@@ -133,8 +133,7 @@ void mel_frequencies(const melt_config &cfg, std::vector<double> &f);
 
 // kernels (melt_fwd.hip, stft_mel.hip, melt_bwd.hip)
 melt_status pack_tables_upload(Plan &p);         // k-group tables of the pack kernels (plan creation)
-melt_status pack_basis(Plan &p, hipStream_t s);   // enqueue only: no allocation, no synchronisation
-melt_status pack_basis_dx(Plan &p, hipStream_t s);
+melt_status pack_basis(Plan &p, const float *src, hipStream_t s);   // enqueue only (plan creation allocates)
 melt_status ensure_chunks(Plan &p, int which, int64_t needed);
 // (variant: the MelT kernel variant that table 0 is for, -1 = the plan's)
 melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clips, int bf, int64_t n_frames,
@@ -155,6 +154,7 @@ melt_status launch_melt_table(Plan &p, int variant, const Chunk *tab, const int 
                               int64_t n_frames, const float *d_wave, float *d_out, float *d_proj, hipStream_t s);
 melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, float *d_proj, hipStream_t s);
+void keep_prepared(Plan &p, int which, int n_clips, int64_t n_frames);
 melt_status launch_stft_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, hipStream_t s);
 void init_variants(Plan &p);             // melt_fwd.hip: fills the plan's variant table

@@ -681,8 +681,10 @@ melt_status launch_stft_forward(Plan &p, const int64_t *d_off, int n_clips, int6
         const size_t lds = stft_lds_bytes(sh, p.M, p.fb_nnz), with = lds + 16 + kStftWaves * kStftList * sizeof(Chunk);
         const int64_t est = n_frames / bf + n_clips;
         if (stft_per_cu(with) == stft_per_cu(lds) && with <= 160 * 1024 &&
-            est <= (int64_t)kStftList * kStftWaves * stft_grid(p, lds, n_frames, bf, n_clips))
+            est <= (int64_t)kStftList * kStftWaves * stft_grid(p, lds, n_frames, bf, n_clips)) {
+            keep_prepared(p, 1, n_clips, n_frames);
             return launch_stft(p, ClipTable{d_off, n_clips, p.N, bf, (int)est}, n_frames, bf, n_clips, d_wave, d_out, s);
+        }
     }
     const melt_status st = launch_schedule(p, 1, d_off, n_clips, stft_chunk_frames(p), n_frames, s);
     return st == MELT_OK ? launch_stft_main(p, d_wave, d_out, s) : st;

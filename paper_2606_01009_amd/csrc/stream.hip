@@ -3,6 +3,7 @@
 // A stream holds the samples that no complete frame has used yet (fewer than n_fft).  A
 // push of chunk_len samples per stream (len = carry + chunk_len samples, k = floor((len -
 // N) / H) + 1 complete frames):
+//   (1. and 2. are one kernel, k_stream_gather, up to kGatherStreams streams)
 //   1. k_stream_pack (one workgroup): k per stream, the packed row offset of each stream
 //      (prefix sums of k + J - 1 over streams with k > 0, J = ceil(N / H)) and the chunk
 //      table of the packed clip
@@ -95,24 +96,86 @@ __global__ __launch_bounds__(1024) void k_stream_pack(const int *__restrict__ ca
 // per stream: the hop rows of its frames from [carry | chunk] into the packed buffer (past
 // the stream's end: zero, since those samples meet only zero basis weights or discarded
 // frames and must be finite), and the tail [k H, len) into its staging slot
+__device__ __forceinline__ void stream_copy(int s, int k, int64_t poff, const float *__restrict__ chunk, int chunk_len,
+                                            const float *__restrict__ carry, int len0, int N, int J, int H,
+                                            float *__restrict__ pack, float *__restrict__ tail) {
+    const int total = len0 + chunk_len;
+    const float *cs = carry + (size_t)s * N;
+    const float *xs = chunk + (size_t)s * chunk_len;
+    auto sample = [&](int i) { return i < len0 ? cs[i] : xs[i - len0]; };
+    if (k > 0) {
+        const int n = (k + J - 1) * H;
+        float *dst = pack + poff * H;
+        for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = i < total ? sample(i) : 0.0f;
+    }
+    const int from = k * H;
+    for (int i = threadIdx.x; i < total - from; i += blockDim.x) tail[(size_t)s * N + i] = sample(from + i);
+}
 __global__ __launch_bounds__(256) void k_stream_copy(const float *__restrict__ chunk, int chunk_len,
                                                      const float *__restrict__ carry, const int *__restrict__ carry_len,
                                                      const int *__restrict__ emitted, const int64_t *__restrict__ poff,
                                                      int N, int J, int H, float *__restrict__ pack,
                                                      float *__restrict__ tail) {
     const int s = blockIdx.x;
-    const int k = emitted[s];
-    const int len0 = carry_len[s], total = len0 + chunk_len;
-    const float *cs = carry + (size_t)s * N;
-    const float *xs = chunk + (size_t)s * chunk_len;
-    auto sample = [&](int i) { return i < len0 ? cs[i] : xs[i - len0]; };
-    if (k > 0) {
-        const int n = (k + J - 1) * H;
-        float *dst = pack + poff[s] * H;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = i < total ? sample(i) : 0.0f;
+    stream_copy(s, emitted[s], poff[s], chunk, chunk_len, carry, carry_len[s], N, J, H, pack, tail);
+}
+
+// k_stream_pack and k_stream_copy in one launch (a workgroup per stream): every workgroup sums
+// the packed rows of the streams before its own, and of all, from the carry lengths itself (two
+// loads a thread at 512 streams); the first one writes the chunk table.  A kernel of 3.8 us and
+// its gap less per push.  Each workgroup's sum is linear in the streams: up to kGatherStreams.
+constexpr int kGatherStreams = 2048;
+__global__ __launch_bounds__(256) void k_stream_gather(const int *__restrict__ carry_len, int chunk_len, int n_streams, int N,
+                                                       int J, int H, int bf, int *__restrict__ emitted,
+                                                       int64_t *__restrict__ poff, Chunk *__restrict__ tab, int max_tab,
+                                                       int *__restrict__ ntab, const float *__restrict__ chunk,
+                                                       const float *__restrict__ carry, float *__restrict__ pack,
+                                                       float *__restrict__ tail) {
+    __shared__ int64_t part[2][4];
+    const int s = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    auto frames = [&](int st) {
+        const int total = carry_len[st] + chunk_len;
+        return total >= N ? 1 + (total - N) / H : 0;
+    };
+    int64_t before = 0, all = 0;
+    for (int st = tid; st < n_streams; st += 256) {
+        const int k = frames(st);
+        const int64_t rows = k > 0 ? k + J - 1 : 0;
+        all += rows;
+        before += st < s ? rows : 0;
     }
-    const int from = k * H;
-    for (int i = threadIdx.x; i < total - from; i += blockDim.x) tail[(size_t)s * N + i] = sample(from + i);
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        before += __shfl_xor(before, d, 64);
+        all += __shfl_xor(all, d, 64);
+    }
+    if (lane == 0) {
+        part[0][tid >> 6] = before;
+        part[1][tid >> 6] = all;
+    }
+    __syncthreads();
+    before = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+    all = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+    const int k = frames(s);
+    if (tid == 0) {
+        emitted[s] = k;
+        poff[s] = before;
+    }
+    if (s == 0) {
+        const int64_t P = all >= J ? all - J + 1 : 0;      // frames of the packed clip
+        const int nt = (int)min<int64_t>((P + bf - 1) / bf, (int64_t)max_tab);
+        for (int j = tid; j < nt; j += 256) {
+            Chunk e;
+            e.sample_start = (int64_t)j * bf * H;
+            e.sample_end = all * H;
+            e.out_row = (int64_t)j * bf;
+            e.n_frames = (int)min<int64_t>(bf, P - (int64_t)j * bf);
+            e.clip = 0;
+            tab[j] = e;
+        }
+        if (tid == 0) *ntab = nt;
+    }
+    stream_copy(s, k, before, chunk, chunk_len, carry, carry_len[s], N, J, H, pack, tail);
 }
 
 // per stream: its k frames of the packed clip's outputs (width W) to its output slot, and
@@ -284,10 +347,16 @@ melt_status melt_stream_push(melt_stream_state S, const float *d_chunk, int32_t 
     melt_status st = hip_check(hipSetDevice(p.device), "hipSetDevice");
     if (st != MELT_OK) return st;
     const int J = (p.N + p.H - 1) / p.H;
-    k_stream_pack<<<1, 1024, 0, s>>>(S->d_carry_len, chunk_len, S->n_streams, p.N, J, p.H, S->bf, d_frames_emitted,
-                                     S->d_poff, S->d_tab, S->max_tab, S->d_ntab);
-    k_stream_copy<<<S->n_streams, 256, 0, s>>>(d_chunk, chunk_len, S->d_carry, S->d_carry_len, d_frames_emitted,
-                                               S->d_poff, p.N, J, p.H, S->d_pack, S->d_tail);
+    if (S->n_streams <= kGatherStreams) {
+        k_stream_gather<<<S->n_streams, 256, 0, s>>>(S->d_carry_len, chunk_len, S->n_streams, p.N, J, p.H, S->bf,
+                                                     d_frames_emitted, S->d_poff, S->d_tab, S->max_tab, S->d_ntab, d_chunk,
+                                                     S->d_carry, S->d_pack, S->d_tail);
+    } else {
+        k_stream_pack<<<1, 1024, 0, s>>>(S->d_carry_len, chunk_len, S->n_streams, p.N, J, p.H, S->bf, d_frames_emitted,
+                                         S->d_poff, S->d_tab, S->max_tab, S->d_ntab);
+        k_stream_copy<<<S->n_streams, 256, 0, s>>>(d_chunk, chunk_len, S->d_carry, S->d_carry_len, d_frames_emitted,
+                                                   S->d_poff, p.N, J, p.H, S->d_pack, S->d_tail);
+    }
     st = hip_check(hipGetLastError(), "stream pack");
     if (st != MELT_OK) return st;
     st = launch_melt_table(p, S->variant, S->d_tab, S->d_ntab, S->max_tab, S->max_pack, S->d_pack, S->d_tmp, nullptr, s);
