@@ -129,14 +129,25 @@ def _check(status, where):
         raise MeltError(status, where)
 
 
+_raw_stream = None
+
+
 def _stream_handle(stream=None):
+    """The hipStream_t of `stream`, or of the current stream of the current device.  Through torch's
+    raw-handle getter where it has one: building a Stream object takes 2.9 us, the handle 0.1 us,
+    of a call that takes 8 us on the GPU."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+            (lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 # ------------------------------------------------------------------ C-ABI mirrors
