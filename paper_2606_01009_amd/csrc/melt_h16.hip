@@ -669,11 +669,17 @@ __global__ __launch_bounds__(X3 ? 512 : 768) void k_melt_h16_pc(FwdArgs a, const
 // For frames whose basis tile is too long for one wave's registers (N = 1024: 64 k-groups;
 // N = 1200 at hop 160: 75): two waves share each row tile.  The first holds the k-groups of
 // the first hop segments (NS0 groups), the second the rest (NS1 <= NS0), whose columns are
-// the first half's, `delta` elements (whole hop rows) further down.  Per pair of frame tiles
-// the second wave hands its partial sums to the first through LDS, which adds them and
-// stores.  A workgroup owns a row group of at most 4 tiles (8 waves); spans are staged as in
-// k_melt_h16_as: the second-half waves, which store nothing, issue the span copies and wait
-// for them, and chunk descriptors come from the LDS ring.
+// the first half's, `delta` elements (whole hop rows) further down.  A workgroup owns a row
+// group of at most 4 tiles (8 waves) and takes chunks of one pair of frame tiles.  Each wave
+// of a pair finishes one of the two: it hands its partial sums of the other to its partner
+// through LDS, adds the partner's and stores.  Every wave then converts its share of the next
+// chunk, whose copy flew during the multiplies, so all eight do the same work at every point
+// and two barriers a chunk are enough.
+// What bounds it: the LDS reads of the frame fragments, one KB per 32-cycle MFMA and SIMD, and
+// the hand-over and conversion, during which the matrix cores are idle.  A finish by the first
+// half alone and a conversion between two barriers of its own took 130 us where this takes 124
+// (64 x 30 s, N = 1200, 128 Mel bins, BF16), and 90 where this takes 73 with one row tile
+// (N = 1024, 16 Mel bins): the fewer multiplies, the more the rest of a chunk counts.
 template <class Conv, int NS0, int NS1, bool IS_F16>
 __global__ __launch_bounds__(512) void k_melt_h16_ks(FwdArgs a, const uint4 *__restrict__ bhi, GroupTableBig gt,
                                                      int bf, int scr_off, int red_off, int rgroups, int delta) {
@@ -702,57 +708,49 @@ __global__ __launch_bounds__(512) void k_melt_h16_ks(FwdArgs a, const uint4 *__r
 #pragma unroll
     for (int s = 0; s < NS0; ++s)
         A[s] = (kh == 0 || s < NS1) ? bhi[((size_t)rt * G + kh * NS0 + s) * 64 + lane] : uint4{};
-    const int wu = __builtin_amdgcn_readfirstlane(wid);
-    const bool copier = wu >= gt_n;                // second-half waves: no output stores
-    if (c < nch) async_span(a, own ? ring_get(ring, 0) : read_chunk(a.chunks, c), scratch);
-    async_wait();
+    if (c < nch) {
+        const Chunk ch = own ? ring_get(ring, 0) : read_chunk(a.chunks, c);
+        async_span(a, ch, scratch);
+        async_wait();
+        __syncthreads();
+        convert_span<Conv>(a, ch, scratch, rows, 0);
+    }
     for (int it = 0; c < nch; c += cstep, ++it) {
         const int ri = it % kRing;
         if (ri == 0 && !own) ring_fill(ring, a.chunks, c, cstep, nch);
-        __syncthreads();                           // span of chunk c is in scratch; rows are free
+        __syncthreads();                           // rows of chunk c ready; scratch and red free
         const Chunk ch = ring_get(ring, ri);
         const Chunk chn = ring_get(ring, ri + 1);
-        convert_span<Conv>(a, ch, scratch, rows, 0);
-        __syncthreads();                           // rows ready; scratch is free
-        if (copier && c + cstep < nch) async_span_waves(a, chn, scratch, wu - gt_n, gt_n);
-        const int nft = (ch.n_frames + 31) >> 5;
-        for (int ft = 0; ft < nft; ft += 2) {      // the same trip count in every wave
-            const bool two = ft + 1 < nft;
-            f32x16 acc0 = f32x16{}, acc1 = f32x16{};
-            if (!idle) {
-                int off = (ft * 32 + (lane & 31)) * a.S + 8 * (lane >> 5) + kh * delta;
-                asm volatile("" : "+v"(off));
-                const unsigned short *l0 = rows + off;
-                const unsigned short *l1 = two ? l0 + 32 * a.S : l0;
-                if constexpr (NS0 == NS1) {
-                    mfma_sweep<NS0, false, IS_F16, D>(A, Al, l0, l1, gt, 0, acc0, acc1);
-                } else if (kh == 0) {
-                    mfma_sweep<NS0, false, IS_F16, D>(A, Al, l0, l1, gt, 0, acc0, acc1);
-                } else {
-                    mfma_sweep<NS1, false, IS_F16, D>(reinterpret_cast<const uint4(&)[NS1]>(A), Al, l0, l1, gt, 0,
-                                                      acc0, acc1);
-                }
-                if (kh == 1) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        red[r * 64 + lane] = acc0[r];
-                        red[1024 + r * 64 + lane] = acc1[r];
-                    }
-                }
+        const bool more = c + cstep < nch;
+        if (more) async_span(a, chn, scratch);
+        const bool two = ch.n_frames > 32;
+        f32x16 acc0 = f32x16{}, acc1 = f32x16{};
+        if (!idle) {
+            int off = (lane & 31) * a.S + 8 * (lane >> 5) + kh * delta;
+            asm volatile("" : "+v"(off));
+            const unsigned short *l0 = rows + off;
+            const unsigned short *l1 = two ? l0 + 32 * a.S : l0;
+            if constexpr (NS0 == NS1) {
+                mfma_sweep<NS0, false, IS_F16, D>(A, Al, l0, l1, gt, 0, acc0, acc1);
+            } else if (kh == 0) {
+                mfma_sweep<NS0, false, IS_F16, D>(A, Al, l0, l1, gt, 0, acc0, acc1);
+            } else {
+                mfma_sweep<NS1, false, IS_F16, D>(reinterpret_cast<const uint4(&)[NS1]>(A), Al, l0, l1, gt, 0, acc0,
+                                                  acc1);
             }
-            __syncthreads();                       // partial sums of the second halves in LDS
-            if (!idle && kh == 0) {
+            float *give = red + (kh ? 0 : 1024) + lane;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    acc0[r] += red[r * 64 + lane];
-                    acc1[r] += red[1024 + r * 64 + lane];
-                }
-                store_tile(a, ch, rt, ft * 32 + (lane & 31), lane, acc0);
-                if (two) store_tile(a, ch, rt, (ft + 1) * 32 + (lane & 31), lane, acc1);
-            }
-            __syncthreads();                       // the partial-sum area is free again
+            for (int r = 0; r < 16; ++r) give[r * 64] = kh ? acc0[r] : acc1[r];
         }
-        if (copier) async_wait();                  // the next chunk's copy has landed
+        async_wait();                              // this wave's copies of the next chunk have landed
+        __syncthreads();                           // partial sums in LDS; rows free
+        if (!idle) {
+            const float *take = red + (kh ? 1024 : 0) + lane;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc0[r] = (kh ? acc1[r] : acc0[r]) + take[r * 64];
+            store_tile(a, ch, rt, 32 * kh + (lane & 31), lane, acc0);
+        }
+        if (more) convert_span<Conv>(a, chn, scratch, rows, 0);
     }
 }
 
