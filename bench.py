@@ -4,12 +4,14 @@
 Workload: 64 clips x 30 s at 16 kHz (float32 pink noise + amplitude-modulated tones), N=400,
 H=160, 80 HTK Mel bins over 0-8 kHz: T = 191 872 frames, GEMM 191 872 x 400 x 160.  Inputs
 are resident in HBM before the timed region.  One step = one MelT forward over the batch
-(chunk schedule + the persistent MFMA kernel); the comparator (hand-written FFT + sparse
+(the persistent MFMA kernel, which finds its own chunks); the comparator (hand-written FFT + sparse
 filterbank) and the other precisions are timed the same way on the same batch and reported
 beside it, each with its log-Mel error against the FP64 oracle on sampled frames.
 
 Prints one JSON line.  `roofline` is for the dominant kernel (the MelT FP32 projection),
-timed alone with HIP events over the same number of launches; `cpu_baseline` times the FP64
+timed alone with HIP events over the same number of launches: each FP32 product is six
+bfloat16 products of the operands' exact planes, so the work is six times the method's FLOP at
+the bfloat16 rate.  `cpu_baseline` times the FP64
 oracle on the host over the whole batch.
 """
 from __future__ import annotations
@@ -27,10 +29,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK = {"f32": 157.3e12, "bf16": 2.5e15, "f16": 2.5e15, "fp8": 5.0e15, "hbm": 8.0e12}
-# the sources of the dominant kernel (the FP32 MelT projection): a change to either makes the
+# the sources of the dominant kernel (the FP32 MelT projection): a change to any makes the
 # committed traffic counters stale
-KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_01009_amd", "csrc", f) for f in ("melt_f32.hip", "fwd_common.h")]
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "melt_f32_ws_config2_m80_traffic.json")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_01009_amd", "csrc", f)
+               for f in ("melt_split.h", "melt_split_f32.hip", "fwd_common.h", "schedule.h")]
+# products on the matrix cores per product of the method: six of the nine of three bfloat16
+# planes for FP32, three of the four of two planes for the split precisions
+PRODUCTS = {"fp32": 6, "bf16x3": 3, "fp16x3": 3}
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "melt_split_f32_config2_m80_traffic.json")
 
 
 def log(msg):
@@ -330,7 +336,7 @@ def run_systems(torch, melt, workloads, path):
         flop = 8.0 * N * M * T          # dX = G W and dW = G^T X, 4 N M each per frame
         emit({"workload": f"backward 32 x 10 s, sr {sr:g}, N {N}, H {H}, M {M}, {prec} forward", "frames": T,
               "forward_ms": fwd, "backward_ms": bwd, "backward_tflops": flop / (bwd * 1e-3) / 1e12,
-              "backward_frac_fp32_mfma": flop / (bwd * 1e-3) / PEAK["f32"]})
+              "backward_frac_bf16_mfma": PRODUCTS["fp32"] * flop / (bwd * 1e-3) / PEAK["bf16"]})
     with open(path, "w") as fh:
         for r in rows:
             fh.write(json.dumps(r) + "\n")
@@ -357,14 +363,14 @@ def write_traffic(pmc_dir, T, bytes_algo, wave_bytes):
     Each counter is scaled by what it reads for the copy kernel, which reads and writes
     wave_bytes once per launch."""
     find = lambda sub: os.path.join(pmc_dir, sub, "run_counter_collection.csv")
-    fetch, nf = _pmc_average(find("fp32_f"), "k_melt_f32_ws", "FETCH_SIZE")
-    write, nw = _pmc_average(find("fp32_w"), "k_melt_f32_ws", "WRITE_SIZE")
+    fetch, nf = _pmc_average(find("fp32_f"), "k_melt_split", "FETCH_SIZE")
+    write, nw = _pmc_average(find("fp32_w"), "k_melt_split", "WRITE_SIZE")
     cf, _ = _pmc_average(find("copy_f"), "vectorized_elementwise_kernel", "FETCH_SIZE")
     cw, _ = _pmc_average(find("copy_w"), "vectorized_elementwise_kernel", "WRITE_SIZE")
     kib = wave_bytes / 1024.0
     fs, ws = kib / cf, kib / cw
     hbm = fetch * 1024 * fs + write * 1024 * ws
-    t = {"kernel": "k_melt_f32_ws (MelT FP32, 64 clips x 30 s, n_fft 400, hop 160, 80 Mel bins)",
+    t = {"kernel": "k_melt_split (MelT FP32, 64 clips x 30 s, n_fft 400, hop 160, 80 Mel bins)",
          "kernel_source_id": kernel_source_id(),
          "fetch_kib_per_dispatch": round(fetch, 1), "write_kib_per_dispatch": round(write, 1),
          "dispatches_averaged": [nf, nw], "fetch_scale": round(fs, 5), "write_scale": round(ws, 5),
@@ -522,13 +528,11 @@ def main():
             res["trials"] = trial_stats(torch, step, args.steps, args.trials)
             if meter is not None:
                 res["energy"] = energy_per_call(meter, torch, step, res["trials"]["median_ms"], idle[0], T)
-        # the bound of each precision: FP32 and the split 16-bit products (three products per
-        # term) are MFMA-bound, the others HBM-bound (the waveform read once and the output
-        # written once)
-        if prec in ("fp32", "bf16x3", "fp16x3"):
-            work = T * flop_per_frame * (1 if prec == "fp32" else 3)
-            peak = PEAK["f32"] if prec == "fp32" else PEAK["bf16"]
-            res["roofline"] = {"bound": "mfma", "frac": work / (kern_ms * 1e-3) / peak}
+        # the bound of each precision: FP32 and the split precisions are MFMA-bound, the others
+        # HBM-bound (the waveform read once and the output written once)
+        if prec in PRODUCTS:
+            work = T * flop_per_frame * PRODUCTS[prec]
+            res["roofline"] = {"bound": "mfma", "frac": work / (kern_ms * 1e-3) / PEAK["bf16"]}
         else:
             res["roofline"] = {"bound": "hbm", "frac": bytes_per_launch / (kern_ms * 1e-3) / PEAK["hbm"]}
         if not args.no_check:
@@ -597,11 +601,12 @@ def main():
 
     source_id = kernel_source_id()
     traffic = load_traffic(TRAFFIC_FILE, source_id)
-    achieved = T * flop_per_frame / (fp32["kernel_ms"] * 1e-3) / 1e12
-    roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK["f32"] / 1e12, "unit": "TFLOP/s",
-                "frac": achieved / (PEAK["f32"] / 1e12), "traffic": traffic,
+    work = T * flop_per_frame * PRODUCTS["fp32"]
+    achieved = work / (fp32["kernel_ms"] * 1e-3) / 1e12
+    roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK["bf16"] / 1e12, "unit": "TFLOP/s",
+                "frac": achieved / (PEAK["bf16"] / 1e12), "traffic": traffic,
                 "kernel": f"{melt.melt_variant_name(plan32.handle, plan32_variant)} (MelT FP32 projection + energy + log)",
-                "flop_per_launch": T * flop_per_frame, "kernel_ms": fp32["kernel_ms"],
+                "flop_per_launch": work, "method_flop_per_launch": T * flop_per_frame, "kernel_ms": fp32["kernel_ms"],
                 "kernel_source_id": source_id}
 
     line = {
@@ -618,7 +623,7 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": "64 clips x 30 s at 16 kHz (pink noise + AM tones), n_fft=400, hop=160, "
-                               f"n_mels={M} HTK 0-8 kHz, T={T} frames; MelT FP32 (v_mfma_f32_32x32x2f32)",
+                               f"n_mels={M} HTK 0-8 kHz, T={T} frames; MelT FP32 (three exact bfloat16 planes, v_mfma_f32_16x16x32_bf16)",
                    "frames": T, "n_fft": 400, "hop": 160, "n_mels": M, "clips": 64, "seconds_per_clip": 30},
         "error_vs_fp64_oracle": fp32.get("error_vs_fp64_oracle"),
         "comparator_fft_filterbank": comparator,

@@ -199,13 +199,14 @@ melt_status melt_forward(melt_plan plan, const float *d_wave, const int64_t *d_c
                          int32_t n_clips, int64_t n_frames, float *d_out, void *stream);
 
 /* As melt_forward, for callers that cannot allocate device memory (code under hipGraph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the chunk count and chunk
- * table live in a fixed 1 MiB device array of the library (one per GPU, held until the
- * process ends) instead of the plan's growable workspace, and the call makes no hipMalloc,
- * hipFree or other allocating call.  The scratch holds at most 32 760 chunk-table entries:
+ * capture, tight serving loops, harnesses that forbid hipMalloc): where the kernel does not
+ * find its own chunks, the chunk count and chunk table live in a fixed 1 MiB device array
+ * of the library (one per GPU, held until the process ends) instead of the plan's growable
+ * workspace, and the call makes no hipMalloc, hipFree or other allocating call.  The scratch holds at most 32 760 chunk-table entries:
  * the call needs n_frames / F + n_clips + 1 of them, F being the frames per chunk of the
- * plan's kernel variant (the "-bfF" suffix of melt_variant_name; 128 for the default FP32,
- * BF16 and FP16 kernels), so e.g. up to about 4 million frames in few clips.  Every call on
+ * plan's kernel variant (the "-bfF" suffix of melt_variant_name; 128 for the default FP32
+ * kernel, 96 for the BF16 and FP16 ones at n_fft 400), so e.g. up to about 4 million FP32
+ * frames in few clips.  Every call on
  * one GPU shares that GPU's scratch (from every plan): calls that overlap in time on one
  * GPU (on different streams, or from several host threads) race and must be serialised by
  * the caller.  Prepared batches of the plan are left untouched.  Arguments as in
@@ -278,9 +279,9 @@ melt_status melt_backward(melt_plan plan, const float *d_wave, const int64_t *d_
  *                        MELT_OUT_MFCC) rows [s * max_frames, + k) and k to
  *                        d_frames_emitted[s] (device int32 [n_streams]); under
  *                        MELT_OUT_MFCC the rows past k are written too, with no meaning.
- * A push is three kernel launches (four under MELT_OUT_MFCC: assemble, project, cepstrum,
- * keep the tail) with no host
- * synchronisation and no allocation: it can be captured in a hipGraph and replayed with
+ * A push is three kernel launches (assemble, project, keep the tail; four beyond 2048
+ * streams, and one more, the cepstrum, under MELT_OUT_MFCC) with no host synchronisation
+ * and no allocation: it can be captured in a hipGraph and replayed with
  * new chunk contents (one graph per chunk length).  Pushes on one state must be ordered
  * (one stream). */
 melt_status melt_stream_create(melt_plan plan, int32_t n_streams, int32_t max_chunk_len,
