@@ -155,113 +155,214 @@ melt_status launch_dx_split(const Plan &p, const float *G, const RowChunk *rows,
 // ------------------------------------------------------------------ dW
 
 // dW = G^T X.  A workgroup of 8 waves owns a 128 (q) x 256 (n) block over the frames of its
-// split; a wave a 64 x 64 quarter-by-half of it (4 x 4 tiles of 16 x 16).  A step is 32 frames:
-// each thread loads 8 consecutive frames of one q and of two n (coalesced over q and n), splits
-// them and writes each plane's 8 values as one 16-byte piece of an MFMA fragment, so the
-// transposition costs nothing and neither write nor read conflicts.  Two LDS buffers, one
-// barrier per step: step s + 1 is in flight to registers while step s multiplies.
-// What bounds it: the matrix cores (96 MFMAs of 16 cycles per wave and step, two waves per SIMD),
-// with the split's VALU work (144 instructions per wave and step) issued between them.
+// split, 32 frames a step.  Four waves, one per SIMD, multiply: 64 q x 128 n each (4 x 8 tiles
+// of 16 x 16).  Four stage, each eight consecutive frames of the step: a lane loads two columns
+// of G and four of X of every frame (8- and 16-byte loads), splits them and writes each plane's
+// 8 values of a column as one 16-byte piece of an MFMA fragment, so the transposition costs
+// nothing; 16 bytes between tiles keep the writes off one another's banks.  Two LDS buffers, one
+// barrier per step; two steps of samples are in registers, landed and in flight.
+// What bounds it: the matrix cores (192 MFMAs of 16 cycles per multiply wave and step).  With
+// every wave staging its share behind its multiplies (24 4-byte loads each, the VALU work of
+// the split after the last MFMA) a step took 7300 cycles for those 3072; the whole backward of
+// 27 456 frames, N = 1024, M = 128, was 182 us where it is 164.
+typedef float dw_f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kDwQ = 128, kDwN = 256, kDwT = 32;
-constexpr int kDwBuf = (kDwQ + kDwN) / 16 * 3 * 1024;      // bytes of one step's fragments
+constexpr int kDwTile = 3 * 1024 + 16;                     // bytes from one tile's planes to the next's
+constexpr int kDwBuf = (kDwQ + kDwN) / 16 * kDwTile;       // bytes of one step's fragments
+// How a lane loads its four columns of X: DW_QUADS where N is a multiple of 4, so that they exist
+// together or not at all; DW_TAIL otherwise, the last lane with a column loading the frame's last
+// four and moving its own to the front; DW_SINGLE, one by one, in frames of fewer than four samples.
+enum DwLoad { DW_QUADS, DW_TAIL, DW_SINGLE };
+template <DwLoad LX>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
 void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fstart, const float *__restrict__ wave,
                     int64_t T, int M, int N, int splits, float *part) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int Q = 2 * M, NB = (N + kDwN - 1) / kDwN, blocks = (Q + kDwQ - 1) / kDwQ * NB;
-    const int split = blockIdx.x / blocks, bb = blockIdx.x - split * blocks;
+    // Workgroups go round the eight XCDs: where the splits are a multiple of 8, the blocks of one
+    // are put eight apart, so that its samples and gradients are read into one L2.
+    const bool even = splits % 8 == 0;
+    const int split = even ? blockIdx.x / (8 * blocks) * 8 + blockIdx.x % 8 : blockIdx.x / blocks;
+    const int bb = even ? blockIdx.x / 8 % blocks : blockIdx.x - split * blocks;
     const int q0 = bb / NB * kDwQ, n0 = bb % NB * kDwN;
     const int64_t per = ((T + splits - 1) / splits + kDwT - 1) / kDwT * kDwT;
     const int64_t t0 = (int64_t)split * per, t1 = t0 + per < T ? t0 + per : T;
-    // staging: unit 0 is column sq of G, frames 8 tg .. 8 tg + 7 (tg = wid / 2); units 1 and 2 are
-    // columns sn and sn + 128 of X, the same frames
-    const int tg = wid >> 1, sc = tid & 127;
-    const int qc = q0 + sc < Q ? q0 + sc : 0, na = n0 + sc < N ? n0 + sc : 0, nb = n0 + 128 + sc < N ? n0 + 128 + sc : 0;
-    const bool vq = q0 + sc < Q, va = n0 + sc < N, vb = n0 + 128 + sc < N;
-    float rg[8], ra[8], rb[8];
-    unsigned ok = 0;                                   // frames of the step that exist (wave-uniform)
-    // Unconditional loads, all in flight together; what does not exist is cleared when it is
-    // staged.  A row without a frame has no samples: it reads N floats of the partial sums instead.
-    auto load = [&](int64_t tb) {
-        int64_t st[8];
+    if (wid >= 4) {
+        if (t0 >= t1) return;
+        const int tg = wid - 4;
+        const int q = q0 + 2 * lane, n = n0 + 4 * lane;
+        // byte offsets of the lane's columns; where there is none, of column 0
+        const bool tail = LX == DW_TAIL && n < N && n + 4 > N;
+        const unsigned qo = q < Q ? 4 * q : 0, no = tail ? 4 * (N - 4) : n < N ? 4 * n : 0;
+        struct Raw {
+            float2 g[8];
+            f32x4 x[8];
+            unsigned ok;                               // frames of the step that exist (wave-uniform)
+        };
+        int64_t st[8], s0[8], s1[8];                   // first samples of a load's frames, read ahead; -1: a row without one
+        auto starts = [&](int64_t tb, int64_t (&st)[8]) {
+            const int64_t t = tb + 8 * tg;
+            if (t + 8 <= t1) {
+                typedef long long cs64x8 __attribute__((ext_vector_type(8), aligned(8)));
+                typedef const __attribute__((address_space(4))) cs64x8 *cptr;
+                const cs64x8 v = *(cptr)(fstart + t);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t t = tb + 8 * tg + e;
-            st[e] = split_scalar(fstart, t < t1 ? t : t1 - 1);      // -1: a row without a frame
+                for (int e = 0; e < 8; ++e) st[e] = v[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) st[e] = split_scalar(fstart, t + e < t1 ? t + e : t1 - 1);
+            }
+        };
+        // Unconditional loads, all in flight together; frames past the split read its last one, and
+        // what does not exist is cleared when it is staged.  A row without a frame has no samples:
+        // it reads N floats of the partial sums instead.
+        auto load = [&](int64_t tb, Raw &r, const int64_t (&st)[8]) {
+            const int64_t t = tb + 8 * tg;
+            const char *g[8], *x[8];
+            int64_t any = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) any |= st[e];
+            if (t + 8 <= t1 && any >= 0) {
+                r.ok = 255;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    g[e] = (const char *)(G + (t + e) * Q);
+                    x[e] = (const char *)(wave + st[e]);
+                }
+            } else {
+                r.ok = 0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    r.ok |= (t + e < t1 && st[e] >= 0 ? 1u : 0u) << e;
+                    g[e] = (const char *)(G + (t + e < t1 ? t + e : t1 - 1) * Q);
+                    x[e] = (const char *)(st[e] >= 0 ? wave + st[e] : part);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                r.g[e] = *(const float2 *)(g[e] + qo);
+                if constexpr (LX == DW_SINGLE) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) r.x[e][c] = *(const float *)(x[e] + (n + c < N ? 4 * (n + c) : 0));
+                } else {
+                    r.x[e] = *(const dw_f32x4 *)(x[e] + no);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto put = [&](const float (&v)[8], unsigned char *d) {
+            unsigned w0[6], w1[6];
+            Split3BF16::split(f32x4{v[0], v[1], v[2], v[3]}, w0);
+            Split3BF16::split(f32x4{v[4], v[5], v[6], v[7]}, w1);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) *(split_u32x4 *)(d + p * 1024) = split_u32x4{w0[2 * p], w0[2 * p + 1], w1[2 * p], w1[2 * p + 1]};
+        };
+        // (columns past Q or N hold column 0's values: their sums are not stored)
+        auto stage = [&](Raw &r, unsigned char *buf) {
+            unsigned char *dg = buf + (lane >> 3) * kDwTile + (16 * tg + (2 * lane & 15)) * 16;
+            unsigned char *dx = buf + (8 + (lane >> 2)) * kDwTile + (16 * tg + (4 * lane & 15)) * 16;
+            if (r.ok != 255) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (!(r.ok >> e & 1)) {
+                        r.g[e] = float2{0.0f, 0.0f};
+                        r.x[e] = f32x4{};
+                    }
+            }
+            if constexpr (LX == DW_TAIL) {
+                const int have = N & 3;                // columns of the lane that has some, not all
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const f32x4 y = r.x[e];
+                    r.x[e][0] = tail ? have == 3 ? y[1] : have == 2 ? y[2] : y[3] : y[0];
+                    r.x[e][1] = tail ? have == 3 ? y[2] : y[3] : y[1];
+                    r.x[e][2] = tail ? y[3] : y[2];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = c ? r.g[e].y : r.g[e].x;
+                put(v, dg + 16 * c);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = r.x[e][c];
+                put(v, dx + 16 * c);
+            }
+        };
+        // One step: `r` holds step s and then takes step s + 2, while s + 1 flies in the other set.
+        // Steps past the split are loaded (its last frame) and staged (as zeros) too, in pairs
+        // without a branch: every wait is then for a known number of younger loads, and no
+        // register set is copied.
+        auto step = [&](int64_t tb, Raw &r, unsigned char *buf) {
+            stage(r, buf);
+            load(tb + 2 * kDwT, r, st);
+            starts(tb + 3 * kDwT, st);
+            __syncthreads();                           // step s is staged, step s - 1 multiplied
+        };
+        Raw r0, r1;
+        starts(t0, s0);
+        starts(t0 + kDwT, s1);
+        starts(t0 + 2 * kDwT, st);
+        load(t0, r0, s0);
+        load(t0 + kDwT, r1, s1);
+        for (int64_t tb = t0; tb < t1; tb += 2 * kDwT) {
+            step(tb, r0, lds);
+            step(tb + kDwT, r1, lds + kDwBuf);
         }
-        ok = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t t = tb + 8 * tg + e;
-            ok |= (t < t1 && st[e] >= 0 ? 1u : 0u) << e;
-            const float *x = st[e] >= 0 ? wave + st[e] : part;
-            rg[e] = G[(t < t1 ? t : t1 - 1) * Q + qc];
-            ra[e] = x[na];
-            rb[e] = x[nb];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto put = [&](const float (&r)[8], bool exists, int tile, unsigned char *buf) {
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = exists && (ok >> e & 1) ? r[e] : 0.0f;
-        unsigned w0[6], w1[6];
-        Split3BF16::split(f32x4{v[0], v[1], v[2], v[3]}, w0);
-        Split3BF16::split(f32x4{v[4], v[5], v[6], v[7]}, w1);
-        unsigned char *d = buf + tile * 3072 + (16 * tg + (sc & 15)) * 16;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) *(split_u32x4 *)(d + p * 1024) = split_u32x4{w0[2 * p], w0[2 * p + 1], w1[2 * p], w1[2 * p + 1]};
-    };
-    auto stage = [&](unsigned char *buf) {
-        put(rg, vq, sc >> 4, buf);
-        put(ra, va, 8 + (sc >> 4), buf);
-        put(rb, vb, 16 + (sc >> 4), buf);
-    };
-    const int wq = wid & 1, wn = wid >> 1;             // the wave's 64-wide quarters
-    f32x4 acc[4][4];
+        return;
+    }
+    const int wq = wid & 1, wn = wid >> 1;             // the wave's quarter of the block
+    f32x4 acc[4][8];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{};
-    if (t0 < t1) {
-        load(t0);
-        stage(lds);
-    }
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{};
     int cur = 0;
     for (int64_t tb = t0; tb < t1; tb += kDwT, cur ^= 1) {
-        __syncthreads();                               // this step's fragments are written, the other buffer is free
-        const bool more = tb + kDwT < t1;
-        if (more) load(tb + kDwT);
+        __syncthreads();                               // this step is staged
         const unsigned char *fr = lds + cur * kDwBuf + lane * 16;
-        split_u32x4 A[4][3], B[3];
+        split_u32x4 A[4][3], B[2][3];
+        // a step's six products are summed on their own and added once, behind the next tile's first
+        // MFMAs: a sixth of the roundings at the magnitude of a sum over all the frames
+        f32x4 sum[2][4];
+        auto load_b = [&](int j) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+            for (int p = 0; p < 3; ++p) B[j & 1][p] = *(const split_u32x4 *)(fr + (8 + 8 * wn + j) * kDwTile + p * 1024);
+        };
+        load_b(0);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) A[i][p] = *(const split_u32x4 *)(fr + (4 * wq + i) * 3072 + p * 1024);
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+            for (int i = 0; i < 4; ++i) A[i][p] = *(const split_u32x4 *)(fr + (4 * wq + i) * kDwTile + p * 1024);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) B[p] = *(const split_u32x4 *)(fr + (8 + 4 * wn + j) * 3072 + p * 1024);
-            // a step's six products are summed on their own and added once: a sixth of the roundings at
-            // the magnitude of a sum over all the frames
-            f32x4 sum[4];
+        for (int j = 0; j < 8; ++j) {
+            if (j < 7) load_b(j + 1);
 #pragma unroll
-            for (int k = 0; k < 6; ++k)
+            for (int k = 0; k < 6; ++k) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    sum[i] = Split3BF16::mma(A[i][Split3BF16::pa[k]], B[Split3BF16::pb[k]], k ? sum[i] : f32x4{});
+                    sum[j & 1][i] = Split3BF16::mma(A[i][Split3BF16::pa[k]], B[j & 1][Split3BF16::pb[k]], k ? sum[j & 1][i] : f32x4{});
+                if (k == 0 && j > 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i][j] += sum[i];
+                    for (int i = 0; i < 4; ++i) acc[i][j - 1] += sum[(j - 1) & 1][i];
+                }
+            }
         }
-        if (more) stage(lds + (cur ^ 1) * kDwBuf);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][7] += sum[1][i];
     }
     // lane holds column n, rows q = tile base + 4 (lane / 16) + r (interleaved q)
     float *o = part + (size_t)split * Q * N;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int n = n0 + 64 * wn + 16 * j + (lane & 15);
+    for (int j = 0; j < 8; ++j) {
+        const int n = n0 + 128 * wn + 16 * j + (lane & 15);
         if (n >= N) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -271,14 +372,16 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
                 if (q < Q) o[(size_t)q * N + n] = acc[i][j][r];
             }
     }
+    if (cur) __syncthreads();                          // the staging waves take steps in pairs
 }
 
 int dw_split_blocks(const Plan &p) { return (2 * p.M + kDwQ - 1) / kDwQ * ((p.N + kDwN - 1) / kDwN); }
 
 melt_status launch_dw_split(const Plan &p, const float *G, const int64_t *fstart, const float *wave, int64_t n_frames,
                             int splits, float *part, hipStream_t s) {
-    allow_lds(k_bwd_dw_split);
-    k_bwd_dw_split<<<dw_split_blocks(p) * splits, 512, 2 * kDwBuf, s>>>(G, fstart, wave, n_frames, p.M, p.N, splits, part);
+    const auto kernel = p.N % 4 == 0 ? k_bwd_dw_split<DW_QUADS> : p.N > 4 ? k_bwd_dw_split<DW_TAIL> : k_bwd_dw_split<DW_SINGLE>;
+    allow_lds(kernel);
+    kernel<<<dw_split_blocks(p) * splits, 512, 2 * kDwBuf, s>>>(G, fstart, wave, n_frames, p.M, p.N, splits, part);
     return hip_check(hipGetLastError(), "bwd dW");
 }
 
