@@ -149,13 +149,16 @@ __device__ __forceinline__ Chunk ring_get(const ChunkRing &r, int i) {
 // of the chunk loop and its registers) or the list of kListEntries of the kernels that keep one.
 // For the whole workgroup, with a barrier.
 __device__ __forceinline__ int ring_start(const FwdArgs &a, ChunkRing &r, int c0, int cstep) {
-    const int n = chunk_list(a.clips, a.H, c0 + (int64_t)(threadIdx.x & 63) * cstep, kRing + 2, r.e, threadIdx.x < 64);
+    const int64_t c = c0 + (int64_t)(threadIdx.x & 63) * cstep;
+    const int n = chunk_list(a.clips, a.H, c, kRing + 2, r.e, threadIdx.x < 64);
     __syncthreads();
+    if (threadIdx.x < 64) leave_chunks(a.clips, c, kRing + 2, r.e, n);
     return n;
 }
 __device__ __forceinline__ int list_start(const FwdArgs &a, Chunk *list, int64_t c_lane) {
     const int n = chunk_list(a.clips, a.H, c_lane, kListEntries, list, threadIdx.x < 64);
     __syncthreads();
+    if (threadIdx.x < 64) leave_chunks(a.clips, c_lane, kListEntries, list, n);
     return n;
 }
 constexpr int kListBytes = kListEntries * (int)sizeof(Chunk);

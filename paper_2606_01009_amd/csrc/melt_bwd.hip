@@ -130,12 +130,14 @@ __global__ __launch_bounds__(256) void k_bwd_grad(const float *__restrict__ gout
     }
 }
 
-// Up to 64 clips: the start sample of every frame (-1 past the last one) and the row chunks, from
-// the clips in the lanes of each wave (schedule.h; a frame is a chunk of one).  One launch where
-// the chunk table, the fill, the frame starts and the row schedule were four.
-__global__ __launch_bounds__(256) void k_bwd_tables(const int64_t *__restrict__ off, int n_clips, int N, int H,
-                                                    int64_t n_frames, int64_t *__restrict__ fstart,
+// Up to 64 clips: the start sample of every frame (-1 past the last one), the forward's chunk table
+// (of which the backward itself reads nothing: its batch is the plan's prepared one afterwards) and
+// the row chunks, from the clips in the lanes of each wave (schedule.h; a frame is a chunk of one).
+// One launch where the chunk table, the fill, the frame starts and the row schedule were four.
+__global__ __launch_bounds__(256) void k_bwd_tables(ClipTable b, int H, int64_t n_frames, int64_t *__restrict__ fstart,
                                                     RowChunk *__restrict__ rc, int64_t rc_cap, int *__restrict__ n_rc) {
+    const int64_t *__restrict__ off = b.off;
+    const int n_clips = b.n_clips, N = b.N;
     const int lane = threadIdx.x & 63;
     const int64_t wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = gridDim.x * 4;
     const ClipScan s = clip_scan(off, n_clips, N, H, 1);
@@ -144,6 +146,17 @@ __global__ __launch_bounds__(256) void k_bwd_tables(const int64_t *__restrict__ 
         const int64_t q = q0 + lane;
         const Chunk e = clip_chunk(s, H, 1, q);
         if (q < n_frames) fstart[q] = q < total ? e.sample_start : -1;
+    }
+    // the chunk table on the last waves, the row chunks on the first
+    const int64_t back = waves - 1 - wave;
+    if (b.tab && 64 * back < b.cap) {
+        const ClipScan sc = clip_scan(off, n_clips, N, H, b.bf);
+        const int64_t n = uniform64(sc.total < b.cap ? sc.total : b.cap);
+        for (int64_t q0 = 64 * back; q0 < n; q0 += 64 * waves) {
+            const Chunk e = clip_chunk(sc, H, b.bf, q0 + lane);
+            if (q0 + lane < n) b.tab[q0 + lane] = e;
+        }
+        if (back == 0 && lane == 0) *b.n_tab = (int)n;
     }
     if (!rc) return;
     // rows covering the whole clip (samples in no frame get zero gradient)
@@ -387,11 +400,14 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
     const int64_t rc_cap = (int64_t)(p.bwd_rows_cap / sizeof(RowChunk));
     if (n_clips <= 64) {
         const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((n_frames + 255) / 256, p.cu_count));
-        k_bwd_tables<<<grid, 256, 0, s>>>(d_off, n_clips, N, H, n_frames, fstart,
-                                          d_gwave ? (RowChunk *)p.d_bwd_rows : nullptr, rc_cap, p.d_nchunks + 1);
+        const int v = call_variant(p, n_clips, n_frames);
+        ClipTable clips;
+        st = prepare_clips(p, 0, d_off, n_clips, n_frames, melt_chunk_frames(p, v), v, clips, s);
+        if (st != MELT_OK) return st;
+        k_bwd_tables<<<grid, 256, 0, s>>>(clips, H, n_frames, fstart, d_gwave ? (RowChunk *)p.d_bwd_rows : nullptr, rc_cap,
+                                          p.d_nchunks + 1);
         st = hip_check(hipGetLastError(), "bwd tables");
         if (st != MELT_OK) return st;
-        keep_prepared(p, 0, n_clips, n_frames);
     } else {
         st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p), n_frames, s);
         if (st != MELT_OK) return st;

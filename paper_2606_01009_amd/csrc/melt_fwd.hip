@@ -335,6 +335,13 @@ static melt_status enqueue_schedule(const Plan &p, const int64_t *d_off, int n_c
     return hip_check(hipGetLastError(), "schedule launch");
 }
 
+static void set_prepared(Plan &p, int which, int n_clips, int64_t n_frames, int bf, int variant) {
+    p.prepared_frames[which] = n_frames;
+    p.prepared_bf[which] = bf;
+    p.prepared_clips[which] = n_clips;
+    if (which == 0) p.prepared_variant = variant;
+}
+
 melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clips, int bf_max, int64_t n_frames,
                             hipStream_t s, int variant) {
     // Chunks of at most bf_max frames (the kernel's LDS image).  The comparator sizes its
@@ -347,13 +354,29 @@ melt_status launch_schedule(Plan &p, int which, const int64_t *d_off, int n_clip
     melt_status st = ensure_chunks(p, which, need);
     if (st != MELT_OK) return st;
     st = enqueue_schedule(p, d_off, n_clips, bf, need, p.d_chunks[which], p.chunk_cap[which], p.d_nchunks + which, s);
-    if (st == MELT_OK) {
-        p.prepared_frames[which] = n_frames;
-        p.prepared_bf[which] = bf;
-        p.prepared_clips[which] = n_clips;
-        if (which == 0) p.prepared_variant = variant < 0 ? p.tune_variant : variant;
-    }
+    if (st == MELT_OK) set_prepared(p, which, n_clips, n_frames, bf, variant < 0 ? p.tune_variant : variant);
     return st;
+}
+
+// The batch of a kernel that finds its own chunks and leaves them in table `which` (chunks of bf
+// frames): the batch is the plan's prepared one afterwards, as when a table is built for the call.
+// Where the table would have to grow inside a stream capture, which cannot be, none is left.
+melt_status prepare_clips(Plan &p, int which, const int64_t *d_off, int n_clips, int64_t n_frames, int bf, int variant,
+                          ClipTable &t, hipStream_t s) {
+    const int64_t est = n_frames / bf + n_clips;
+    if (est + 1 > p.chunk_cap[which]) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+            t = {d_off, n_clips, p.N, bf, (int)est, nullptr, nullptr};
+            p.prepared_frames[which] = -1;
+            return MELT_OK;
+        }
+        const melt_status st = ensure_chunks(p, which, est + 1);
+        if (st != MELT_OK) return st;
+    }
+    t = {d_off, n_clips, p.N, bf, (int)est, p.d_chunks[which], p.d_nchunks + which};
+    set_prepared(p, which, n_clips, n_frames, bf, variant);
+    return MELT_OK;
 }
 
 melt_status launch_frame_offsets(const int64_t *d_off, int n_clips, int N, int H, int64_t *d_fo, hipStream_t s) {
@@ -642,12 +665,10 @@ static bool self_scheduled(const Plan &p, int variant, int n_clips, int64_t n_fr
     }
 }
 
-static melt_status launch_melt_clips(Plan &p, int variant, const int64_t *d_off, int n_clips, int64_t n_frames,
-                                     const float *d_wave, float *d_out, float *d_proj, hipStream_t s) {
-    const int bf = melt_chunk_frames(p, variant);
-    const int64_t est = n_frames / bf + n_clips;
-    FwdTask t{nullptr, nullptr, est, n_frames, d_wave, d_out, d_proj, s};
-    t.clips = {d_off, n_clips, p.N, bf, (int)est};
+static melt_status launch_melt_clips(Plan &p, int variant, const ClipTable &clips, int64_t n_frames, const float *d_wave,
+                                     float *d_out, float *d_proj, hipStream_t s) {
+    FwdTask t{nullptr, nullptr, clips.cap, n_frames, d_wave, d_out, d_proj, s};
+    t.clips = clips;
     return launch_variant(p, variant, t);
 }
 
@@ -656,7 +677,7 @@ static melt_status launch_melt_clips(Plan &p, int variant, const int64_t *d_off,
 // CUs, the row-split kernel on those spreads wider and starts without the basis in LDS (16 x 4 s:
 // 11.9 us against 14.1 us frame-split at 80 Mel bins, 12.3 against 16.5 at 128); below 4 row
 // tiles the frame-split one is the faster there too (10.5 against 11.9 us at 24 Mel bins).
-static int call_variant(const Plan &p, int n_clips, int64_t n_frames) {
+int call_variant(const Plan &p, int n_clips, int64_t n_frames) {
     const int v = p.tune_variant;
     if (p.tune_pinned || variant_at(p, v).kind != V_F8_FS || p.row_tiles < 4 || n_frames / 64 + n_clips > p.cu_count) return v;
     for (int i = 0; i < p.n_variants; ++i)
@@ -664,15 +685,8 @@ static int call_variant(const Plan &p, int n_clips, int64_t n_frames) {
     return v;
 }
 
-// After a call that built no table: a batch prepared earlier stays prepared if it is of the
-// call's size (as when the call is over that batch); any other is dropped, as a call that builds
-// its own table in the same place drops it.
-void keep_prepared(Plan &p, int which, int n_clips, int64_t n_frames) {
-    if (p.prepared_frames[which] != n_frames || p.prepared_clips[which] != n_clips) p.prepared_frames[which] = -1;
-}
-
-// The forward over a batch: without a chunk table where the kernel schedules itself (a batch
-// prepared earlier then stays prepared), through table 0 otherwise.
+// The forward over a batch, which is the plan's prepared one afterwards: table 0 is written by the
+// kernel where it schedules itself, and read by it otherwise.
 melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, float *d_proj, hipStream_t s) {
     const int v = call_variant(p, n_clips, n_frames);
@@ -680,10 +694,12 @@ melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int6
         const melt_status st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p, v), n_frames, s, v);
         return st == MELT_OK ? launch_melt_main(p, d_wave, d_out, d_proj, s) : st;
     }
-    keep_prepared(p, 0, n_clips, n_frames);
-    if (p.K == 0) return launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, d_out, d_proj, s);
-    melt_status st = ensure_lmel(p, n_frames);
-    if (st == MELT_OK) st = launch_melt_clips(p, v, d_off, n_clips, n_frames, d_wave, p.d_lmel, d_proj, s);
+    ClipTable clips;
+    melt_status st = prepare_clips(p, 0, d_off, n_clips, n_frames, melt_chunk_frames(p, v), v, clips, s);
+    if (st != MELT_OK) return st;
+    if (p.K == 0) return launch_melt_clips(p, v, clips, n_frames, d_wave, d_out, d_proj, s);
+    st = ensure_lmel(p, n_frames);
+    if (st == MELT_OK) st = launch_melt_clips(p, v, clips, n_frames, d_wave, p.d_lmel, d_proj, s);
     return st == MELT_OK ? launch_cepstrum(p, p.d_lmel, n_frames, d_out, s) : st;
 }
 
@@ -760,8 +776,11 @@ melt_status forward_noalloc(Plan &p, const float *d_wave, const int64_t *d_off, 
     Chunk *tab = reinterpret_cast<Chunk *>(static_cast<unsigned char *>(base) + kScratchTable);
     // the schedule kernels write the count unconditionally, so nothing in the scratch needs clearing
     const int vc = call_variant(p, n_clips, n_frames);
-    if (self_scheduled(p, vc, n_clips, n_frames))
-        return launch_melt_clips(p, vc, d_off, n_clips, n_frames, d_wave, d_out, nullptr, s);
+    if (self_scheduled(p, vc, n_clips, n_frames)) {
+        const int bc = melt_chunk_frames(p, vc);
+        const ClipTable clips{d_off, n_clips, p.N, bc, (int)(n_frames / bc + n_clips), nullptr, nullptr};
+        return launch_melt_clips(p, vc, clips, n_frames, d_wave, d_out, nullptr, s);
+    }
     const melt_status st = enqueue_schedule(p, d_off, n_clips, bf, need, tab, kScratchChunks, n_tab, s);
     if (st != MELT_OK) return st;
     return launch_melt_table(p, v, tab, n_tab, need - 1, n_frames, d_wave, d_out, nullptr, s);

@@ -154,7 +154,10 @@ melt_status launch_melt_table(Plan &p, int variant, const Chunk *tab, const int 
                               int64_t n_frames, const float *d_wave, float *d_out, float *d_proj, hipStream_t s);
 melt_status launch_melt_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, float *d_proj, hipStream_t s);
-void keep_prepared(Plan &p, int which, int n_clips, int64_t n_frames);
+struct ClipTable;
+melt_status prepare_clips(Plan &p, int which, const int64_t *d_off, int n_clips, int64_t n_frames, int bf, int variant,
+                          ClipTable &t, hipStream_t s);
+int call_variant(const Plan &p, int n_clips, int64_t n_frames);
 melt_status launch_stft_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, hipStream_t s);
 void init_variants(Plan &p);             // melt_fwd.hip: fills the plan's variant table

@@ -13,6 +13,8 @@ struct ClipTable {
     const int64_t *off;    // device, n_clips + 1
     int n_clips, N, bf;    // clips (<= 64), frame length, frames per chunk
     int cap;               // chunks at most: those beyond it start past the output's last row
+    Chunk *tab;            // where the entries and their count are left for the prepared calls, as a
+    int *n_tab;            // table's kernel leaves them (nullptr: nowhere)
 };
 
 // a value that is the same on every lane, as a scalar
@@ -87,6 +89,13 @@ __device__ __forceinline__ int chunk_list(const ClipTable &b, int H, int64_t c, 
     const int n = (int)(s.total < b.cap ? s.total : b.cap);
     if (store && lane < count && c < n) list[lane] = e;
     return __builtin_amdgcn_readfirstlane(n);
+}
+// The same wave's entries into the batch's table, and the count (n) from workgroup 0.
+__device__ __forceinline__ void leave_chunks(const ClipTable &b, int64_t c, int count, const Chunk *list, int n) {
+    if (!b.tab) return;
+    const int lane = threadIdx.x & 63;
+    if (lane < count && c < n) b.tab[c] = list[lane];
+    if (lane == 0 && (blockIdx.x | blockIdx.y | blockIdx.z) == 0) *b.n_tab = n;
 }
 
 constexpr int kListEntries = 64;       // a workgroup's own entries, one per lane of the wave that finds them

@@ -357,7 +357,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE)
     Chunk *list = reinterpret_cast<Chunk *>(reinterpret_cast<char *>(smem) + a.list_off) + kStftList * wid;
     const int nch = own ? chunk_list(a.clips, a.H, c + (int64_t)lane * nw, kStftList, list, true) : *a.n_chunks;
     wave_sync();
-    if (c >= nch) return;
+    if (c >= nch) {
+        if (own) leave_chunks(a.clips, c, 0, list, nch);
+        return;
+    }
     // the wave's chunk k (index c), wave-uniform
     auto chunk_at = [&](int k) {
         if (!own) return a.chunks[c];
@@ -535,6 +538,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE)
         wave_sync();
         if (!more) break;
     }
+    // (here rather than when they are found: a global store ahead of the loop costs it 10 registers
+    // and its scalar loads, 84 us of 64 x 30 s where it was 109)
+    if (own) leave_chunks(a.clips, blockIdx.x * WAVES + wid + (int64_t)lane * nw, kStftList, list, nch);
 }
 
 // ------------------------------------------------------------------ host side
@@ -682,8 +688,9 @@ melt_status launch_stft_forward(Plan &p, const int64_t *d_off, int n_clips, int6
         const int64_t est = n_frames / bf + n_clips;
         if (stft_per_cu(with) == stft_per_cu(lds) && with <= 160 * 1024 &&
             est <= (int64_t)kStftList * kStftWaves * stft_grid(p, lds, n_frames, bf, n_clips)) {
-            keep_prepared(p, 1, n_clips, n_frames);
-            return launch_stft(p, ClipTable{d_off, n_clips, p.N, bf, (int)est}, n_frames, bf, n_clips, d_wave, d_out, s);
+            ClipTable clips;
+            const melt_status st = prepare_clips(p, 1, d_off, n_clips, n_frames, bf, -1, clips, s);
+            return st == MELT_OK ? launch_stft(p, clips, n_frames, bf, n_clips, d_wave, d_out, s) : st;
         }
     }
     const melt_status st = launch_schedule(p, 1, d_off, n_clips, stft_chunk_frames(p), n_frames, s);
