@@ -138,25 +138,25 @@ __global__ __launch_bounds__(256) void k_bwd_tables(ClipTable b, int H, int64_t 
                                                     RowChunk *__restrict__ rc, int64_t rc_cap, int *__restrict__ n_rc) {
     const int64_t *__restrict__ off = b.off;
     const int n_clips = b.n_clips, N = b.N;
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = gridDim.x * 4;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blockIdx.x + 1 == gridDim.x) {                   // the last workgroup: the chunk table
+        if (!b.tab) return;
+        const ClipScan s = clip_scan(off, n_clips, N, H, b.bf);
+        const int64_t n = uniform64(s.total < b.cap ? s.total : b.cap);
+        for (int64_t q0 = 64 * w; q0 < n; q0 += 256) {
+            const Chunk e = clip_chunk(s, H, b.bf, q0 + lane);
+            if (q0 + lane < n) b.tab[q0 + lane] = e;
+        }
+        if (threadIdx.x == 0) *b.n_tab = (int)n;
+        return;
+    }
+    const int64_t wave = blockIdx.x * 4 + w, waves = (gridDim.x - 1) * 4;
     const ClipScan s = clip_scan(off, n_clips, N, H, 1);
     const int64_t total = uniform64(s.total);
     for (int64_t q0 = 64 * wave; q0 < n_frames; q0 += 64 * waves) {       // wave-uniform trip count
         const int64_t q = q0 + lane;
         const Chunk e = clip_chunk(s, H, 1, q);
         if (q < n_frames) fstart[q] = q < total ? e.sample_start : -1;
-    }
-    // the chunk table on the last waves, the row chunks on the first
-    const int64_t back = waves - 1 - wave;
-    if (b.tab && 64 * back < b.cap) {
-        const ClipScan sc = clip_scan(off, n_clips, N, H, b.bf);
-        const int64_t n = uniform64(sc.total < b.cap ? sc.total : b.cap);
-        for (int64_t q0 = 64 * back; q0 < n; q0 += 64 * waves) {
-            const Chunk e = clip_chunk(sc, H, b.bf, q0 + lane);
-            if (q0 + lane < n) b.tab[q0 + lane] = e;
-        }
-        if (back == 0 && lane == 0) *b.n_tab = (int)n;
     }
     if (!rc) return;
     // rows covering the whole clip (samples in no frame get zero gradient)
@@ -404,7 +404,7 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
         ClipTable clips;
         st = prepare_clips(p, 0, d_off, n_clips, n_frames, melt_chunk_frames(p, v), v, clips, s);
         if (st != MELT_OK) return st;
-        k_bwd_tables<<<grid, 256, 0, s>>>(clips, H, n_frames, fstart, d_gwave ? (RowChunk *)p.d_bwd_rows : nullptr, rc_cap,
+        k_bwd_tables<<<grid + 1, 256, 0, s>>>(clips, H, n_frames, fstart, d_gwave ? (RowChunk *)p.d_bwd_rows : nullptr, rc_cap,
                                           p.d_nchunks + 1);
         st = hip_check(hipGetLastError(), "bwd tables");
         if (st != MELT_OK) return st;
