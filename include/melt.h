@@ -79,8 +79,8 @@ typedef enum {
  *   FP32     - FP32 operands.  Each is the exact sum of three bfloat16 planes; six of the nine
  *              plane products run on the bfloat16 matrix cores (the others are below 2^-25 of
  *              a term), with an error against 64 bits no larger than the FP32 matrix cores'.
- *              Frames whose samples the planes cannot hold (non-finite, or rounding to infinity
- *              in bfloat16) are computed with plain FP32 arithmetic.  Geometries that would
+ *              Frames whose samples the planes cannot hold (non-finite, or of 1e31 and more) are
+ *              computed with plain FP32 arithmetic.  Geometries that would
  *              pad the planes' 32-column groups by more than half (hops of a few samples) use
  *              v_mfma_f32_32x32x2_f32.
  *   BF16     - bfloat16 operands

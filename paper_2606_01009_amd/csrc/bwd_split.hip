@@ -82,7 +82,7 @@ __device__ __forceinline__ void SplitDx::store(const SplitItem &it, int fbase, i
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
             const int c = 16 * tile[r] + 4 * q;
-            const f32x4 y = acc[f][r];
+            const f32x4 y = acc[f][r] *= kPlaneUnscale;
             probe = fmaf(y[0] + y[1] + y[2] + y[3], 0.0f, probe);
             if (tile[r] >= g.T16) continue;
             if (c + 4 <= hop && s + c + 4 <= s_end) {
@@ -369,7 +369,7 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int q = q0 + 64 * wq + 16 * i + 4 * (lane >> 4) + r;
-                if (q < Q) o[(size_t)q * N + n] = acc[i][j][r];
+                if (q < Q) o[(size_t)q * N + n] = acc[i][j][r] * kPlaneUnscale;
             }
     }
     if (cur) __syncthreads();                          // the staging waves take steps in pairs

@@ -776,6 +776,9 @@ inline size_t ks_lds_bytes(const Plan &p, int bf) {
     return ks_red_offset(p, bf) + (size_t)((p.row_tiles + rg - 1) / rg) * 2048 * 4;
 }
 
+// Both operands of a product on three bfloat16 planes are multiplied by 2^24 (melt_split.h).
+constexpr float kPlaneScale = 0x1p24f, kPlaneUnscale = 0x1p-48f;
+
 // Geometries the FP32-MFMA kernels and the 16-bit frame-split kernel take.
 inline bool f32_fits(const Plan &p) {
     return (size_t)(kBF32 + p.geo32.J - 1) * lds_stride(p.geo32.Hp, 4) * 4 <= (size_t)kMaxLds && p.geo32.n_groups <= 512 &&

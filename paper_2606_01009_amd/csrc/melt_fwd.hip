@@ -146,9 +146,10 @@ __device__ __forceinline__ void pack_h16(const PackJob &j, const float *b32, int
                                                  : f32_to_f16_bits(v - f16_bits_to_f32(f32_to_f16_bits(v)));
 }
 
-// P planes of a value, 512 elements apart
+// P planes of a value, 512 elements apart (three: of the scaled value)
 __device__ __forceinline__ void put_planes(unsigned short *out, float v, int form) {
     const int P = form & 7;
+    if (P == 3) v *= kPlaneScale;
     for (int p = 0; p < P; ++p) {
         const unsigned short b = form & 8 ? f32_to_f16_bits(v) : f32_to_bf16_bits(v);
         out[p * 512] = b;

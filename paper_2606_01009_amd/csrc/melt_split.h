@@ -2,10 +2,13 @@
 // projection runs as the plane products that matter, on the 16-bit matrix cores with FP32
 // accumulation (Eq. dmp_projection, Eq. dmp_matrix_energy, Eq. meltf).
 //
-//   Split3BF16 (FP32)  three bfloat16 planes hold all 24 significand bits of an FP32 value
-//                      (each residual is exact), and bfloat16 has FP32's exponent range; of
-//                      the nine products the six down to 2^-16 relative are kept, so a term is
-//                      off by about 2^-26, below the FP32 rounding of the basis itself
+//   Split3BF16 (FP32)  three bfloat16 planes of 2^24 x hold all 24 significand bits of an FP32
+//                      value (each residual is exact): bfloat16 has FP32's exponent range, and the
+//                      factor, undone on the accumulators, keeps the third plane of the smallest
+//                      values, subnormal ones too, out of bfloat16's own subnormals.  Values of
+//                      2^103 and more become infinities (split_redo).  Of the nine products the
+//                      six down to 2^-16 relative are kept, so a term is off by about 2^-26,
+//                      below the FP32 rounding of the basis itself
 //   Split2BF16, Split2F16 (BF16X3, FP16X3)  hi and lo planes, three products
 //
 // What bounds it: the matrix cores (P = 3: six products, 147 GFLOP on 64 x 30 s at N = 400,
@@ -34,7 +37,7 @@ namespace melt {
 
 typedef unsigned split_u32x4 __attribute__((ext_vector_type(4)));
 
-// Four FP32 values -> P planes of four 16-bit values (two dwords each).
+// Four FP32 values -> P planes of four 16-bit values (two dwords each).  (kPlaneScale: fwd_common.h)
 struct Split3BF16 {
     static constexpr int P = 3, NP = 6;
     // plane products (basis plane, frame plane), frame plane 2 first: the k-loop refills the
@@ -44,7 +47,7 @@ struct Split3BF16 {
     __device__ static void split(f32x4 v, unsigned (&w)[6]) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const float x = v[2 * h], y = v[2 * h + 1];
+            const float x = v[2 * h] * kPlaneScale, y = v[2 * h + 1] * kPlaneScale;
             const unsigned b0 = pk_bf16(x, y);
             const float x1 = x - __builtin_bit_cast(float, b0 << 16), y1 = y - __builtin_bit_cast(float, b0 & 0xffff0000u);
             const unsigned b1 = pk_bf16(x1, y1);
@@ -201,7 +204,7 @@ __device__ __forceinline__ void split_write(const FwdArgs &a, int nrows, int lt,
 }
 
 // One output recomputed with plain FP32 arithmetic: the planes of an infinity (or of a value
-// that rounds to one in bfloat16) are inf and -inf or NaN, so where the split projection is not
+// that becomes one, 2^24 times it in bfloat16) are inf and -inf or NaN, so where the split projection is not
 // finite it is taken again without splitting.
 __device__ __forceinline__ void split_redo(const FwdArgs &a, const SplitGeo &g, int64_t first, int64_t row, int mel) {
     const float *x = a.wave + first, *wr = g.basis + (size_t)mel * g.N, *wi = wr + (size_t)a.M * g.N;
@@ -281,11 +284,12 @@ __device__ __forceinline__ void SplitForward::store(const SplitItem &it, int fba
                                                     f32x4 (&acc)[FT][RT]) const {
     asm volatile("" : "+v"(lane));      // addresses formed per item, not kept across the multiply phase
     const int q = lane >> 4, f0 = fbase + (lane & 15);
-    if constexpr (std::is_same<Op, Split2F16>::value) {
+    if constexpr (!std::is_same<Op, Split2BF16>::value) {
+        constexpr float unscale = Op::P == 3 ? kPlaneUnscale : 1.0f / kF16x3Scale;     // powers of two: exact
 #pragma unroll
         for (int f = 0; f < FT; ++f)
 #pragma unroll
-            for (int r = 0; r < RT; ++r) acc[f][r] *= 1.0f / kF16x3Scale;      // exact
+            for (int r = 0; r < RT; ++r) acc[f][r] *= unscale;
     }
     if (a.proj) {
 #pragma unroll
