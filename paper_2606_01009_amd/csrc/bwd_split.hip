@@ -165,6 +165,52 @@ melt_status launch_dx_split(const Plan &p, const float *G, const RowChunk *rows,
 // every wave staging its share behind its multiplies (24 4-byte loads each, the VALU work of
 // the split after the last MFMA) a step took 7300 cycles for those 3072; the whole backward of
 // 27 456 frames, N = 1024, M = 128, was 182 us where it is 164.
+// A wave's 64 q x 128 n of dW over frames [t0, t1) in plain FP32, on the FP32 matrix cores (4 frames
+// and 1024 cycles a step, the next one's loads in flight): where a sum on planes is not finite.
+// A NaN or infinity costs the waves that meet it about twice the time that their planes took, however
+// many there are: 27 456 frames, N = 1024, M = 128, 0.11 ms a d/dbasis, 0.27 with one NaN gradient,
+// 0.28 with nothing else (36 ms where each sum was one thread's, over all frames).
+__device__ __forceinline__ void dw_plain(const float *__restrict__ G, const int64_t *__restrict__ fstart,
+                                         const float *__restrict__ wave, const float *some, int64_t t0, int64_t t1, int Q,
+                                         int N, int qw, int nw, f32x4 (&acc)[4][8]) {
+    const int lane = threadIdx.x & 63, k = lane >> 4;
+    auto start = [&](int64_t t) { return t + k < t1 ? fstart[t + k] : -1; };
+    auto load = [&](int64_t t, int64_t st, float (&a)[4], float (&b)[8]) {
+        const bool ok = st >= 0;                       // else from where there are N floats (`some`) and a row of G
+        const float *g = G + (ok ? t + k : t0) * Q, *x = ok ? wave + st : some;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = g[min(qw + 16 * i + (lane & 15), Q - 1)];
+            a[i] = ok ? v : 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float v = x[min(nw + 16 * j + (lane & 15), N - 1)];
+            b[j] = ok ? v : 0.0f;
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{};
+    float a[4], b[8], an[4], bn[8];
+    load(t0, start(t0), a, b);
+    int64_t st = start(t0 + 4);
+#pragma unroll 1
+    for (int64_t t = t0; t < t1; t += 4) {
+        load(t + 4, st, an, bn);
+        st = start(t + 8);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = an[i];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) b[j] = bn[j];
+    }
+}
+
 typedef float dw_f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kDwQ = 128, kDwN = 256, kDwT = 32;
 constexpr int kDwTile = 3 * 1024 + 16;                     // bytes from one tile's planes to the next's
@@ -358,21 +404,36 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][7] += sum[1][i];
     }
-    // lane holds column n, rows q = tile base + 4 (lane / 16) + r (interleaved q)
-    float *o = part + (size_t)split * Q * N;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int n = n0 + 128 * wn + 16 * j + (lane & 15);
-        if (n >= N) continue;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int q = q0 + 64 * wq + 16 * i + 4 * (lane >> 4) + r;
-                if (q < Q) o[(size_t)q * N + n] = acc[i][j][r] * kPlaneUnscale;
-            }
-    }
     if (cur) __syncthreads();                          // the staging waves take steps in pairs
+    // lane holds column n, rows q = tile base + 4 (lane / 16) + r (interleaved q)
+    const int qw = q0 + 64 * wq, nw = n0 + 128 * wn;
+    float *o = part + (size_t)split * Q * N, probe = 0.0f;      // probe stays 0 while every sum is finite
+    auto each = [&](auto &&put) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int n = nw + 16 * j + (lane & 15);
+            if (n >= N) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int q = qw + 16 * i + 4 * (lane >> 4) + r;
+                    if (q < Q) put(o + (size_t)q * N + n, acc[i][j][r]);
+                }
+        }
+    };
+    each([&](float *at, float v) {
+        v *= kPlaneUnscale;
+        probe = fmaf(v, 0.0f, probe);
+        *at = v;
+    });
+    if (__any(!(probe == 0.0f))) {
+        // the planes of an infinity are not a product with it
+        dw_plain(G, fstart, wave, part, t0, t1, Q, N, qw, nw, acc);
+        each([&](float *at, float v) {
+            if (!(*at * 0.0f == 0.0f)) *at = v;
+        });
+    }
 }
 
 int dw_split_blocks(const Plan &p) { return (2 * p.M + kDwQ - 1) / kDwQ * ((p.N + kDwN - 1) / kDwN); }

@@ -258,19 +258,8 @@ __global__ __launch_bounds__(256) void k_bwd_dx(const RowChunk *__restrict__ rc,
 
 // Sums the splits' partials in split order (so the result does not depend on the launch),
 // four consecutive n per thread with 16-byte loads when N is a multiple of 4, eight splits'
-// loads in flight at a time.  A sum that is not finite is taken again in plain FP32 (redo): the
-// operand planes of an infinity are not a product with it.
-__device__ __forceinline__ float dw_redo(const float *G, const int64_t *fstart, const float *wave, int64_t T, int Q, int q,
-                                         int n) {
-    float s = 0.0f;
-#pragma unroll 1
-    for (int64_t t = 0; t < T; ++t)
-        if (fstart[t] >= 0) s = fmaf(G[t * Q + q], wave[fstart[t] + n], s);
-    return s;
-}
-__global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, int N, float *__restrict__ dW,
-                             const float *__restrict__ G, const int64_t *__restrict__ fstart,
-                             const float *__restrict__ wave, int64_t T) {
+// loads in flight at a time.
+__global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, int N, float *__restrict__ dW) {
     const int64_t total = (int64_t)2 * M * N;
     if ((N & 3) == 0) {
         const int64_t total4 = total / 4;
@@ -287,10 +276,6 @@ __global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, 
             }
             for (; k < splits; ++k) s += *(const f32x4 *)(part + (size_t)k * total + 4 * i);
             const int q = (int)((4 * i) / N), n = (int)(4 * i - (int64_t)q * N);
-            if (!((s[0] + s[1] + s[2] + s[3]) * 0.0f == 0.0f)) {
-                for (int e = 0; e < 4; ++e)
-                    if (!(s[e] * 0.0f == 0.0f)) s[e] = dw_redo(G, fstart, wave, T, 2 * M, q, n + e);
-            }
             *(f32x4 *)(dW + (size_t)((q & 1) * M + (q >> 1)) * N + n) = s;   // interleaved q -> stacked rows
         }
         return;
@@ -299,7 +284,6 @@ __global__ void k_bwd_reduce(const float *__restrict__ part, int splits, int M, 
         float s = 0.0f;
         for (int k = 0; k < splits; ++k) s += part[(size_t)k * total + i];
         const int q = (int)(i / N), n = (int)(i - (int64_t)q * N);
-        if (!(s * 0.0f == 0.0f)) s = dw_redo(G, fstart, wave, T, 2 * M, q, n);
         dW[(size_t)((q & 1) * M + (q >> 1)) * N + n] = s;    // interleaved q -> stacked rows
     }
 }
@@ -452,7 +436,7 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
     if (d_gbasis) {
         st = launch_dw_split(p, G, fstart, d_wave, n_frames, splits, part, s);
         if (st != MELT_OK) return st;
-        k_bwd_reduce<<<512, 256, 0, s>>>(part, splits, M, N, d_gbasis, G, fstart, d_wave, n_frames);
+        k_bwd_reduce<<<512, 256, 0, s>>>(part, splits, M, N, d_gbasis);
         st = hip_check(hipGetLastError(), "bwd reduce");
     }
     return st;
