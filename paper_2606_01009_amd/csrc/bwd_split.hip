@@ -72,6 +72,7 @@ __device__ __forceinline__ void SplitDx::store(const SplitItem &it, int fbase, i
     const int q = lane >> 4, i0 = fbase + (lane & 15);
     const int64_t ci = it.out_row / kSplitChunk, f0 = it.out_row - ci * kSplitChunk;
     const int64_t s0 = split_scalar(a.chunks, 5 * ci) + f0 * hop, s_end = split_scalar(a.chunks, 5 * ci + 1);
+    const float unscale = split_unscale(kPlaneUnscale);
     float probe = 0.0f;
 #pragma unroll
     for (int f = 0; f < FT; ++f) {
@@ -82,7 +83,7 @@ __device__ __forceinline__ void SplitDx::store(const SplitItem &it, int fbase, i
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
             const int c = 16 * tile[r] + 4 * q;
-            const f32x4 y = acc[f][r] *= kPlaneUnscale;
+            const f32x4 y = acc[f][r] *= unscale;
             probe = fmaf(y[0] + y[1] + y[2] + y[3], 0.0f, probe);
             if (tile[r] >= g.T16) continue;
             if (c + 4 <= hop && s + c + 4 <= s_end) {
@@ -407,6 +408,7 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
     if (cur) __syncthreads();                          // the staging waves take steps in pairs
     // lane holds column n, rows q = tile base + 4 (lane / 16) + r (interleaved q)
     const int qw = q0 + 64 * wq, nw = n0 + 128 * wn;
+    const float unscale = split_unscale(kPlaneUnscale);
     float *o = part + (size_t)split * Q * N, probe = 0.0f;      // probe stays 0 while every sum is finite
     auto each = [&](auto &&put) {
 #pragma unroll
@@ -423,7 +425,7 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
         }
     };
     each([&](float *at, float v) {
-        v *= kPlaneUnscale;
+        v *= unscale;
         probe = fmaf(v, 0.0f, probe);
         *at = v;
     });

@@ -231,6 +231,12 @@ struct SplitItem {
     int64_t start, end, out_row;
     int nf, lo;
 };
+// The factor that undoes the scaling of the operands, hidden from the compiler, which would move its
+// multiplications up into the last block of the k-loop, for every k-group.
+__device__ __forceinline__ float split_unscale(float v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
 // Chunk-table entries through the scalar cache: a vector load's wait would also drain the wave's
 // output stores.
 __device__ __forceinline__ int64_t split_scalar(const void *base, int64_t i) {
@@ -285,7 +291,7 @@ __device__ __forceinline__ void SplitForward::store(const SplitItem &it, int fba
     asm volatile("" : "+v"(lane));      // addresses formed per item, not kept across the multiply phase
     const int q = lane >> 4, f0 = fbase + (lane & 15);
     if constexpr (!std::is_same<Op, Split2BF16>::value) {
-        constexpr float unscale = Op::P == 3 ? kPlaneUnscale : 1.0f / kF16x3Scale;     // powers of two: exact
+        const float unscale = split_unscale(Op::P == 3 ? kPlaneUnscale : 1.0f / kF16x3Scale);     // exact
 #pragma unroll
         for (int f = 0; f < FT; ++f)
 #pragma unroll
