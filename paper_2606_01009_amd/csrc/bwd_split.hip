@@ -44,11 +44,10 @@ struct SplitDx {
         return {start, start + (int64_t)max(r_hi, r_lo) * a.H, (int64_t)ci * kSplitChunk + f0, nf, r_lo * a.H};
     }
     template <class Op, int FT, int RT>
-    __device__ __forceinline__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+    __device__ __forceinline__ bool store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+    template <int FS, int RT>
+    __device__ __forceinline__ void again(const SplitItem &, int, int, const int (&)[RT]) const {}
 };
-
-// four floats at any 4-byte address (the hop and the clips' starts may be odd)
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // One sample of dx in plain FP32: hop-block row b of the chunk (item-local row i), column c.
 __device__ __forceinline__ float dx_redo(const SplitDx &d, const SplitItem &it, int i, int c) {
@@ -66,7 +65,7 @@ __device__ __forceinline__ float dx_redo(const SplitDx &d, const SplitItem &it, 
 }
 
 template <class Op, int FT, int RT>
-__device__ __forceinline__ void SplitDx::store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT],
+__device__ __forceinline__ bool SplitDx::store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT],
                                                f32x4 (&acc)[FT][RT]) const {
     asm volatile("" : "+v"(lane));
     const int q = lane >> 4, i0 = fbase + (lane & 15);
@@ -114,6 +113,7 @@ __device__ __forceinline__ void SplitDx::store(const SplitItem &it, int fbase, i
             if (!(y * 0.0f == 0.0f) && i < it.nf && t < g.T16 && c < hop && s < s_end) a.out[s] = dx_redo(*this, it, i, c);
         }
     }
+    return false;
 }
 
 // k-groups of G rows: J segments of 2M columns

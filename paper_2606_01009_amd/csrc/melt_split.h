@@ -6,7 +6,7 @@
 //                      value (each residual is exact): bfloat16 has FP32's exponent range, and the
 //                      factor, undone on the accumulators, keeps the third plane of the smallest
 //                      values, subnormal ones too, out of bfloat16's own subnormals.  Values of
-//                      2^103 and more become infinities (split_redo).  Of the nine products the
+//                      2^103 and more become infinities (split_again).  Of the nine products the
 //                      six down to 2^-16 relative are kept, so a term is off by about 2^-26,
 //                      below the FP32 rounding of the basis itself
 //   Split2BF16, Split2F16 (BF16X3, FP16X3)  hi and lo planes, three products
@@ -203,34 +203,67 @@ __device__ __forceinline__ void split_write(const FwdArgs &a, int nrows, int lt,
     }
 }
 
-// One output recomputed with plain FP32 arithmetic: the planes of an infinity (or of a value
-// that becomes one, 2^24 times it in bfloat16) are inf and -inf or NaN, so where the split projection is not
-// finite it is taken again without splitting.
-__device__ __forceinline__ void split_redo(const FwdArgs &a, const SplitGeo &g, int64_t first, int64_t row, int mel) {
-    const float *x = a.wave + first, *wr = g.basis + (size_t)mel * g.N, *wi = wr + (size_t)a.M * g.N;
-    float R = 0.0f, I = 0.0f;
-#pragma unroll 1
-    for (int n = 0; n < g.N; ++n) {
-        R = fmaf(x[n], wr[n], R);
-        I = fmaf(x[n], wi[n], I);
-    }
-    const float S = R * R + I * I;
-    a.out[row * a.M + mel] = a.out_kind == MELT_OUT_LOG_POWER       ? out_map_k<MELT_OUT_LOG_POWER>(S, a.eps)
-                             : a.out_kind == MELT_OUT_LOG_MAGNITUDE ? out_map_k<MELT_OUT_LOG_MAGNITUDE>(S, a.eps)
-                             : a.out_kind == MELT_OUT_POWER         ? S
-                                                                    : sqrtf(S);
-    if (a.proj) {
-        a.proj[row * (2 * a.M) + 2 * mel] = R;
-        a.proj[row * (2 * a.M) + 2 * mel + 1] = I;
-    }
-}
-
 // One item of a workgroup: frames [f0, f0 + nf) of a chunk.  Its hop-block rows start at sample
 // `start`; samples before start + lo and from `end` on are zero.
 struct SplitItem {
     int64_t start, end, out_row;
     int nf, lo;
 };
+// four floats at any 4-byte address
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// FS frame tiles (from the item's frame f0 on) of a wave's RT row tiles in plain FP32, on the FP32
+// matrix cores.  Sixteen columns a step, four of them consecutive per lane, of one segment after the
+// other; frames and rows that do not exist repeat others.
+template <class Job, int FS, int RT>
+__device__ __forceinline__ void split_plain(const Job &job, const SplitItem &it, int f0, int lane, const int (&tile)[RT],
+                                            f32x4 (&acc)[FS][RT]) {
+    const int cols = job.plain_columns();
+#pragma unroll
+    for (int f = 0; f < FS; ++f)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) acc[f][r] = f32x4{};
+#pragma unroll 1
+    for (int s = 0; s < job.plain_segments(); ++s) {
+#pragma unroll 1
+        for (int c0 = 0; c0 < cols; c0 += 16) {
+            const int c = c0 + 4 * (lane >> 4);
+            f32x4 x[FS], w[RT];
+#pragma unroll
+            for (int f = 0; f < FS; ++f) x[f] = job.plain_samples(it, min(f0 + 16 * f + (lane & 15), it.nf - 1), s, c);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) w[r] = job.plain_weights(tile[r], lane & 15, s, c);
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int f = 0; f < FS; ++f)
+                        acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[r][e], x[f][e], acc[f][r], 0, 0, 0);
+        }
+        if (s == 0) {
+#pragma unroll
+            for (int f = 0; f < FS; ++f)
+#pragma unroll
+                for (int r = 0; r < RT; ++r) job.plain_first_segment(tile[r], lane >> 4, acc[f][r]);
+        }
+    }
+}
+
+// The kernel's first argument, read again: what a rare path alone uses of it takes no scalar registers
+// on the way there.
+template <class Job>
+__device__ __forceinline__ Job split_job_again() {
+    struct Words {
+        unsigned w[sizeof(Job) / 4];
+    } words;
+    auto p = (const __attribute__((address_space(4))) unsigned *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(Job) / 4; ++i) words.w[i] = p[i];
+    return __builtin_bit_cast(Job, words);
+}
+
 // The factor that undoes the scaling of the operands, hidden from the compiler, which would move its
 // multiplications up into the last block of the k-loop, for every k-group.
 __device__ __forceinline__ float split_unscale(float v) {
@@ -269,8 +302,30 @@ struct SplitForward {
         const int nf = min(SF, (int)split_scalar(a.chunks, 4 * (int64_t)ci + 3) - f0);      // low half: n_frames
         return {st + (int64_t)f0 * a.H, en, row + f0, nf > 0 ? nf : 0, 0};
     }
+    // (whether an output is not finite, where Op has three planes)
     template <class Op, int FT, int RT>
-    __device__ __forceinline__ void store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+    __device__ __forceinline__ bool store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
+    template <int FS, int RT>
+    __device__ __forceinline__ void again(const SplitItem &it, int f0, int lane, const int (&tile)[RT]) const;
+    // split_plain: one segment, the frame
+    __device__ __forceinline__ int plain_segments() const { return 1; }
+    __device__ __forceinline__ int plain_columns() const { return g.N; }
+    __device__ __forceinline__ f32x4 columns4(const float *p, int c) const {
+        if (c + 4 <= g.N) return *(const f32x4_any *)(p + c);
+        f32x4 v{};
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (c + e < g.N) v[e] = p[c + e];
+        return v;
+    }
+    __device__ __forceinline__ f32x4 plain_samples(const SplitItem &it, int frame, int, int c) const {
+        return columns4(a.wave + it.start + (int64_t)frame * a.H, c);
+    }
+    __device__ __forceinline__ f32x4 plain_weights(int t, int row, int, int c) const {
+        const int mel = min(split_tile_mel(min(t, g.T16 - 1), row >> 2, g.T16) + (row >> 1 & 1), a.M - 1);
+        return columns4(g.basis + (size_t)((row & 1) * a.M + mel) * g.N, c);
+    }
+    __device__ __forceinline__ void plain_first_segment(int, int, f32x4 &) const {}
 };
 
 // Output values of the two bins of each tile of one frame.
@@ -286,7 +341,7 @@ __device__ __forceinline__ void split_map(float eps, const f32x4 (&acc)[RT], flo
 
 // Accumulators -> output rows.  tile[]: pairs (r, r + 1) start at even tiles.
 template <class Op, int FT, int RT>
-__device__ __forceinline__ void SplitForward::store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT],
+__device__ __forceinline__ bool SplitForward::store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT],
                                                     f32x4 (&acc)[FT][RT]) const {
     asm volatile("" : "+v"(lane));      // addresses formed per item, not kept across the multiply phase
     const int q = lane >> 4, f0 = fbase + (lane & 15);
@@ -350,31 +405,84 @@ __device__ __forceinline__ void SplitForward::store(const SplitItem &it, int fba
             }
         }
     }
-    if constexpr (Op::P == 3) {
-        if (__any(!(probe == 0.0f))) {
-            uint64_t redo = 0;
+    return Op::P == 3 && __any(!(probe == 0.0f));
+}
+
+// The outputs and projections of FS frame tiles that are not finite, once more in plain FP32.
+template <int FS, int RT>
+__device__ __forceinline__ void SplitForward::again(const SplitItem &it, int f0, int lane, const int (&tile)[RT]) const {
+    const int q = lane >> 4;
+    unsigned bad[FS], any = 0;                          // of a row tile's two bins: output, projection
 #pragma unroll
-            for (int f = 0; f < FT; ++f)
+    for (int f = 0; f < FS; ++f) {
+        const int fl = f0 + 16 * f + (lane & 15);
+        const int64_t row = it.out_row + fl;
+        bad[f] = 0;
+        if (fl < it.nf && row < a.n_frames) {
 #pragma unroll
-                for (int r = 0; r < RT; ++r)
+            for (int r = 0; r < RT; ++r)
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const float R = acc[f][r][2 * k], I = acc[f][r][2 * k + 1];
-                        if (!((R * R + I * I) * 0.0f == 0.0f)) redo |= uint64_t(1) << ((f * RT + r) * 2 + k);
-                    }
-            while (redo) {
-                const int i = __builtin_ctzll(redo);
-                redo &= redo - 1;
-                const int k = i & 1, f = (i >> 1) / RT, r = (i >> 1) - f * RT;
-                int t = 0;
-#pragma unroll
-                for (int rr = 0; rr < RT; ++rr)
-                    if (rr == r) t = tile[rr];
-                const int fl = f0 + 16 * f, mel = split_tile_mel(t, q, g.T16) + k;
-                if (fl < it.nf && it.out_row + fl < a.n_frames && t < g.T16 && mel < a.M)
-                    split_redo(a, g, it.start + (int64_t)fl * a.H, it.out_row + fl, mel);
-            }
+                for (int k = 0; k < 2; ++k) {
+                    const int mel = split_tile_mel(tile[r], q, g.T16) + k;
+                    if (tile[r] >= g.T16 || mel >= a.M) continue;
+                    if (!(a.out[row * a.M + mel] * 0.0f == 0.0f)) bad[f] |= 1u << (4 * r + 2 * k);
+                    if (!a.proj) continue;
+                    const float2 p = *(const float2 *)(a.proj + row * (2 * a.M) + 2 * mel);
+                    if (!(fmaf(p.x, 0.0f, p.y * 0.0f) == 0.0f)) bad[f] |= 2u << (4 * r + 2 * k);
+                }
         }
+        any |= bad[f];
+    }
+    if (!__any(any != 0)) return;
+    f32x4 acc[FS][RT];
+    split_plain(*this, it, f0, lane, tile, acc);
+#pragma unroll
+    for (int f = 0; f < FS; ++f) {
+        const int64_t row = it.out_row + f0 + 16 * f + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int mel = split_tile_mel(tile[r], q, g.T16) + k;
+                const float R = acc[f][r][2 * k], I = acc[f][r][2 * k + 1], S = R * R + I * I;
+                if (bad[f] >> (4 * r + 2 * k) & 1)
+                    a.out[row * a.M + mel] = a.out_kind == MELT_OUT_LOG_POWER       ? out_map_k<MELT_OUT_LOG_POWER>(S, a.eps)
+                                             : a.out_kind == MELT_OUT_LOG_MAGNITUDE ? out_map_k<MELT_OUT_LOG_MAGNITUDE>(S, a.eps)
+                                             : a.out_kind == MELT_OUT_POWER         ? S
+                                                                                    : sqrtf(S);
+                if (bad[f] >> (4 * r + 2 * k) & 2) *(float2 *)(a.proj + row * (2 * a.M) + 2 * mel) = float2{R, I};
+            }
+    }
+}
+
+// The row tiles of a multiply wave (the row part is the workgroup's).
+template <int RT, int WF>
+__device__ __forceinline__ void split_wave_tiles(int wid, int parts, int (&tile)[RT]) {
+    const int t0 = ((int)(blockIdx.x % parts) * (4 / WF) + wid / WF) * RT;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        // an odd tile count that starts at an odd tile keeps its unpaired tile for last
+        tile[r] = (RT & 1) && (t0 & 1) ? (r == RT - 1 ? t0 : t0 + 1 + r) : t0 + r;
+    }
+}
+
+// A wave's items k0 .. k1 once more, where an output is not finite.  The planes of an infinity (or of a
+// value that becomes one, 2^24 times it in bfloat16) are inf and -inf or NaN, so what comes out is not
+// what FP32 arithmetic gives.  After the wave's last item rather than where it is found: there it cost
+// every call 1 to 2 % (scalar registers).  64 x 30 s, N 400, M 80: 0.130 ms, 0.161 with one NaN sample,
+// 0.525 with nothing else (0.63 and 17.2 where one lane took an output's terms one by one).
+template <class Job, int FT, int RT, int WF>
+__device__ __forceinline__ void split_again(int k0, int k1, int wid, const unsigned short *rows) {
+    const Job job = split_job_again<Job>();
+    const Chunk *list = reinterpret_cast<const Chunk *>(reinterpret_cast<const char *>(rows) + job.a.list_off);
+    const int lane = threadIdx.x & 63, fbase = wid % WF * FT * 16;
+    int tile[RT];
+    split_wave_tiles<RT, WF>(wid, job.g.parts, tile);
+    for (int k = k0; k <= k1; ++k) {
+        const SplitItem it = job.item(blockIdx.x + k * gridDim.x, k, list, WF * FT * 16);
+        constexpr int FS = FT > 1 && RT < 8 ? 2 : 1;       // (two of eight row tiles would spill)
+#pragma unroll 1
+        for (int f = fbase; f < fbase + 16 * FT && f < it.nf; f += 16 * FS) job.template again<FS, RT>(it, f, lane, tile);
     }
 }
 
@@ -425,16 +533,11 @@ void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
         }
         return;
     }
-    const int wf = wid % WF, wr = wid / WF;
-    constexpr int WR = 4 / WF, D = split_ring(FT, RT), U = D > RT ? D / RT : 1;
+    const int wf = wid % WF;
+    constexpr int D = split_ring(FT, RT), U = D > RT ? D / RT : 1;
     static_assert((U * RT) % D == 0, "the ring's slots repeat every U k-groups");
-    const int t0 = ((w % g.parts) * WR + wr) * RT;
     int tile[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        // an odd tile count that starts at an odd tile keeps its unpaired tile for last
-        tile[r] = (RT & 1) && (t0 & 1) ? (r == RT - 1 ? t0 : t0 + 1 + r) : t0 + r;
-    }
+    split_wave_tiles<RT, WF>(wid, g.parts, tile);
     const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)bpack, (short)0, g.T16 * g.NG * P * 1024, 0x00020000);
     const int voff = lane * 16;
@@ -453,6 +556,7 @@ void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
     __syncthreads();                               // rows of the first item ready
     const int fbase = wf * FT * 16;
     const int la0 = (fbase + (lane & 15)) * a.S + 8 * (lane >> 4);
+    int again0 = 0, again1 = -1;                   // items with an output that is not finite lie between
     for (; w < nitems; w += G, ++k) {
         const SplitItem it = job.item(w, k, list, SF);
         // two planes: a k-group's three products are summed on their own and added once, behind the
@@ -540,9 +644,14 @@ void k_melt_split(Job job, const split_u32x4 *__restrict__ bpack) {
             }
         }
         __syncthreads();                           // A: every row read; the stagers may overwrite
-        if (fbase < it.nf) job.template store<Op, FT, RT>(it, fbase, lane, tile, acc);
+        if (fbase < it.nf && job.template store<Op, FT, RT>(it, fbase, lane, tile, acc)) {
+            if (again1 < 0) again0 = k;
+            again1 = k;
+        }
         __syncthreads();                           // B: rows of the next item ready
     }
+    if constexpr (P == 3)
+        if (again1 >= 0) split_again<Job, FT, RT, WF>(again0, again1, wid, rows);
 }
 
 // ------------------------------------------------------------------ launch

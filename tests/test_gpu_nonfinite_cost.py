@@ -67,6 +67,58 @@ def test_cost_of_d_dbasis(torch, melt, geom, clips, seconds, bad):
     assert torch.isnan(gb).any() and dirty < COST * clean
 
 
+@pytest.mark.parametrize("bad", ["one", "all"])
+@pytest.mark.parametrize("geom,clips,seconds", [((16000, 400, 160, 80), 64, 30.0), ((22050, 1024, 256, 128), 32, 10.0),
+                                                ((16000, 400, 160, 16), 1, 1.0)])
+def test_cost_of_a_forward(torch, melt, geom, clips, seconds, bad):
+    plan, wave, off, T, _ = _setup(torch, melt, geom, clips, seconds)
+    out = torch.empty((T, plan.n_mels), device="cuda")
+    run = lambda: plan.forward(wave, off, T, out=out)
+    clean = _ms(torch, run)
+    wave[12345 if bad == "one" else slice(None)] = float("nan")
+    dirty = _ms(torch, run)
+    print(f"\nforward {geom} {bad}: {clean:.3f} -> {dirty:.3f} ms")
+    assert torch.isnan(out).any() and dirty < COST * clean
+
+
+@pytest.mark.parametrize("frames", [20, 3000])
+@pytest.mark.parametrize("N,H,M", [(400, 160, 1), (400, 160, 8), (400, 160, 13), (400, 160, 24), (400, 160, 80), (480, 161, 40),
+                                   (400, 50, 64), (1024, 256, 128), (401, 160, 100), (512, 128, 200), (400, 160, 512)])
+def test_values_of_a_forward(torch, melt, N, H, M, frames):
+    """Samples of 2^110, beyond what the planes hold, in some frames, at every count of row tiles a
+    wave: their projections are within FP32's rounding of the 64-bit ones (2 N steps of 2^-24 of the
+    terms' sum: products and sums), all others' are bit for bit as without them."""
+    plan = melt.MeltPlan(sample_rate=16000, n_fft=N, hop=H, n_mels=M, output=melt.MELT_OUT_LOG_MAGNITUDE)
+    assert "split-planes" in melt.melt_variant_name(plan.handle, 0)
+    wave, off = workloads.random_clips([frames * H + N, 2 * H + N + 1], seed=M)
+    T = melt.total_frames(off, N, H)
+    d_off = torch.from_numpy(off).cuda()
+
+    def run():
+        proj, out = torch.empty((T, 2 * M), device="cuda"), torch.empty((T, M), device="cuda")
+        plan.forward(torch.from_numpy(wave).cuda(), d_off, T, out=out, proj=proj)
+        return out.cpu().numpy(), proj.cpu().numpy()
+
+    clean_out, clean = run()
+    at = [5, 3 * H + 7, (frames // 2) * H + N - 1, off[-1] - 1]
+    wave[at] = 2.0 ** 110
+    out, got = run()
+    starts = np.concatenate([np.arange(a, b - N + 1, H) for a, b in zip(off[:-1], off[1:])])
+    hit = np.zeros(T, bool)
+    for p in at:
+        hit |= (starts <= p) & (p < starts + N)
+    # (frames that meet such a sample with zero weights alone are recomputed too)
+    near = np.zeros(T, bool)
+    for p in at:
+        near |= (starts <= p) & (p < starts + -(-N // H) * H + 32)
+    assert np.array_equal(got[~near], clean[~near]) and np.array_equal(out[~near], clean_out[~near])
+    W = plan.basis().astype(np.float64).reshape(2, M, N).transpose(1, 0, 2).reshape(2 * M, N)
+    X = wave[starts[near][:, None] + np.arange(N)].astype(np.float64)
+    want, mass = X @ W.T, np.abs(X) @ np.abs(W).T
+    assert np.all(np.abs(got[near] - want) <= 2 * N * 2.0 ** -24 * mass)
+    assert np.all(np.isfinite(out[near & ~hit]))
+
+
 @pytest.mark.parametrize("geom", [(16000, 400, 160, 40), (16000, 301, 33, 17), (16000, 512, 128, 100)])
 def test_values_of_d_dbasis(torch, melt, geom):
     """NaN and both infinities in samples and upstream gradients, over several frame ranges: d/dbasis is
