@@ -46,23 +46,36 @@ struct SplitDx {
     template <class Op, int FT, int RT>
     __device__ __forceinline__ bool store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT], f32x4 (&acc)[FT][RT]) const;
     template <int FS, int RT>
-    __device__ __forceinline__ void again(const SplitItem &, int, int, const int (&)[RT]) const {}
-};
-
-// One sample of dx in plain FP32: hop-block row b of the chunk (item-local row i), column c.
-__device__ __forceinline__ float dx_redo(const SplitDx &d, const SplitItem &it, int i, int c) {
-    const int Q = d.a.H, J = d.a.J, M = Q / 2;
-    float s = 0.0f;
-#pragma unroll 1
-    for (int j = 0; j < J; ++j) {
-        const int64_t at = it.start + (int64_t)(i + J - 1 - j) * Q;
-        if (at < it.start + it.lo || at >= it.end || j * d.hop + c >= d.g.N) continue;
-#pragma unroll 1
-        for (int q = 0; q < Q; ++q)
-            s = fmaf(d.a.wave[at + q], d.g.basis[(size_t)((q & 1) * M + (q >> 1)) * d.g.N + j * d.hop + c], s);
+    __device__ __forceinline__ void again(const SplitItem &it, int f0, int lane, const int (&tile)[RT]) const;
+    // split_plain: segment s holds G of the frame that began j = J - 1 - s hops before the row.  The one
+    // of the most hops comes first: its sums are dropped for the samples that its frame has not (a
+    // weight of zero is not the absence of a term, if G is not finite).
+    __device__ __forceinline__ int plain_segments() const { return a.J; }
+    __device__ __forceinline__ int plain_columns() const { return a.H; }
+    __device__ __forceinline__ f32x4 plain_samples(const SplitItem &it, int row, int s, int c) const {
+        const int64_t at = it.start + (int64_t)(row + s) * a.H;
+        f32x4 v{};
+        if (at < it.start + it.lo || at >= it.end) return v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < a.H) v[e] = a.wave[at + c + e];
+        return v;
     }
-    return s;
-}
+    __device__ __forceinline__ f32x4 plain_weights(int t, int row, int s, int c) const {
+        const int n = (a.J - 1 - s) * hop + 16 * t + row;
+        f32x4 v{};
+        if (16 * t + row >= hop || n >= g.N) return v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < a.H) v[e] = g.basis[(size_t)(((c + e) & 1) * (a.H / 2) + ((c + e) >> 1)) * g.N + n];
+        return v;
+    }
+    __device__ __forceinline__ void plain_first_segment(int t, int q, f32x4 &acc) const {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((a.J - 1) * hop + 16 * t + 4 * q + e >= g.N) acc[e] = 0.0f;
+    }
+};
 
 template <class Op, int FT, int RT>
 __device__ __forceinline__ bool SplitDx::store(const SplitItem &it, int fbase, int lane, const int (&tile)[RT],
@@ -94,26 +107,43 @@ __device__ __forceinline__ bool SplitDx::store(const SplitItem &it, int fbase, i
             }
         }
     }
-    if (__any(!(probe == 0.0f))) {
-#pragma unroll 1
-        for (int n = 0; n < FT * RT * 4; ++n) {
-            const int e = n & 3, f = (n >> 2) / RT, r = (n >> 2) - f * RT;
-            float y = 0.0f;
-            int t = 0;
+    return __any(!(probe == 0.0f));
+}
+
+template <int FS, int RT>
+__device__ __forceinline__ void SplitDx::again(const SplitItem &it, int f0, int lane, const int (&tile)[RT]) const {
+    const int64_t ci = it.out_row / kSplitChunk;
+    const int64_t s0 = split_scalar(a.chunks, 5 * ci) + (it.out_row - ci * kSplitChunk) * hop, s_end = split_scalar(a.chunks, 5 * ci + 1);
+    unsigned bad[FS], any = 0;                          // of a row tile's four samples
+    // calls each(address, element, bit) for the samples of tile r of frame tile f
+    auto samples = [&](int f, auto &&each) {
+        int l = lane;
+        asm volatile("" : "+v"(l));                     // addresses and conditions formed here, not kept
+        const int i = f0 + 16 * f + (l & 15);
+        const int64_t s = s0 + (int64_t)i * hop;
+        if (i >= it.nf) return;
 #pragma unroll
-            for (int ff = 0; ff < FT; ++ff)
+        for (int r = 0; r < RT; ++r)
 #pragma unroll
-                for (int rr = 0; rr < RT; ++rr)
-                    if (ff == f && rr == r) {
-                        t = tile[rr];
-                        y = e == 0 ? acc[ff][rr][0] : e == 1 ? acc[ff][rr][1] : e == 2 ? acc[ff][rr][2] : acc[ff][rr][3];
-                    }
-            const int i = i0 + 16 * f, c = 16 * t + 4 * q + e;
-            const int64_t s = s0 + (int64_t)i * hop + c;
-            if (!(y * 0.0f == 0.0f) && i < it.nf && t < g.T16 && c < hop && s < s_end) a.out[s] = dx_redo(*this, it, i, c);
-        }
+            for (int e = 0; e < 4; ++e) {
+                const int c = 16 * tile[r] + 4 * (l >> 4) + e;
+                if (c < hop && s + c < s_end) each(a.out + s + c, r, e);
+            }
+    };
+#pragma unroll
+    for (int f = 0; f < FS; ++f) {
+        bad[f] = 0;
+        samples(f, [&](const float *o, int r, int e) { bad[f] |= (*o * 0.0f == 0.0f ? 0u : 1u) << (4 * r + e); });
+        any |= bad[f];
     }
-    return false;
+    if (!__any(any != 0)) return;
+    f32x4 acc[FS][RT];
+    split_plain(*this, it, f0, lane, tile, acc);
+#pragma unroll
+    for (int f = 0; f < FS; ++f)
+        samples(f, [&](float *o, int r, int e) {
+            if (bad[f] >> (4 * r + e) & 1) *o = acc[f][r][e];
+        });
 }
 
 // k-groups of G rows: J segments of 2M columns

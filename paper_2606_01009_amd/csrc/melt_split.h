@@ -227,12 +227,14 @@ __device__ __forceinline__ void split_plain(const Job &job, const SplitItem &it,
     for (int s = 0; s < job.plain_segments(); ++s) {
 #pragma unroll 1
         for (int c0 = 0; c0 < cols; c0 += 16) {
-            const int c = c0 + 4 * (lane >> 4);
+            int l = lane;
+            asm volatile("" : "+v"(l));                 // addresses and conditions formed here, not kept
+            const int c = c0 + 4 * (l >> 4);
             f32x4 x[FS], w[RT];
 #pragma unroll
-            for (int f = 0; f < FS; ++f) x[f] = job.plain_samples(it, min(f0 + 16 * f + (lane & 15), it.nf - 1), s, c);
+            for (int f = 0; f < FS; ++f) x[f] = job.plain_samples(it, min(f0 + 16 * f + (l & 15), it.nf - 1), s, c);
 #pragma unroll
-            for (int r = 0; r < RT; ++r) w[r] = job.plain_weights(tile[r], lane & 15, s, c);
+            for (int r = 0; r < RT; ++r) w[r] = job.plain_weights(tile[r], l & 15, s, c);
 #pragma unroll
             for (int r = 0; r < RT; ++r)
 #pragma unroll

@@ -81,6 +81,22 @@ def test_cost_of_a_forward(torch, melt, geom, clips, seconds, bad):
     assert torch.isnan(out).any() and dirty < COST * clean
 
 
+@pytest.mark.parametrize("bad", ["one", "all"])
+@pytest.mark.parametrize("geom,clips,seconds", [((16000, 400, 160, 80), 16, 10.0), ((22050, 1024, 256, 128), 32, 10.0)])
+def test_cost_of_d_dwave(torch, melt, geom, clips, seconds, bad):
+    plan, wave, off, T, gen = _setup(torch, melt, geom, clips, seconds)
+    proj = torch.empty((T, 2 * plan.n_mels), device="cuda")
+    plan.forward(wave, off, T, proj=proj)
+    g = torch.randn((T, plan.n_mels), generator=gen, device="cuda")
+    gw = torch.empty_like(wave)
+    run = lambda: melt.melt_backward(plan.handle, wave, off, T, g, proj, gw, None)
+    clean = _ms(torch, run)
+    g[7 if bad == "one" else slice(None), 3 if bad == "one" else slice(None)] = float("nan")
+    dirty = _ms(torch, run)
+    print(f"\nd/dwave {geom} {bad}: {clean:.3f} -> {dirty:.3f} ms")
+    assert torch.isnan(gw).any() and dirty < COST * clean
+
+
 @pytest.mark.parametrize("frames", [20, 3000])
 @pytest.mark.parametrize("N,H,M", [(400, 160, 1), (400, 160, 8), (400, 160, 13), (400, 160, 24), (400, 160, 80), (480, 161, 40),
                                    (400, 50, 64), (1024, 256, 128), (401, 160, 100), (512, 128, 200), (400, 160, 512)])
@@ -117,6 +133,41 @@ def test_values_of_a_forward(torch, melt, N, H, M, frames):
     want, mass = X @ W.T, np.abs(X) @ np.abs(W).T
     assert np.all(np.abs(got[near] - want) <= 2 * N * 2.0 ** -24 * mass)
     assert np.all(np.isfinite(out[near & ~hit]))
+
+
+@pytest.mark.parametrize("frames", [20, 3000])
+@pytest.mark.parametrize("N,H,M", [(400, 160, 40), (401, 16, 17), (300, 33, 9), (512, 128, 100), (250, 250, 24), (400, 160, 5)])
+def test_values_of_d_dwave(torch, melt, N, H, M, frames):
+    """Upstream gradients that make G 2^110, beyond what the planes hold, in some frames: the samples of
+    those frames are within FP32's rounding of the 64-bit gradients, all others bit for bit as without
+    them but for the samples that only share such a frame's last hop (recomputed too)."""
+    plan = melt.MeltPlan(sample_rate=16000, n_fft=N, hop=H, n_mels=M, output=melt.MELT_OUT_POWER)
+    wave, off = workloads.random_clips([frames * H + N, N - 1, 2 * H + N + 1], seed=M)
+    T = melt.total_frames(off, N, H)
+    g = np.random.default_rng(1).standard_normal((T, M)).astype(np.float32)
+    proj = np.random.default_rng(2).uniform(0.5, 1, (T, 2 * M)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(a).cuda()
+
+    def grad():
+        return plan.backward(dev(wave), dev(off), T, dev(g), proj=dev(proj), want_basis=False)[0].cpu().numpy()
+
+    clean = grad()
+    at = [0, 3, frames // 2, T - 1]
+    g[at, [0, M - 1, M // 2, 1]] = 2.0 ** 110
+    got = grad()
+    starts = np.concatenate([np.arange(a, b - N + 1, H) for a, b in zip(off[:-1], off[1:])])
+    W = plan.basis().astype(np.float64).reshape(2, M, N).transpose(1, 0, 2).reshape(2 * M, N)
+    G = (2 * proj * np.repeat(g, 2, axis=1)).astype(np.float64)
+    near, want, mass = np.zeros(wave.size, bool), np.zeros(wave.size), np.zeros(wave.size)
+    for t in at:
+        near[starts[t]:min(starts[t] + -(-N // H) * H, off[np.searchsorted(off, starts[t], "right")])] = True
+    reach = np.flatnonzero([near[s:s + N].any() for s in starts])
+    for t in reach:
+        want[starts[t]:starts[t] + N] += G[t] @ W
+        mass[starts[t]:starts[t] + N] += np.abs(G[t]) @ np.abs(W)
+    assert np.array_equal(got[~near], clean[~near])
+    terms = 2 * M * -(-N // H)
+    assert np.all(np.abs(got[near] - want[near]) <= 2 * terms * 2.0 ** -24 * mass[near])
 
 
 @pytest.mark.parametrize("geom", [(16000, 400, 160, 40), (16000, 301, 33, 17), (16000, 512, 128, 100)])
