@@ -129,7 +129,7 @@ __global__ __launch_bounds__(512) void k_melt_f8_rs(FwdArgs a, const i32x8 *__re
 // as 0.  Outputs are stored straight from the
 // accumulators.  Waves map to row tiles and frame tiles as in the 16-bit kernel
 // (wave_layout: one or two leftover row tiles are shared by four waves, by frame tiles).
-template <int NG>
+template <int NG, bool OWN>
 __global__ __launch_bounds__(512) void k_melt_f8_as(FwdArgs a, const i32x8 *__restrict__ bq,
                                                     const float *__restrict__ rinv_g, int N, int bf, int scr_off,
                                                     int full, int psplit) {
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(512) void k_melt_f8_as(FwdArgs a, const i32x8 *__re
     float *scratch = lds_f8 + scr_off;                                           // FP32 span
     // before the basis tile is in registers
     __shared__ ChunkRing ring;
-    const bool own = a.clips.off != nullptr;
+    constexpr bool own = OWN;
     const int nch = own ? ring_start(a, ring, blockIdx.x, gridDim.x) : *a.n_chunks;
     i32x8 A[NG];
 #pragma unroll
@@ -677,7 +677,7 @@ __device__ __forceinline__ Chunk slot_get(const Chunk *slots, int i) {
     return e;
 }
 
-template <int NG>
+template <int NG, bool OWN>
 __global__ __launch_bounds__(768) void k_melt_f8b_pc(FwdArgs a, const i32x8 *__restrict__ bq,
                                                     const float *__restrict__ rinv_g, F8BlockTable bt, int S8,
                                                     int buf_bytes, int code_off, int n_codes, int scr_off,
@@ -700,7 +700,7 @@ __global__ __launch_bounds__(768) void k_melt_f8b_pc(FwdArgs a, const i32x8 *__r
     const int cstep = gridDim.x / rgroups;
     const int c0 = blockIdx.x / rgroups;
     // descriptors: the four slots, or the list of a kernel that schedules itself
-    const bool own = a.clips.off != nullptr;
+    constexpr bool own = OWN;
     Chunk *slots = own ? reinterpret_cast<Chunk *>(reinterpret_cast<char *>(lds_pc) + a.list_off) : dslot;
     const int smask = own ? kListEntries - 1 : 3;
     const int nch = own ? list_start(a, slots, c0 + (int64_t)(threadIdx.x & 63) * cstep) : *a.n_chunks;
@@ -994,10 +994,11 @@ static melt_status launch_f8_pc_ng(Plan &p, const FwdArgs &a, size_t lds, int gr
 
 template <int NG>
 static melt_status launch_f8_as(Plan &p, const FwdArgs &a, size_t lds, int grid, int bf, hipStream_t s) {
-    allow_lds(k_melt_f8_as<NG>, kRingBytes);
+    const auto kernel = a.clips.off ? k_melt_f8_as<NG, true> : k_melt_f8_as<NG, false>;
+    allow_lds(kernel, kRingBytes);
     const WaveLayout w = wave_layout(p);
-    k_melt_f8_as<NG><<<grid, 64 * w.waves, lds, s>>>(a, (const i32x8 *)p.d_pack_f8, p.d_rowscale, p.N, bf,
-                                                     (int)(f8_as_scratch_offset(p, bf) / 4), w.full, w.psplit);
+    kernel<<<grid, 64 * w.waves, lds, s>>>(a, (const i32x8 *)p.d_pack_f8, p.d_rowscale, p.N, bf,
+                                           (int)(f8_as_scratch_offset(p, bf) / 4), w.full, w.psplit);
     return hip_check(hipGetLastError(), "melt f8 lds-dma launch");
 }
 
@@ -1043,10 +1044,11 @@ size_t f8b_pc_static_bytes() { return 4 * sizeof(Chunk) + 8 * 32 * sizeof(float)
 template <int NG>
 static melt_status launch_f8b_pc_ng(Plan &p, const FwdArgs &a, const F8BlockTable &bt, size_t lds, int grid, int bf,
                                     int rg, hipStream_t s) {
-    allow_lds(k_melt_f8b_pc<NG>, (int)f8b_pc_static_bytes());
-    k_melt_f8b_pc<NG><<<grid, 768, lds, s>>>(a, (const i32x8 *)p.d_pack_f8, p.d_rowscale, bt, f8b_stride(p),
-                                             (int)f8b_buf_bytes(p, bf), (int)f8b_codes_offset(p, bf),
-                                             (int)f8b_codes(p, bf), (int)(2 * f8b_buf_bytes(p, bf) / 4), rg);
+    const auto kernel = a.clips.off ? k_melt_f8b_pc<NG, true> : k_melt_f8b_pc<NG, false>;
+    allow_lds(kernel, (int)f8b_pc_static_bytes());
+    kernel<<<grid, 768, lds, s>>>(a, (const i32x8 *)p.d_pack_f8, p.d_rowscale, bt, f8b_stride(p), (int)f8b_buf_bytes(p, bf),
+                                  (int)f8b_codes_offset(p, bf), (int)f8b_codes(p, bf),
+                                  (int)(2 * f8b_buf_bytes(p, bf) / 4), rg);
     return hip_check(hipGetLastError(), "melt f8 block-scaled producer/consumer launch");
 }
 

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(512) void k_melt_h16_rs(FwdArgs a, const uint4 *__r
 // are shared by four waves, psplit per tile, each taking every psplit-th frame tile.  With
 // 80 Mel bins (5 row tiles) that is 8 waves, 4 for tile 4, so every SIMD carries 1.25 row
 // tiles of work instead of one SIMD carrying two.
-template <class Conv, int NS, bool X3, bool IS_F16>
+template <class Conv, int NS, bool X3, bool IS_F16, bool OWN>
 __global__ __launch_bounds__(512) void k_melt_h16_as(FwdArgs a, const uint4 *__restrict__ bhi,
                                                      const uint4 *__restrict__ blo, GroupTableBig gt, int bf,
                                                      int scr_off, int scr_len, int nbuf, int rgroups) {
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(512) void k_melt_h16_as(FwdArgs a, const uint4 *__r
     __shared__ ChunkRing ring;
     const int cstep = gridDim.x / rgroups;         // the grid is a multiple of rgroups
     int c = blockIdx.x / rgroups;
-    const bool own = a.clips.off != nullptr;
+    constexpr bool own = OWN;
     const int nch = own ? ring_start(a, ring, c, cstep) : *a.n_chunks;
     uint4 A[NS];
     uint4 Al[X3 ? NS : 1];
@@ -577,7 +577,7 @@ __global__ __launch_bounds__(512) void k_melt_h16_pp(FwdArgs a, const uint4 *__r
 // producer loads descriptor k + 3 in iteration k and stores it before the barrier (slot
 // (k + 3) mod 4 was last read in iteration k - 1).  The first chunk is copied and converted by
 // all twelve waves.
-template <class Conv, int NS, bool X3, bool IS_F16>
+template <class Conv, int NS, bool X3, bool IS_F16, bool OWN>
 __global__ __launch_bounds__(X3 ? 512 : 768) void k_melt_h16_pc(FwdArgs a, const uint4 *__restrict__ bhi,
                                                                const uint4 *__restrict__ blo, GroupTableBig gt,
                                                                int bf, int rows_len, int lo_off, int scr_off,
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(X3 ? 512 : 768) void k_melt_h16_pc(FwdArgs a, const
     const int c0 = blockIdx.x / rgroups;
     // a kernel that schedules itself has the descriptors of all its chunks in a list of its own,
     // and the slots below are the list's
-    const bool own = a.clips.off != nullptr;
+    constexpr bool own = OWN;
     Chunk *slots = own ? reinterpret_cast<Chunk *>(reinterpret_cast<char *>(lds_hpc) + a.list_off) : dslot;
     const int smask = own ? kListEntries - 1 : 3;
     const int nch = own ? list_start(a, slots, c0 + (int64_t)(threadIdx.x & 63) * cstep) : *a.n_chunks;
@@ -856,10 +856,11 @@ struct SpanBufs {
 template <class Conv, int NS, bool X3, bool F16>
 static melt_status launch_as_ns(Plan &p, const FwdArgs &a, const GroupTableBig &gt, size_t lds, int grid, int bf,
                                 SpanBufs sb, hipStream_t s) {
-    allow_lds(k_melt_h16_as<Conv, NS, X3, F16>, kRingBytes);
+    const auto kernel = a.clips.off ? k_melt_h16_as<Conv, NS, X3, F16, true> : k_melt_h16_as<Conv, NS, X3, F16, false>;
+    allow_lds(kernel, kRingBytes);
     const WaveLayout w = wave_layout(p);
     const int rg = row_groups(p);
-    k_melt_h16_as<Conv, NS, X3, F16><<<grid, 64 * w.waves, lds, s>>>(
+    kernel<<<grid, 64 * w.waves, lds, s>>>(
         a, (const uint4 *)p.d_pack_h16, (const uint4 *)p.d_pack_lo, gt, bf, sb.off, sb.len, sb.n, rg);
     return hip_check(hipGetLastError(), "melt h16 lds-dma launch");
 }
@@ -953,10 +954,11 @@ bool pc_list_fits(const Plan &p, bool f8b, int bf) {
 template <class Conv, int NS, bool X3, bool F16>
 static melt_status launch_pc_ns(Plan &p, const FwdArgs &a, const GroupTableBig &gt, size_t lds, int grid, int bf,
                                 int rg, hipStream_t s) {
-    allow_lds(k_melt_h16_pc<Conv, NS, X3, F16>, (int)(4 * sizeof(Chunk)));
+    const auto kernel = a.clips.off ? k_melt_h16_pc<Conv, NS, X3, F16, true> : k_melt_h16_pc<Conv, NS, X3, F16, false>;
+    allow_lds(kernel, (int)(4 * sizeof(Chunk)));
     const int part = (int)(pc_rows_bytes(p, bf) / 2);            // elements of one row image
     const int rows_len = X3 ? 2 * part : part;
-    k_melt_h16_pc<Conv, NS, X3, F16><<<grid, X3 ? 512 : 768, lds, s>>>(
+    kernel<<<grid, X3 ? 512 : 768, lds, s>>>(
         a, (const uint4 *)p.d_pack_h16, (const uint4 *)p.d_pack_lo, gt, bf, rows_len, X3 ? part : 0,
         (int)(2 * rows_len * 2 / 4), rg);
     return hip_check(hipGetLastError(), "melt h16 producer/consumer launch");
