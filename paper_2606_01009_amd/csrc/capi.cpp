@@ -270,7 +270,8 @@ melt_status melt_batch_prepare(melt_plan plan, const int64_t *d_clip_offsets, in
         p->prepared_frames[0] = p->prepared_frames[1] = 0;
         return MELT_OK;
     }
-    st = launch_schedule(*p, 0, d_clip_offsets, n_clips, melt_chunk_frames(*p), n_frames, s);
+    const int v = call_variant(*p, n_clips, n_frames);
+    st = launch_schedule(*p, 0, d_clip_offsets, n_clips, melt_chunk_frames(*p, v), n_frames, s, v);
     if (st != MELT_OK) return st;
     return launch_schedule(*p, 1, d_clip_offsets, n_clips, stft_chunk_frames(*p), n_frames, s);
 }

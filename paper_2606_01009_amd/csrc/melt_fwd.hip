@@ -674,17 +674,34 @@ static melt_status launch_melt_clips(Plan &p, int variant, const ClipTable &clip
     return launch_variant(p, variant, t);
 }
 
-// The variant of one call.  The FP8 kernels with per-frame scales give the same bits, so unless a
-// variant is pinned a call may take either: where 64-frame chunks fill at most one round of the
-// CUs, the row-split kernel on those spreads wider and starts without the basis in LDS (16 x 4 s:
-// 11.9 us against 14.1 us frame-split at 80 Mel bins, 12.3 against 16.5 at 128); below 4 row
-// tiles the frame-split one is the faster there too (10.5 against 11.9 us at 24 Mel bins).
+// The variant of one call, prepared batch or streaming state.  The FP8 kernels with per-frame scales
+// give the same bits, so unless a variant is pinned a call may take either.  The frame-split one is the
+// faster per frame, the row-split one per chunk (a chunk costs the first about the same however few
+// its frames) and to start.  With clips of one length assumed, n_frames / n_clips frames each
+// (N 400 and 80 Mel bins unless stated, us, frame-split against row-split):
+//   from 4 row tiles, 64-frame chunks of at most one round of the CUs: row-split on those (16 x 4 s
+//     14.1 : 11.9, one 1 s clip 11.8 : 9.7; below 4 row tiles frame-split, 24 Mel bins: 10.5 : 11.9)
+//   chunks of 128 less than half full: row-split (512 x 0.3 s 22.3 : 17.5, 128 Mel bins 26.1 : 18.6;
+//     three quarters full, 512 x 1 s, 28.4 : 28.8); below 4 row tiles less than a tenth, 3 row tiles
+//     three tenths (512 x 0.1 s, 16 Mel bins, 15.9 : 12.5)
+//   more than 64 clips and at most one round of 128-frame chunks, each a clip or (more than 6 row tiles,
+//     the basis streamed) not: row-split (256 x 1 s 19.7 : 19.0, 128 Mel bins 22.3 : 20.5)
 int call_variant(const Plan &p, int n_clips, int64_t n_frames) {
     const int v = p.tune_variant;
-    if (p.tune_pinned || variant_at(p, v).kind != V_F8_FS || p.row_tiles < 4 || n_frames / 64 + n_clips > p.cu_count) return v;
+    if (p.tune_pinned || variant_at(p, v).kind != V_F8_FS || n_clips < 1 || n_frames < 1) return v;
+    const int64_t each = (n_frames + n_clips - 1) / n_clips, c64 = n_clips * ((each + 63) / 64), c128 = n_clips * ((each + 127) / 128);
+    bool small, large = false;                     // row-split on 64-frame chunks, on its largest
+    if (p.row_tiles >= 4) {
+        small = c64 <= p.cu_count;
+        large = 2 * n_frames < 128 * c128 ||
+                (n_clips > 64 && c128 <= p.cu_count && (each <= 128 || p.row_tiles > 6));
+    } else {
+        small = 10 * n_frames < (p.row_tiles == 3 ? 3 : 1) * 128 * c128;
+    }
+    int best = v;
     for (int i = 0; i < p.n_variants; ++i)
-        if (p.var_kind[i] == V_F8_AS && p.var_bf[i] == 64) return i;
-    return v;
+        if (p.var_kind[i] == V_F8_AS && (small ? p.var_bf[i] == 64 : large && best == v)) best = i;
+    return best;
 }
 
 // The forward over a batch, which is the plan's prepared one afterwards: table 0 is written by the
@@ -767,23 +784,25 @@ melt_status forward_noalloc(Plan &p, const float *d_wave, const int64_t *d_off, 
         base = g_scratch_ptr[p.device];
     }
     if (!base) return set_error(MELT_E_HIP, "melt_forward_noalloc: no scratch address for this device");
-    const int v = p.tune_variant;
-    const int bf = melt_chunk_frames(p, v);
+    // (the limit is the plan's variant's, which the call falls back to where another needs more)
+    const int bf = melt_chunk_frames(p, p.tune_variant);
     // every clip ends in at most one partial chunk
-    const int64_t need = n_frames / bf + n_clips + 1;
+    int64_t need = n_frames / bf + n_clips + 1;
     if (need > kScratchChunks)
         return set_error(MELT_E_SHAPE, "melt_forward_noalloc: n_frames / " + std::to_string(bf) + " + n_clips + 1 = " +
                                            std::to_string(need) + " chunk entries exceed the 32760 of the scratch");
     int *n_tab = static_cast<int *>(base);
     Chunk *tab = reinterpret_cast<Chunk *>(static_cast<unsigned char *>(base) + kScratchTable);
     // the schedule kernels write the count unconditionally, so nothing in the scratch needs clearing
-    const int vc = call_variant(p, n_clips, n_frames);
-    if (self_scheduled(p, vc, n_clips, n_frames)) {
-        const int bc = melt_chunk_frames(p, vc);
-        const ClipTable clips{d_off, n_clips, p.N, bc, (int)(n_frames / bc + n_clips), nullptr, nullptr};
-        return launch_melt_clips(p, vc, clips, n_frames, d_wave, d_out, nullptr, s);
+    int v = call_variant(p, n_clips, n_frames);
+    if (n_frames / melt_chunk_frames(p, v) + n_clips + 1 > kScratchChunks) v = p.tune_variant;
+    const int bc = melt_chunk_frames(p, v);
+    need = n_frames / bc + n_clips + 1;
+    if (self_scheduled(p, v, n_clips, n_frames)) {
+        const ClipTable clips{d_off, n_clips, p.N, bc, (int)(need - 1), nullptr, nullptr};
+        return launch_melt_clips(p, v, clips, n_frames, d_wave, d_out, nullptr, s);
     }
-    const melt_status st = enqueue_schedule(p, d_off, n_clips, bf, need, tab, kScratchChunks, n_tab, s);
+    const melt_status st = enqueue_schedule(p, d_off, n_clips, bc, need, tab, kScratchChunks, n_tab, s);
     if (st != MELT_OK) return st;
     return launch_melt_table(p, v, tab, n_tab, need - 1, n_frames, d_wave, d_out, nullptr, s);
 }

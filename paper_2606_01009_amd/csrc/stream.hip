@@ -283,10 +283,10 @@ melt_status melt_stream_create(melt_plan plan, int32_t n_streams, int32_t max_ch
     S->n_streams = n_streams;
     S->max_chunk = max_chunk_len;
     S->max_frames = (max_chunk_len - 1) / p->H + 1;
-    S->variant = p->tune_variant;     // kept for the life of the state
-    S->bf = melt_chunk_frames(*p, S->variant);
     const int J = (p->N + p->H - 1) / p->H;
     S->max_pack = (int64_t)n_streams * (S->max_frames + J - 1);
+    S->variant = call_variant(*p, 1, S->max_pack);     // kept for the life of the state
+    S->bf = melt_chunk_frames(*p, S->variant);
     S->max_tab = (int)((S->max_pack + S->bf - 1) / S->bf);
     // packed buffer: the rows of every stream, plus the span a chunk's staging may read past
     // the last frame (J - 1 rows) and a vector of slack
