@@ -446,21 +446,22 @@ melt_status melt_autotune(melt_plan plan, int64_t total_frames, char *desc, int3
             }
         }
     }
-    p->tune_variant = best_v;
-    p->tune_pinned = true;
-    p->tune_grid = best_g;
+    // a run that failed leaves the plan's choice as it was, also whether it was pinned
+    const bool tuned = ok && st == MELT_OK;
+    p->tune_variant = tuned ? best_v : save_v;
+    p->tune_grid = tuned ? best_g : save_g;
+    if (tuned) p->tune_pinned = true;
     p->prepared_frames[0] = -1;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipFree(d_wave);
     (void)hipFree(d_out);
     (void)hipFree(d_off);
-    if (!ok) return set_error(MELT_E_NO_MEMORY, "autotune buffers");
-    if (st != MELT_OK) {
-        p->tune_variant = save_v;
-        p->tune_grid = save_g;
-        return st;
+    if (!ok) {
+        (void)hipGetLastError();                   // the failed allocation's, which the next launch would report
+        return set_error(MELT_E_NO_MEMORY, "autotune buffers");
     }
+    if (st != MELT_OK) return st;
     char buf[256];
     std::snprintf(buf, sizeof(buf), "%s grid=%dx%d CUs %.1f us for %lld frames", best_name.c_str(), best_g,
                   p->cu_count, best_us, (long long)T);

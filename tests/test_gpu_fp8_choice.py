@@ -73,3 +73,17 @@ def test_pushes(torch, melt, M, streams, chunk, split):
     x = torch.randn(streams, chunk, device="cuda")
     names = kernels_of(torch, melt, lambda: melt.melt_stream_push(st.handle, x, st.out, st.count))
     assert ("k_melt_f8_fs" if split else "k_melt_f8_as") in _fp8(names)
+
+
+def test_a_failed_autotune_pins_nothing(torch, melt):
+    """A batch that no GPU holds: the run is refused, the plan chooses by call as before, and the next
+    launch does not report the failed allocation."""
+    plan = _plan(melt, 80)
+    wave, off, T = _batch(torch, 1, 98)
+    out = torch.empty((T, 80), device="cuda")
+    with pytest.raises(melt.MeltError) as e:
+        melt.melt_autotune(plan.handle, 4 * 10 ** 9)
+    assert e.value.status == melt.MELT_E_NO_MEMORY
+    assert "k_melt_f8_as" in _fp8(kernels_of(torch, melt, lambda: plan.forward(wave, off, T, out=out)))
+    plan.forward(wave, off, T, out=out)
+    torch.cuda.synchronize()
