@@ -393,10 +393,12 @@ melt_status launch_melt_backward(Plan &p, const float *d_wave, const int64_t *d_
         st = hip_check(hipGetLastError(), "bwd tables");
         if (st != MELT_OK) return st;
     } else {
-        st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p), n_frames, s);
+        // (the forward over more than 64 clips has built the chunk table)
+        const int v = call_variant(p, n_clips, n_frames);
+        if (d_proj) st = launch_schedule(p, 0, d_off, n_clips, melt_chunk_frames(p, v), n_frames, s, v);
         if (st != MELT_OK) return st;
         k_fill_i64<<<256, 256, 0, s>>>(fstart, n_frames, -1);
-        const int64_t nchunk_est = n_frames / melt_chunk_frames(p) + n_clips + 1;
+        const int64_t nchunk_est = n_frames / p.prepared_bf[0] + n_clips + 1;
         const int grid_prep = (int)std::min<int64_t>(nchunk_est, (int64_t)p.cu_count * 4);
         k_bwd_fstart<<<grid_prep, 256, 0, s>>>(p.d_chunks[0], p.d_nchunks, n_frames, H, fstart);
         if (d_gwave)
