@@ -128,6 +128,7 @@ melt_status melt_plan_create(const melt_config *cfg, int device, melt_plan *out)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
         p->cu_count = cus;
     st = plan_build_host(*p);
+    if (st == MELT_OK) init_variants(*p);
     const size_t nb = size_t(2) * p->M * p->N;
     const size_t RT = p->row_tiles;
     if (st == MELT_OK) st = alloc((void **)&p->d_basis32, nb * sizeof(float));
@@ -135,7 +136,7 @@ melt_status melt_plan_create(const melt_config *cfg, int device, melt_plan *out)
     if (st == MELT_OK) st = alloc(&p->d_pack_h16, RT * p->geo16.n_groups * 64 * 8 * 2);
     if (st == MELT_OK) st = alloc(&p->d_pack_lo, RT * p->geo16.n_groups * 64 * 8 * 2);
     if (st == MELT_OK) st = alloc(&p->d_pack_f8, RT * ((p->N + 63) / 64) * 64 * 32);
-    if (st == MELT_OK && split_planes(*p))
+    if (st == MELT_OK && split_used(*p))
         st = alloc(&p->d_pack_split, size_t((p->M + 7) / 8) * p->geoS.n_groups * split_planes(*p) * 1024);
     if (st == MELT_OK) st = alloc((void **)&p->d_rowscale, RT * 32 * sizeof(float));
     if (st == MELT_OK) st = alloc((void **)&p->d_nchunks, 2 * sizeof(int));
@@ -157,7 +158,6 @@ melt_status melt_plan_create(const melt_config *cfg, int device, melt_plan *out)
                               prec == MELT_PREC_FP8_E4M3_BLOCK32))
             st = pack_dct_x3(*p);
     }
-    if (st == MELT_OK) init_variants(*p);
     if (st == MELT_OK) st = pack_tables_upload(*p);
     if (st == MELT_OK) st = pack_basis(*p, p->d_basis32, nullptr);
     if (st == MELT_OK) st = hip_check(hipStreamSynchronize(nullptr), "pack basis");

@@ -161,6 +161,7 @@ int call_variant(const Plan &p, int n_clips, int64_t n_frames);
 melt_status launch_stft_forward(Plan &p, const int64_t *d_off, int n_clips, int64_t n_frames, const float *d_wave,
                                 float *d_out, hipStream_t s);
 void init_variants(Plan &p);             // melt_fwd.hip: fills the plan's variant table
+bool split_used(const Plan &p);          // the split-plane forward is among them: the plan packs its planes
 size_t pc_x3_lds_bytes(const Plan &p, int bf);   // melt_h16.hip: split-precision producer/consumer LDS
 int forward_variants(const Plan &p);
 void apply_tune_cache(Plan &p);          // stream.hip: apply a MELT_AUTOTUNE_CACHE entry
