@@ -397,8 +397,8 @@ melt_status launch_frame_offsets(const int64_t *d_off, int n_clips, int N, int H
 
 // Kernel variants of a plan, in the order the autotuner times them (p.tune_variant selects;
 // the first one is the default):
-//   FP32       operand planes (melt_split.h), frame-split on FP32 MFMA with staging waves, the same
-//              with register prefetch
+//   FP32       operand planes (melt_split.h; last for frames of few samples), frame-split on FP32 MFMA
+//              with staging waves, the same with register prefetch
 //   BF16/FP16  the 12-wave producer/consumer kernel (96- or 64-frame chunks) where its
 //              register tiles and LDS fit; row pairs (two basis tiles per wave) where they fit;
 //              row-split with direct-to-LDS staging (one span buffer: 128- then 64-frame
@@ -469,6 +469,20 @@ static bool split_fits(const Plan &p) {
            split_shape(p.geoS, split_planes(p), (p.M + 7) / 8, p.cu_count, 1 << 20, (int64_t)kSplitChunk << 20).parts > 0;
 }
 
+// Frames of few samples and few Mel bins: the staging and hand-over of an item outweigh its products, and
+// batches are the faster on the kernels that were there before (FP32 MFMA with staging waves, 16-bit
+// frame-split).  64 clips of 30 s, us, planes against those: FP32 N 64, hop 32, 8 Mel bins 125 : 108,
+// 24 Mel bins 119 : 153; N 128, hop 64, 8 Mel bins 68 : 72.  BF16X3, 16 Mel bins, N 40, hop 20
+// 183 : 102, N 64 in one hop 57 : 57.  FP16X3, whose conversion costs the others more, only where the
+// k-groups pad a frame by more than half (N 40, hop 20, 16 Mel bins 196 : 157).  One 1 s clip takes
+// 9.1 us there where planes take 7.3.
+static bool split_tiny(const Plan &p) {
+    if (p.cfg.precision == MELT_PREC_FP16X3) return p.M <= 16 && 2 * p.geoS.n_groups * 32 > 3 * p.N;
+    if (p.cfg.precision == MELT_PREC_BF16X3)
+        return (p.M <= 16 && p.N < 128 && (p.N < 64 || p.H < p.N)) || (p.M <= 40 && p.N < 64);
+    return p.M <= 16 && p.N < 128;
+}
+
 bool split_self_scheduled(const Plan &p, int64_t est_chunks, int64_t n_frames) {
     const int P = split_planes(p);
     const SplitShape h = split_shape(p.geoS, P, (p.M + 7) / 8, p.cu_count, est_chunks, n_frames);
@@ -482,9 +496,10 @@ static std::vector<Variant> variant_list(const Plan &p) {
     switch (p.cfg.precision) {
     case MELT_PREC_FP32:
         // (the geometries the FP32-MFMA kernels refuse stay refused)
-        if (f32_fits(p) && split_fits(p)) v.push_back({V_SPLIT, kSplitChunk});
+        if (f32_fits(p) && split_fits(p) && !split_tiny(p)) v.push_back({V_SPLIT, kSplitChunk});
         v.push_back({V_F32_WS, kBF32});
         v.push_back({V_F32_FS, kBF32});
+        if (f32_fits(p) && split_fits(p) && split_tiny(p)) v.push_back({V_SPLIT, kSplitChunk});
         break;
     case MELT_PREC_FP8_E4M3: {
         // up to 8 row tiles: the largest all-wave chunk that fits LDS (one workgroup per CU),
@@ -538,7 +553,8 @@ static std::vector<Variant> variant_list(const Plan &p) {
         if (pc_x3_first) v.push_back({V_H16_PC, 64});
         // frame lengths without a register tile for it (N = 512, 480, ...): operand planes first
         // (512 ragged clips, N 512, M 128: 942 -> 676 us BF16X3; one 1 s clip: 23.2 -> 10.1 us)
-        if (x3 && !pc_fits(p) && h16_fs_fits(p) && split_fits(p)) v.push_back({V_SPLIT, kSplitChunk});
+        const bool split = x3 && !pc_fits(p) && h16_fs_fits(p) && split_fits(p);
+        if (split && !split_tiny(p)) v.push_back({V_SPLIT, kSplitChunk});
         if (!x3 && ap_fits(p) && as_lds_bytes(p, 128) + kRingBytes <= (size_t)kMaxLds) v.push_back({V_H16_AP, 128});
         if (as_fits(p)) {
             // one span buffer (128 then 64 frames per chunk; 96 then 64 for BF16X3), then two
@@ -577,6 +593,7 @@ static std::vector<Variant> variant_list(const Plan &p) {
         // frame-split: the fallback for every 16-bit precision (the split ones only where no
         // register-tile kernel applies)
         if (!x3 || v.empty()) v.push_back({V_H16_FS, kBF32});
+        if (split && split_tiny(p)) v.push_back({V_SPLIT, kSplitChunk});
     }
     }
     return v;
