@@ -435,7 +435,6 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i][7] += sum[1][i];
     }
-    if (cur) __syncthreads();                          // the staging waves take steps in pairs
     // lane holds column n, rows q = tile base + 4 (lane / 16) + r (interleaved q)
     const int qw = q0 + 64 * wq, nw = n0 + 128 * wn;
     const float unscale = split_unscale(kPlaneUnscale);
@@ -459,6 +458,7 @@ void k_bwd_dw_split(const float *__restrict__ G, const int64_t *__restrict__ fst
         probe = fmaf(v, 0.0f, probe);
         *at = v;
     });
+    if (cur) __syncthreads();                          // the staging waves take steps in pairs
     if (__any(!(probe == 0.0f))) {
         // the planes of an infinity are not a product with it
         dw_plain(G, fstart, wave, part, t0, t1, Q, N, qw, nw, acc);
