@@ -424,17 +424,25 @@ struct Variant {
 };
 
 // Shape of the split-plane kernel for a batch: the one with the fewest cycles in the model
-//   rounds over the CUs x (k-groups x RT x max(MFMA, L1) + fixed)
-// where a k-group of a tile costs FT NP MFMAs of 16 cycles on its SIMD or, if that is more, P KB
-// for each of the four multiply waves through the CU's 64-byte L1 port; the fixed part is an
-// item's barriers, hand-over and first fragment reads.  128-frame items are the cheapest per
-// frame; 64-frame ones (four row groups) serve rows too long for LDS at 128, and 32-frame ones
-// spread a call of few frames over the chip.
+//   rounds over the CUs x max(k-groups x RT x max(MFMA, L1) + fixed, staging)
+// where a k-group of a tile costs FT NP MFMAs of 16 cycles on its SIMD or, if that is more, P KB for
+// each of the four multiply waves through the CU's 64-byte L1 port.  Clips of one length are assumed.
+// 128-frame items are the cheapest per frame; 64-frame ones (four row groups) serve rows too long for
+// LDS at 128 and fill a last round better, and 32-frame ones spread a call of few frames over the chip.
+// The other terms are fitted to whole calls of 28 front ends (N 48 to 1200, 8 to 512 Mel bins, FP32 and
+// BF16X3) in 1 to 64 clips of 1 to 30 s, every shape timed: fixed, an item's barriers, hand-over and
+// first fragment reads, 320 a tile of accumulators, and 3700 where the fragment ring has to be filled
+// again (ring slots that are no divisor of the k-groups); staging, 9500 and 4.2 a vector.  The choice
+// is then within 0.3 % of the fastest shape on average, 17 % at worst; with one fixed term of 4500 and
+// a chunk too many assumed for each clip it was 11 % and up to twice as long (FP32, N 400, 80 Mel bins,
+// 32 x 10 s: 54.8 us with five row parts, 27.3 with one).
 SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t est_chunks, int64_t n_frames) {
     const int NP = P == 3 ? 6 : 3;
     static const struct {
         int wf, ft, rt_max, pv[2];
-    } families[3] = {{2, 4, 8, {18, 0}}, {1, 4, 4, {18, 18}}, {2, 1, 2, {10, 10}}};
+        double fixed;
+    } families[3] = {{2, 4, 8, {18, 0}, 11600}, {1, 4, 4, {18, 18}, 11300}, {2, 1, 2, {10, 10}, 5200}};
+    const int64_t clips = std::max<int64_t>(1, est_chunks - n_frames / kSplitChunk), each = (n_frames + clips - 1) / clips;
     SplitShape best{0, 0, 0, 0, 0};
     double best_cost = 1e300;
     for (int i = 0; i < 3; ++i) {
@@ -445,13 +453,16 @@ SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t 
         const int wide = i == 0 ? (P == 3 ? 26 : 34) : f.pv[1];
         h.pv = vectors <= f.pv[0] * 256 ? f.pv[0] : wide;
         if (vectors > h.pv * 256 || split_lds(P, g, h) > (size_t)kMaxLds) continue;
-        const int64_t subs = n_frames / sf + std::max<int64_t>(est_chunks - n_frames / kSplitChunk, 0);
         for (int parts = (T16 + wr * f.rt_max - 1) / (wr * f.rt_max); parts <= (T16 + wr - 1) / wr; ++parts) {
             h.parts = parts;
             h.rt = (T16 + wr * parts - 1) / (wr * parts);
             if (h.rt == 7) h.rt = 8;
-            const int64_t rounds = (std::max<int64_t>(subs, 1) * parts + cu_count - 1) / cu_count;
-            const double cost = (double)rounds * (std::max(f.ft * NP * 16, P * 64) * (double)g.n_groups * h.rt + 4500.0);
+            const int64_t items = std::max<int64_t>(clips * ((each + sf - 1) / sf), 1) * parts;
+            const int64_t rounds = (items + cu_count - 1) / cu_count;
+            const int ring = split_ring(f.ft, h.rt), U = ring > h.rt ? ring / h.rt : 1;
+            const double multiply = std::max(f.ft * NP * 16, P * 64) * (double)g.n_groups * h.rt + f.fixed +
+                                    320.0 * h.rt * f.ft + (U > 1 && g.n_groups % U ? 3700.0 : 0.0);
+            const double cost = (double)rounds * std::max(multiply, 9500.0 + 4.2 * vectors);
             if (cost < best_cost) {
                 best_cost = cost;
                 best = h;

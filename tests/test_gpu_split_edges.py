@@ -37,3 +37,21 @@ def test_default(torch, melt, orc, prec, N, H, M, planes):
         melt.melt_set_variant(plan.handle, v, 0)
         L, _ = _gpu_forward(torch, melt, plan, wave, off)
         _check(orc, melt, plan, L, wave, off, prec, label=f"{prec} {N} {H} {M} {names[v]}")
+
+
+# front end, clips, frames each -> (frame tiles, row tiles, frame groups) of a multiply wave, as every shape timed
+SHAPES = [((400, 160, 80), 32, 998, (4, 5, 2)), ((400, 160, 80), 16, 998, (4, 3, 1)), ((400, 160, 80), 64, 2998, (4, 5, 2)),
+          ((400, 160, 80), 1, 98, (1, 2, 2)), ((120, 40, 24), 16, 3998, (4, 2, 2)), ((1024, 256, 128), 16, 122, (1, 2, 2)),
+          ((480, 161, 64), 16, 196, (1, 2, 2)), ((400, 160, 40), 16, 198, (1, 2, 2))]
+
+
+@pytest.mark.parametrize("geom,clips,frames,shape", SHAPES)
+def test_shape(torch, melt, geom, clips, frames, shape):
+    from tests.hip_graph import kernels_of
+    N, H, M = geom
+    plan = melt.MeltPlan(sample_rate=16000, n_fft=N, hop=H, n_mels=M)
+    off = torch.zeros(clips + 1, dtype=torch.int64, device="cuda")      # captured, never run
+    x = torch.empty(1, device="cuda")
+    names = kernels_of(torch, melt, lambda: melt.melt_forward(plan.handle, x, off, clips * frames, x))
+    want = "Li%dELi%dELi%dE" % shape
+    assert any("k_melt_split" in n and want in n for n in names), names
