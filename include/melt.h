@@ -279,7 +279,7 @@ melt_status melt_backward(melt_plan plan, const float *d_wave, const int64_t *d_
  *                        MELT_OUT_MFCC) rows [s * max_frames, + k) and k to
  *                        d_frames_emitted[s] (device int32 [n_streams]); under
  *                        MELT_OUT_MFCC the rows past k are written too, with no meaning.
- * A push is three kernel launches (assemble, project, keep the tail; four beyond 2048
+ * A push is three kernel launches (assemble, project, keep the tail; four beyond 1536
  * streams, and one more, the cepstrum, under MELT_OUT_MFCC) with no host synchronisation
  * and no allocation: it can be captured in a hipGraph and replayed with
  * new chunk contents (one graph per chunk length).  Pushes on one state must be ordered
