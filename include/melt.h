@@ -80,8 +80,10 @@ typedef enum {
  *              plane products run on the bfloat16 matrix cores (the others are below 2^-25 of
  *              a term), with an error against 64 bits no larger than the FP32 matrix cores'.
  *              Frames whose samples the planes cannot hold (non-finite, or of 1e31 and more) are
- *              computed with plain FP32 arithmetic.  Geometries that would
- *              pad the planes' 32-column groups by more than half (hops of a few samples) use
+ *              computed with plain FP32 arithmetic (a call of nothing else takes about four
+ *              times as long).  Geometries that would
+ *              pad the planes' 32-column groups by more than half (hops of a few samples) and
+ *              frames of fewer than 128 samples with at most 16 Mel bins use
  *              v_mfma_f32_32x32x2_f32.
  *   BF16     - bfloat16 operands
  *   FP16     - binary16 operands
@@ -257,7 +259,8 @@ melt_status stft_mel_forward_prepared(melt_plan plan, const float *d_wave, float
  *   d_grad_wave  device float32, same length as d_wave's samples up to
  *                d_clip_offsets[n_clips] (written: samples in no frame get 0), or NULL
  *   d_grad_basis device float32 [2 n_mels, n_fft] (written, not accumulated), or NULL
- * Deterministic: no floating-point atomics. */
+ * Sums that are not finite are recomputed with plain FP32 arithmetic: a call of NaN gradients
+ * takes up to six times as long.  Deterministic: no floating-point atomics. */
 melt_status melt_backward(melt_plan plan, const float *d_wave, const int64_t *d_clip_offsets,
                           int32_t n_clips, int64_t n_frames, const float *d_grad_out,
                           const float *d_proj, float *d_grad_wave, float *d_grad_basis,

@@ -8,9 +8,9 @@
 //   dW  G^T X over frames: k_bwd_dw_split below
 //
 // Measured on 32 x 10 s at 22.05 kHz, N 1024, M 128 (27 456 frames, 14.4 GFLOP each; FP32 MFMA
-// kernels before): dx 202 -> 80 us, dW 224 -> 104 us, a training step with its forward 617 ->
-// 296 us.  Relative error against 64 bits: dx 7.9e-7 -> 6.5e-7,
-// dW 7.8e-7 -> 5.2e-7.
+// kernels before): dx 202 -> 76-80 us, dW 224 -> 80-88 us, a training step with its forward 617 ->
+// 258-274 us, card to card.  Relative error against 64 bits: dx 7.9e-7 -> 6.5e-7, dW 7.8e-7 -> 5.2e-7.
+// Scaling the operands (exact for small gradients) takes 2.4 of dW's microseconds.
 #include "bwd.h"
 #include "melt_split.h"
 
@@ -195,7 +195,7 @@ melt_status launch_dx_split(const Plan &p, const float *G, const RowChunk *rows,
 // What bounds it: the matrix cores (192 MFMAs of 16 cycles per multiply wave and step).  With
 // every wave staging its share behind its multiplies (24 4-byte loads each, the VALU work of
 // the split after the last MFMA) a step took 7300 cycles for those 3072; the whole backward of
-// 27 456 frames, N = 1024, M = 128, was 182 us where it is 164.
+// 27 456 frames, N = 1024, M = 128, was 182 us where it became 164 (168 with scaled operands).
 // A wave's 64 q x 128 n of dW over frames [t0, t1) in plain FP32, on the FP32 matrix cores (4 frames
 // and 1024 cycles a step, the next one's loads in flight): where a sum on planes is not finite.
 // A NaN or infinity costs the waves that meet it about twice the time that their planes took, however

@@ -9,17 +9,19 @@
 // into the B operand of RT MFMAs.  No image.  The basis (2 KB per tile and k-group, 70 KB for 80
 // Mel bins at N = 400) sits in LDS where it fits beside the rows, else its fragments stream from
 // L2 through a ring of registers (a fragment feeds one MFMA of 64 cycles on each of four waves,
-// and L1 delivers 64 bytes a cycle: 56.9 us that way, 50.5 us from LDS).  Four more waves stage: they hold
-// the samples of the next two chunks in registers, one landed and one in flight, and write
-// the landed one to LDS between the two barriers of a chunk, while the multiply waves store.
-// Hop a multiple of 32 (a lane's 32 samples then lie in one row) and small enough that two
+// and L1 delivers 64 bytes a cycle: 56.9 us that way, 50.5 us from LDS, side by side).  Four more
+// waves stage: they hold the samples of the next two chunks in registers, one landed and one in
+// flight, and write the landed one to LDS between the two barriers of a chunk, while the multiply
+// waves store.  Hop a multiple of 32 (a lane's 32 samples then lie in one row) and small enough that two
 // chunks fit the stagers' registers.
 //
-// What bounds it: HBM (184.5 MB on 64 x 30 s, 36 us at the rate of a large copy) up to 2 or 3 row
-// tiles (24 Mel bins: 38.6 us a call), then the multiply waves' LDS reads and conversions.
-// Measured against the row-split kernel, whole calls of 64 x 30 s: 80 Mel bins 73.2 -> 50.5 us,
-// 24 Mel bins 92.6 -> 38.6 us, 128 Mel bins 81.5 -> 76.1 us, N 256 71.6 -> 49.0 us, N 512 with
-// 128 Mel bins 97.2 -> 93.2 us.
+// What bounds it: HBM (184.5 MB on 64 x 30 s, 26 us at the rate of a copy of this size and 36 at that
+// of one beyond the caches) up to 2 or 3 row tiles (24 Mel bins: 38.6 us a call), then the multiply
+// waves' LDS reads and conversions.  Measured against the row-split kernel, whole calls of 64 x 30 s:
+// 80 Mel bins 73.2 -> 50.5 us (up to 55 on other cards, where the row-split one takes 77-80), 24 Mel
+// bins 92.6 -> 38.6 us, 128 Mel bins 81.5 -> 76.1 us (eight row tiles spill four registers), N 256
+// 71.6 -> 49.0 us, N 512 with 128 Mel bins 97.2 -> 93.2 us.  Where calls are small or clips short
+// the row-split kernel is the faster: call_variant (melt_fwd.hip).
 #include "fwd_common.h"
 
 namespace melt {

@@ -24,7 +24,7 @@
 // while the multiply waves run; between the two barriers of an item they write the planes to
 // LDS while the multiply waves empty their accumulators.
 //
-// Measured (whole calls, same box): FP32 64 x 30 s, N 400, M 80: 213.5 us on FP32 MFMA, 123.4 us
+// Measured (whole calls, side by side): FP32 64 x 30 s, N 400, M 80: 213.5 us on FP32 MFMA, 123.4 us
 // here (200 TFLOP/s of the method, 1.2 PFLOP/s of products); FP32 ragged 512 clips, N 512,
 // M 128: 2.11 ms -> 1.00 ms (1.49 PFLOP/s of products); FP16X3 ragged, N 1024, M 128: 4.0 ms on
 // the frame-split kernel with 128-frame chunks -> 0.84-0.92 ms.  Relative error of the log-Mel
