@@ -426,23 +426,27 @@ struct Variant {
 // Shape of the split-plane kernel for a batch: the one with the fewest cycles in the model
 //   rounds over the CUs x max(k-groups x RT x max(MFMA, L1) + fixed, staging)
 // where a k-group of a tile costs FT NP MFMAs of 16 cycles on its SIMD or, if that is more, P KB for
-// each of the four multiply waves through the CU's 64-byte L1 port.  Clips of one length are assumed.
+// each of the four multiply waves through the CU's 64-byte L1 port.  Clips are taken to be of one length
+// where their number divides the frames, else to end half an item short.
 // 128-frame items are the cheapest per frame; 64-frame ones (four row groups) serve rows too long for
 // LDS at 128 and fill a last round better, and 32-frame ones spread a call of few frames over the chip.
 // The other terms are fitted to whole calls of 28 front ends (N 48 to 1200, 8 to 512 Mel bins, FP32 and
-// BF16X3) in 1 to 64 clips of 1 to 30 s, every shape timed: fixed, an item's barriers, hand-over and
-// first fragment reads, 320 a tile of accumulators, and 3700 where the fragment ring has to be filled
-// again (ring slots that are no divisor of the k-groups); staging, 9500 and 4.2 a vector.  The choice
-// is then within 0.3 % of the fastest shape on average, 17 % at worst; with one fixed term of 4500 and
-// a chunk too many assumed for each clip it was 11 % and up to twice as long (FP32, N 400, 80 Mel bins,
-// 32 x 10 s: 54.8 us with five row parts, 27.3 with one).
+// BF16X3) in 1 to 64 clips of 1 to 30 s, and of 11 in 16 to 300 clips of mixed lengths, every shape
+// timed: fixed, an item's barriers, hand-over and first fragment reads, 300 a tile of accumulators, and
+// 900 where the fragment ring has to be filled again (ring slots that are no divisor of the k-groups);
+// staging, 20400 and a quarter a vector.  The choice is then within 0.4 % of the fastest shape on
+// average (0.7 % for mixed lengths), 24 % at worst (BF16X3, N 800, 80 Mel bins, 16 x 4 s: 25.1 us in
+// 64-frame items of three row parts, 20.3 of two); with one fixed term of 4500 and a chunk too many
+// assumed for each clip it was 6 % and up to twice as long (FP32, N 400, 80 Mel bins, 32 x 10 s: 54.8 us
+// with five row parts, 27.3 with one).  Fitted to clips of one length alone, 61 clips of 0.5 to 12 s
+// (FP32, N 480, hop 161, 64 Mel bins) took 44.3 us in 128-frame items where 64-frame ones take 38.4.
 SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t est_chunks, int64_t n_frames) {
     const int NP = P == 3 ? 6 : 3;
     static const struct {
         int wf, ft, rt_max, pv[2];
         double fixed;
-    } families[3] = {{2, 4, 8, {18, 0}, 11600}, {1, 4, 4, {18, 18}, 11300}, {2, 1, 2, {10, 10}, 5200}};
-    const int64_t clips = std::max<int64_t>(1, est_chunks - n_frames / kSplitChunk), each = (n_frames + clips - 1) / clips;
+    } families[3] = {{2, 4, 8, {18, 0}, 17900}, {1, 4, 4, {18, 18}, 14000}, {2, 1, 2, {10, 10}, 2900}};
+    const int64_t clips = std::max<int64_t>(1, est_chunks - n_frames / kSplitChunk);
     SplitShape best{0, 0, 0, 0, 0};
     double best_cost = 1e300;
     for (int i = 0; i < 3; ++i) {
@@ -457,12 +461,14 @@ SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t 
             h.parts = parts;
             h.rt = (T16 + wr * parts - 1) / (wr * parts);
             if (h.rt == 7) h.rt = 8;
-            const int64_t items = std::max<int64_t>(clips * ((each + sf - 1) / sf), 1) * parts;
+            const int64_t whole = n_frames % clips == 0 ? clips * ((n_frames / clips + sf - 1) / sf)
+                                                        : (n_frames + clips * sf / 2 + sf - 1) / sf;
+            const int64_t items = std::max<int64_t>(whole, 1) * parts;
             const int64_t rounds = (items + cu_count - 1) / cu_count;
             const int ring = split_ring(f.ft, h.rt), U = ring > h.rt ? ring / h.rt : 1;
             const double multiply = std::max(f.ft * NP * 16, P * 64) * (double)g.n_groups * h.rt + f.fixed +
-                                    320.0 * h.rt * f.ft + (U > 1 && g.n_groups % U ? 3700.0 : 0.0);
-            const double cost = (double)rounds * std::max(multiply, 9500.0 + 4.2 * vectors);
+                                    300.0 * h.rt * f.ft + (U > 1 && g.n_groups % U ? 900.0 : 0.0);
+            const double cost = (double)rounds * std::max(multiply, 20400.0 + 0.25 * vectors);
             if (cost < best_cost) {
                 best_cost = cost;
                 best = h;

@@ -55,3 +55,15 @@ def test_shape(torch, melt, geom, clips, frames, shape):
     names = kernels_of(torch, melt, lambda: melt.melt_forward(plan.handle, x, off, clips * frames, x))
     want = "Li%dELi%dELi%dE" % shape
     assert any("k_melt_split" in n and want in n for n in names), names
+
+
+@pytest.mark.parametrize("geom,frames", [((480, 161, 64), 41154), ((480, 160, 64), 41403)])
+def test_shape_of_mixed_lengths(torch, melt, geom, frames):
+    """61 clips of 0.5 to 12 s: 64-frame items of all rows are 14 % faster than 128-frame ones."""
+    from tests.hip_graph import kernels_of
+    N, H, M = geom
+    plan = melt.MeltPlan(sample_rate=16000, n_fft=N, hop=H, n_mels=M)
+    off = torch.zeros(62, dtype=torch.int64, device="cuda")             # captured, never run
+    x = torch.empty(1, device="cuda")
+    names = kernels_of(torch, melt, lambda: melt.melt_forward(plan.handle, x, off, frames, x))
+    assert any("k_melt_split" in n and "Li4ELi2ELi1E" in n for n in names), names
