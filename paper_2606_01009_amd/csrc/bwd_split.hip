@@ -151,7 +151,11 @@ static Geometry dx_geometry(const Plan &p) { return make_geometry(2 * p.M * p.ge
 
 // Six products on the bfloat16 matrix cores take 1 / 2.6 of the time of one on the FP32 ones, so
 // the plane kernel is the faster one while its columns of 32 pad a G row by no more than that
-// (5 Mel bins and up), where a shape fits (frames of very many hops do not).
+// (5 Mel bins and up), where a shape fits (frames of very many hops do not).  d/dwave calls at that
+// line, 5 Mel bins, us, planes against FP32 MFMA: 64 x 30 s N 400 68 : 84, N 1024 66 : 85, N 128 218 : 223;
+// 32 x 10 s 24 : 24, 28 : 30, 48 : 48, N 480, hop 161 29 : 25; one 1 s clip N 400 13.9 : 17.4.  16 x 4 s at
+// N 128, hop 32, one item a workgroup, is the other way round up to 16 Mel bins (24.4 : 17.2 at 5,
+// 24.7 : 22.5 at 16).
 bool dx_split_fits(const Plan &p) {
     const Geometry g = dx_geometry(p);
     return p.H <= 256 && 2 * g.Hp <= 5 * ((2 * p.M + 7) / 8 * 8) &&

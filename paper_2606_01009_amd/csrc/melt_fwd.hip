@@ -479,8 +479,13 @@ SplitShape split_shape(const Geometry &g, int P, int T16, int cu_count, int64_t 
 }
 
 // The split-plane kernel takes a plan if a shape fits LDS and its k-groups of 32 do not pad the
-// frame by more than half (short hops do: at hop 8 three of four columns would be padding),
-// where FP32 MFMA on k-groups of 8 is the faster product again.
+// frame by more than half (short hops do: at hop 8 three of four columns would be padding).
+// 32 x 10 s, us, planes against the kernels on k-groups of 8 and 16.  Inside the line: FP32 N 400, hop 22,
+// 80 Mel bins 209 : 339, 16 Mel bins 75 : 109; N 128, hop 20, 16 Mel bins 53 : 49.  Beyond it BF16X3
+// loses where Mel bins are few or hops shorter still: N 400, hop 20, 16 Mel bins 63 : 52, 80 Mel bins
+// 144 : 218; hop 12 140 : 66 and 332 : 273; N 128, hop 16, 16 Mel bins 50 : 30.  FP32 gains there down to
+// hop 16 or so (hop 20 222 : 354, hop 12 540 : 593; 16 Mel bins 77 : 103, 176 : 174, N 128, hop 16
+// 61 : 51): one line for both is drawn on the safe side.
 static bool split_fits(const Plan &p) {
     return split_planes(p) && p.geoS.n_groups * 32 <= p.N + p.N / 2 + 32 && p.geoS.n_groups <= 512 &&
            split_shape(p.geoS, split_planes(p), (p.M + 7) / 8, p.cu_count, 1 << 20, (int64_t)kSplitChunk << 20).parts > 0;
